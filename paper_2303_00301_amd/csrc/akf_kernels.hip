@@ -29,6 +29,7 @@
 
 #include "akf_team.hpp"
 #include "akf_internal.h"
+#include "akf_wave.hpp"
 
 namespace akf {
 
@@ -606,15 +607,6 @@ __device__ __forceinline__ void vec_load(double* s, const double* __restrict__ g
   if (tid < D) s[tid] = (tid < d && g) ? g[tid] : 0.0;
 }
 
-// Load a rows x cols user matrix (row-major) into an LDS buffer, zero padded.
-template <int D>
-__device__ __forceinline__ void lds_load_rect(double* s, const double* __restrict__ g, int rows,
-                                              int cols) {
-  for (int e = threadIdx.x; e < D * D; e += Cfg<D>::NT) {
-    const int i = e / D, j = e % D;
-    s[i * Cfg<D>::LD + j] = (i < rows && j < cols) ? g[i * cols + j] : 0.0;
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Filter, phase 1: fold the elements of one block.
@@ -628,9 +620,8 @@ __device__ __forceinline__ void lds_load_rect(double* s, const double* __restric
 // which is the element combine of App. A with the raw element of step t
 // written in terms of F, Q and Omega_t.  The block containing t = 0 starts
 // from the prior (A = 0 throughout).  Output element layout: ElemLayout.
-// GH (general observation y_t = H x_t + N(0, R), D <= 32): S = H Pp H' + R,
-// Pp S^{-1} Pp -> (H Pp)' S^{-1} (H Pp), T' S^{-1} T -> (H T)' S^{-1} (H T),
-// w = y_t - H mu.
+// Below D = 64 a team is one wave and runs wave_fold, which also takes general
+// observations y_t = H x_t + N(0, R).
 // ---------------------------------------------------------------------------
 // FIRST: the block contains t = 0 (its element has A = 0 and J = 0).  The
 // two cases are compiled separately so that A and T hold no registers across
@@ -638,18 +629,16 @@ __device__ __forceinline__ void lds_load_rect(double* s, const double* __restric
 template <int D, int OBS, bool FIRST, int U = 4>
 __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterArgs& P, int item) {
   using C = Cfg<D>;
-  constexpr bool GH = (OBS == OBS_GH);
-  static_assert(!GH || D <= 32, "general observation matrices need D <= 32");
+  static_assert(D == 64 && OBS != OBS_GH, "narrower teams are one wave (akf_wave.hpp)");
   extern __shared__ double lds[];
   double* sF = lds;
   double* B1 = sF + C::MAT;
   double* B2 = B1 + C::MAT;
   double* B3 = B2 + C::MAT;
-  double* sH = B3 + C::MAT;                // GH only
-  double* vb = sH + (GH ? C::MAT : 0);     // b
+  double* vb = B3 + C::MAT;                // b
   double* veta = vb + D;                   // eta
   double* vmu = veta + D;                  // mu
-  double* vw = vmu + D;                    // omega - mu  (GH: y - H mu)
+  double* vw = vmu + D;                    // omega - mu
   double* vs = vw + D;                     // S^{-1} w
   double* vom = vs + D;                    // diagonal Omega_t
   double* red = vom + D;
@@ -658,12 +647,10 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
   constexpr bool first = FIRST;
   // lc: log of the normaliser, the sum over the block's steps of the
   // x_prev-independent part of log N(omega_t; T x_prev + mu, S),
-  // -(dobs log 2 pi + log det S + w' S^{-1} w) / 2; log det S and this thread's
+  // -(d log 2 pi + log det S + w' S^{-1} w) / 2; log det S and this thread's
   // share of w' S^{-1} w are accumulated, the team sum is taken once at the end
   double ld_sum = 0.0, q_part = 0.0;
-  const int dobs = GH ? P.dyo : d;
   if (!P.Ft) lds_load_mat<D>(sF, M.F, d);
-  if (GH) lds_load_rect<D>(sH, P.Ho, P.dyo, d);
   if (tid < D) {
     vb[tid] = 0.0;
     veta[tid] = 0.0;
@@ -688,24 +675,15 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
       }
       rm_load<D>(Pp, M.Q, d, d);  // issued early: its latency overlaps F C
       rm_stage<D>(Cc, B1);
-      // below D = 64 F C and T = F A are formed together; at D = 64 the
-      // register file cannot hold both through the next product
-      constexpr bool PAIR = (D < 64);
-      if (first || !PAIR) {
-        team_sync();
-        gemm<D, false, false, false, U>(R1, sF, B1);  // F C
-      } else {
-        rm_stage<D>(A, B3);
-        team_sync();
-        gemm2<D, false, false, U>(R1, T, sF, B1, B3);  // F C and T = F A
-      }
+      team_sync();
+      gemm<D, false, false, false, U>(R1, sF, B1);  // F C
       team_sync();
       rm_stage<D>(R1, B1);
       team_sync();
       gemm<D, false, true, true, U>(Pp, B1, sF);  // Q + (F C) F'
       matvec<D, false>(vmu, sF, vb);
       if (tid < d && bt) vmu[tid] += bt[tid];
-      if (!first && !PAIR) {
+      if (!first) {
         rm_stage<D>(A, B1);
         team_sync();
         gemm<D, false, false, false, U>(T, sF, B1);  // T = F A
@@ -732,7 +710,7 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
       team_sync();
       // S^{-1} Pp and S^{-1} T formed together (not in the batched D = 64
       // fold, U = 4, whose register allocation spills more with the pair)
-      constexpr bool PAIR2 = !(D == 64 && U < 8);
+      constexpr bool PAIR2 = U >= 8;
       if (first || !PAIR2)
         gemm<D, false, false, false, U>(Cc, B2, B1);  // S^{-1} Pp
       else
@@ -746,7 +724,7 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
         rm_stage<D>(R1, B1);
         team_sync();
         // fully unrolled where the register budget still allows it
-        gemm<D, true, false, true, (OBS == OBS_DIAG && D == 64) ? D / 4 : U>(J, B3, B1);  // J += T' S^{-1} T
+        gemm<D, true, false, true, D / 4>(J, B3, B1);  // J += T' S^{-1} T
         AKF_RM_FOR(D, q, r, i, j) A.t[q][r] = vom[i] * R1.t[q][r];
         matvec<D, true>(veta, B3, vs, veta);  // eta += T' S^{-1} w
       }
@@ -754,61 +732,41 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
       rm_symmetrise<D>(Cc, B2);
       continue;
     }
-    // B1 <- Mo (Pp, or H Pp); R2 <- S; vw <- innovation
     rm_stage<D>(Pp, B1);
-    if constexpr (GH) {
-      team_sync();
-      gemm<D, false, false, false, U>(R1, sH, B1);  // H Pp
-      team_sync();
-      rm_stage<D>(R1, B1);
-      team_sync();
-      gemm<D, false, true, false, U>(R2, B1, sH);  // H Pp H'
-      rm_add_load<D>(R2, P.Ro, P.dyo, P.dyo);
-      matvec<D, false>(vw, sH, vmu);
-      team_sync();
-      if (tid < D) vw[tid] = (tid < P.dyo) ? P.yo[(int64_t)t * P.dyo + tid] - vw[tid] : 0.0;
+    R2 = Pp;
+    if (P.Omd) {
+      rm_add_load<D>(R2, P.Omd, d, d);
     } else {
-      R2 = Pp;
-      if (P.Omd) {
-        rm_add_load<D>(R2, P.Omd, d, d);
-      } else {
-        const double* Om = P.Om + (int64_t)t * d;
-        AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) R2.t[q][r] += Om[i];
-      }
-      if (tid < D) vw[tid] = (tid < d) ? P.om[(int64_t)t * d + tid] - vmu[tid] : 0.0;
+      const double* Om = P.Om + (int64_t)t * d;
+      AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) R2.t[q][r] += Om[i];
     }
+    if (tid < D) vw[tid] = (tid < d) ? P.om[(int64_t)t * d + tid] - vmu[tid] : 0.0;
     double logdet;
-    ok = spd_inv<D>(R2, dobs, B2, &logdet) && ok;  // R2 = S^{-1}
+    ok = spd_inv<D>(R2, d, B2, &logdet) && ok;  // R2 = S^{-1}
     rm_stage<D>(R2, B3);
     team_sync();
-    gemm<D, false, false, false, U>(R1, B3, B1);  // S^{-1} Mo
+    gemm<D, false, false, false, U>(R1, B3, B1);  // S^{-1} Pp
     matvec<D, false>(vs, B3, vw);              // S^{-1} w
     ld_sum += logdet;
     if (tid < D) q_part += vw[tid] * vs[tid];
     team_sync();
     rm_stage<D>(R1, B2);
     team_sync();
-    gemm<D, true, false, false, U>(Cc, B1, B2);  // Mo' S^{-1} Mo
-    rm_rsub<D>(Cc, Pp);  // C = Pp - Mo' S^{-1} Mo
-    matvec<D, true>(vb, B1, vs, vmu);  // b = mu + Mo' S^{-1} w
+    gemm<D, true, false, false, U>(Cc, B1, B2);  // Mo' S^{-1} Pp
+    rm_rsub<D>(Cc, Pp);  // C = Pp - Mo' S^{-1} Pp
+    matvec<D, true>(vb, B1, vs, vmu);  // b = mu + Pp S^{-1} w
     if (!first) {
       team_sync();
-      rm_stage<D>(T, B2);  // B2 <- Mt (T, or H T)
-      if constexpr (GH) {
-        team_sync();
-        gemm<D, false, false, false, U>(R1, sH, B2);  // H T
-        team_sync();
-        rm_stage<D>(R1, B2);
-      }
+      rm_stage<D>(T, B2);
       team_sync();
-      gemm<D, false, false, false, U>(R1, B3, B2);  // S^{-1} Mt
+      gemm<D, false, false, false, U>(R1, B3, B2);  // S^{-1} T
       team_sync();
       rm_stage<D>(R1, B3);
       team_sync();
-      gemm<D, true, false, true, U>(J, B2, B3);   // J += Mt' S^{-1} Mt
-      gemm<D, true, false, false, U>(A, B1, B3);  // Mo' S^{-1} Mt
-      rm_rsub<D>(A, T);  // A = T - Mo' S^{-1} Mt
-      matvec<D, true>(veta, B2, vs, veta);  // eta += Mt' S^{-1} w
+      gemm<D, true, false, true, U>(J, B2, B3);   // J += T' S^{-1} T
+      gemm<D, true, false, false, U>(A, B1, B3);  // Pp S^{-1} T
+      rm_rsub<D>(A, T);  // A = T - Pp S^{-1} T
+      matvec<D, true>(veta, B2, vs, veta);  // eta += T' S^{-1} w
     } else if (first) {
       rm_zero<D>(A);
     }
@@ -829,22 +787,29 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
     out[ElemLayout<D>::eta + tid] = veta[tid];
   }
   const double q = team_sum<D>(q_part, red);
-  if (tid == 0) out[ElemLayout<D>::lc] = -0.5 * ((s1 - s0) * dobs * LOG2PI + ld_sum + q);
+  if (tid == 0) out[ElemLayout<D>::lc] = -0.5 * ((s1 - s0) * d * LOG2PI + ld_sum + q);
 }
 
 template <int D, int OBS, int U = 4>
 __device__ __forceinline__ void filter_fold_body(const KModel& M, const FilterArgs& P, int item) {
-  if (item == 0)
-    filter_fold_impl<D, OBS, true, U>(M, P, item);
-  else
-    filter_fold_impl<D, OBS, false, U>(M, P, item);
+  if constexpr (D <= 32) {
+    if (item == 0)
+      wave_fold<D, OBS, true>(M, P, item);
+    else
+      wave_fold<D, OBS, false>(M, P, item);
+  } else {
+    if (item == 0)
+      filter_fold_impl<D, OBS, true, U>(M, P, item);
+    else
+      filter_fold_impl<D, OBS, false, U>(M, P, item);
+  }
 }
 
 template <int D, int OBS>
 __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_fold(KModel M, FilterArgs P) {
   // k-steps per unrolled GEMM iteration: the most that fits the register budget
   // without spills (the D = 64 diagonal fold holds 512 registers per lane)
-  constexpr int U = (D < 64) ? D / 4 : (OBS == OBS_DIAG ? 8 : 4);
+  constexpr int U = OBS == OBS_DIAG ? 8 : 4;
   if (gate_shut(M.gate)) return;
   filter_fold_body<D, OBS, U>(M, P, blockIdx.x);
 }
@@ -874,105 +839,109 @@ __device__ __forceinline__ void filter_combine(const KModel& M, const double* __
                                                const double* __restrict__ ej,
                                                double* __restrict__ out, int* status,
                                                int fail_bit) {
-  using C = Cfg<D>;
-  using EL = ElemLayout<D>;
-  extern __shared__ double lds[];
-  double* S0 = lds;
-  double* S1 = S0 + C::MAT;
-  double* S2 = S1 + C::MAT;
-  double* S3 = S2 + C::MAT;
-  double* vbi = S3 + C::MAT;
-  double* vc = vbi + D;
-  double* vw = vc + D;
-  double* vk = vw + D;
-  double* red = vk + D;
-  const int tid = threadIdx.x, d = M.d;
-  bool ok = true;
-  double ld;
-  RM<D> R1, R2, R3;
-  rm_load<D>(R1, ei + EL::C, D, d);
-  lds_load_pad<D, G>(S1, ej + EL::J);
-  if (tid < D) vbi[tid] = ei[EL::b + tid];
-  // the operands needed later are fetched now, so their HBM latency overlaps
-  // the factorisations (no global stores precede the barriers until then)
-  RM<D> Ai, Ji, Aj, Cj;
-  rm_load<D>(Ai, ei + EL::A, D, D);
-  rm_load<D>(Ji, ei + EL::J, D, D);
-  rm_load<D>(Aj, ej + EL::A, D, D);
-  rm_load<D>(Cj, ej + EL::C, D, D);
-  ok = chol_reg<D>(R1, d, S3, &ld) && ok;  // R1 = L
-  rm_stage<D>(R1, S0);                        // S0 = L
-  team_sync();
-  gemm<D, false, false, false, U>(R2, S1, S0);  // J_j L
-  rm_stage<D>(R2, S2);
-  team_sync();
-  gemm<D, true, false, false, U>(R2, S0, S2);  // L' J_j L
-  AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) R2.t[q][r] += 1.0;
-  ok = spd_inv<D>(R2, d, S3, &ld) && ok;  // W^{-1}
-  const double ldW = ld;
-  rm_stage<D>(R2, S2);
-  team_sync();
-  gemm<D, false, false, false, U>(R3, S0, S2);  // L W^{-1}
-  rm_stage<D>(R3, S3);
-  team_sync();
-  gemm<D, false, true, false, U>(R2, S3, S0);  // M = L W^{-1} L'
-  matvec<D, false>(vc, S1, vbi);            // J_j b_i
-  team_sync();
-  rm_stage<D>(R2, S2);  // S2 = M
-  if (tid < D) vc[tid] = ej[EL::eta + tid] - vc[tid];
-  team_sync();
-  matvec<D, false>(vw, S2, vc);     // w = M c
-  const double lc = ei[EL::lc] + ej[EL::lc] - 0.5 * ldW +
-                    0.5 * team_sum<D>(tid < D ? vbi[tid] * (ej[EL::eta + tid] + vc[tid]) +
-                                                    vc[tid] * vw[tid]
-                                              : 0.0,
-                                      red);
-  if constexpr (SIDE != 2) {
-    rm_stage<D>(Ai, S0);  // S0 = A_i
+  if constexpr (D <= 32) {
+    wave_combine<D, SIDE>(M, ei, ej, out, status, fail_bit);
+  } else {
+    using C = Cfg<D>;
+    using EL = ElemLayout<D>;
+    extern __shared__ double lds[];
+    double* S0 = lds;
+    double* S1 = S0 + C::MAT;
+    double* S2 = S1 + C::MAT;
+    double* S3 = S2 + C::MAT;
+    double* vbi = S3 + C::MAT;
+    double* vc = vbi + D;
+    double* vw = vc + D;
+    double* vk = vw + D;
+    double* red = vk + D;
+    const int tid = threadIdx.x, d = M.d;
+    bool ok = true;
+    double ld;
+    RM<D> R1, R2, R3;
+    rm_load<D>(R1, ei + EL::C, D, d);
+    lds_load_pad<D, G>(S1, ej + EL::J);
+    if (tid < D) vbi[tid] = ei[EL::b + tid];
+    // the operands needed later are fetched now, so their HBM latency overlaps
+    // the factorisations (no global stores precede the barriers until then)
+    RM<D> Ai, Ji, Aj, Cj;
+    rm_load<D>(Ai, ei + EL::A, D, D);
+    rm_load<D>(Ji, ei + EL::J, D, D);
+    rm_load<D>(Aj, ej + EL::A, D, D);
+    rm_load<D>(Cj, ej + EL::C, D, D);
+    ok = chol_reg<D>(R1, d, S3, &ld) && ok;  // R1 = L
+    rm_stage<D>(R1, S0);                        // S0 = L
     team_sync();
-    matvec<D, false>(vk, S1, vw);              // J_j w
-    gemm<D, false, false, false, U>(R1, S1, S0);  // P = J_j A_i
-    rm_stage<D>(R1, S3);                       // S3 = P
+    gemm<D, false, false, false, U>(R2, S1, S0);  // J_j L
+    rm_stage<D>(R2, S2);
     team_sync();
-    if (tid < D) vk[tid] = vc[tid] - vk[tid];  // c - J_j M c
-    gemm<D, false, false, false, U>(R2, S2, S3);  // M P
-    R3 = Ai;
-    rm_axpy<D>(R3, -1.0, R2);  // Z1 = A_i - M P
+    gemm<D, true, false, false, U>(R2, S0, S2);  // L' J_j L
+    AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) R2.t[q][r] += 1.0;
+    ok = spd_inv<D>(R2, d, S3, &ld) && ok;  // W^{-1}
+    const double ldW = ld;
+    rm_stage<D>(R2, S2);
     team_sync();
-    matvec<D, true>(out + EL::eta, S0, vk, ei + EL::eta);  // eta = A_i' (c - J_j M c) + eta_i
-    rm_stage<D>(R3, S1);  // S1 = Z1
+    gemm<D, false, false, false, U>(R3, S0, S2);  // L W^{-1}
+    rm_stage<D>(R3, S3);
     team_sync();
-    gemm<D, true, false, false, U>(R1, S1, S3);  // J = Z1' P + J_i = A_i'P - P'MP + J_i
-    rm_axpy<D>(R1, 1.0, Ji);
-    rm_symmetrise<D>(R1, S3);  // ends synchronised
-    rm_store<D>(R1, out + EL::J, D, D);
+    gemm<D, false, true, false, U>(R2, S3, S0);  // M = L W^{-1} L'
+    matvec<D, false>(vc, S1, vbi);            // J_j b_i
+    team_sync();
+    rm_stage<D>(R2, S2);  // S2 = M
+    if (tid < D) vc[tid] = ej[EL::eta + tid] - vc[tid];
+    team_sync();
+    matvec<D, false>(vw, S2, vc);     // w = M c
+    const double lc = ei[EL::lc] + ej[EL::lc] - 0.5 * ldW +
+                      0.5 * team_sum<D>(tid < D ? vbi[tid] * (ej[EL::eta + tid] + vc[tid]) +
+                                                      vc[tid] * vw[tid]
+                                                : 0.0,
+                                        red);
+    if constexpr (SIDE != 2) {
+      rm_stage<D>(Ai, S0);  // S0 = A_i
+      team_sync();
+      matvec<D, false>(vk, S1, vw);              // J_j w
+      gemm<D, false, false, false, U>(R1, S1, S0);  // P = J_j A_i
+      rm_stage<D>(R1, S3);                       // S3 = P
+      team_sync();
+      if (tid < D) vk[tid] = vc[tid] - vk[tid];  // c - J_j M c
+      gemm<D, false, false, false, U>(R2, S2, S3);  // M P
+      R3 = Ai;
+      rm_axpy<D>(R3, -1.0, R2);  // Z1 = A_i - M P
+      team_sync();
+      matvec<D, true>(out + EL::eta, S0, vk, ei + EL::eta);  // eta = A_i' (c - J_j M c) + eta_i
+      rm_stage<D>(R3, S1);  // S1 = Z1
+      team_sync();
+      gemm<D, true, false, false, U>(R1, S1, S3);  // J = Z1' P + J_i = A_i'P - P'MP + J_i
+      rm_axpy<D>(R1, 1.0, Ji);
+      rm_symmetrise<D>(R1, S3);  // ends synchronised
+      rm_store<D>(R1, out + EL::J, D, D);
+    }
+    rm_stage<D>(Aj, S0);  // S0 = A_j
+    if (tid < D) vw[tid] += vbi[tid];
+    team_sync();
+    // both sides: A_j Z1 and A_j M formed together (not in the batched D = 64
+    // up-sweep, U = 4, whose register allocation spills more with the pair)
+    constexpr bool PAIR = (SIDE == 0) && !(D == 64 && U < 8);
+    if constexpr (PAIR) {
+      gemm2<D, false, false, U>(R3, R2, S0, S1, S2);  // A = A_j Z1, A_j M
+      rm_store<D>(R3, out + EL::A, D, D);
+    } else if constexpr (SIDE != 2) {
+      gemm<D, false, false, false, U>(R3, S0, S1);  // A = A_j Z1
+      rm_store<D>(R3, out + EL::A, D, D);
+    }
+    if constexpr (SIDE != 1) {
+      if constexpr (!PAIR) gemm<D, false, false, false, U>(R2, S0, S2);  // A_j M
+      matvec<D, false>(vc, S0, vw);              // A_j (b_i + M c)
+      rm_stage<D>(R2, S3);
+      team_sync();
+      gemm<D, false, true, false, U>(R3, S3, S0);  // A_j M A_j'
+      rm_axpy<D>(R3, 1.0, Cj);
+      if (tid < D) out[EL::b + tid] = vc[tid] + ej[EL::b + tid];
+      if (tid == 0) out[EL::lc] = lc;
+      rm_symmetrise<D>(R3, S1);
+      rm_store<D>(R3, out + EL::C, D, D);
+    }
+    if (!ok && tid == 0) flag_status(status, fail_bit);
   }
-  rm_stage<D>(Aj, S0);  // S0 = A_j
-  if (tid < D) vw[tid] += vbi[tid];
-  team_sync();
-  // both sides: A_j Z1 and A_j M formed together (not in the batched D = 64
-  // up-sweep, U = 4, whose register allocation spills more with the pair)
-  constexpr bool PAIR = (SIDE == 0) && !(D == 64 && U < 8);
-  if constexpr (PAIR) {
-    gemm2<D, false, false, U>(R3, R2, S0, S1, S2);  // A = A_j Z1, A_j M
-    rm_store<D>(R3, out + EL::A, D, D);
-  } else if constexpr (SIDE != 2) {
-    gemm<D, false, false, false, U>(R3, S0, S1);  // A = A_j Z1
-    rm_store<D>(R3, out + EL::A, D, D);
-  }
-  if constexpr (SIDE != 1) {
-    if constexpr (!PAIR) gemm<D, false, false, false, U>(R2, S0, S2);  // A_j M
-    matvec<D, false>(vc, S0, vw);              // A_j (b_i + M c)
-    rm_stage<D>(R2, S3);
-    team_sync();
-    gemm<D, false, true, false, U>(R3, S3, S0);  // A_j M A_j'
-    rm_axpy<D>(R3, 1.0, Cj);
-    if (tid < D) out[EL::b + tid] = vc[tid] + ej[EL::b + tid];
-    if (tid == 0) out[EL::lc] = lc;
-    rm_symmetrise<D>(R3, S1);
-    rm_store<D>(R3, out + EL::C, D, D);
-  }
-  if (!ok && tid == 0) flag_status(status, fail_bit);
 }
 
 template <int D, int U = 4, int G = D * D / Cfg<D>::NT>
@@ -1035,67 +1004,71 @@ __device__ __forceinline__ void moment_combine(const KModel& M, const double* Pi
                                                double* Pout, double* mout, int* status,
                                                int fail_bit, const double* lcin = nullptr,
                                                double* lcout = nullptr) {
-  using C = Cfg<D>;
-  using EL = ElemLayout<D>;
-  extern __shared__ double lds[];
-  double* S0 = lds;
-  double* S1 = S0 + C::MAT;
-  double* S2 = S1 + C::MAT;
-  double* S3 = S2 + C::MAT;
-  double* vm = S3 + C::MAT;
-  double* vc = vm + D;
-  double* vz = vc + D;
-  double* vw = vz + D;
-  double* red = vw + D;
-  const int tid = threadIdx.x, d = M.d;
-  bool ok = true;
-  double ld;
-  RM<D> R1, R2, Ae, Ce;
-  rm_load<D>(R1, Pin, D, d);
-  lds_load_pad<D>(S1, el + EL::J);
-  if (tid < D) vm[tid] = min_[tid];
-  rm_load<D>(Ae, el + EL::A, D, D);  // needed after the factorisations
-  rm_load<D>(Ce, el + EL::C, D, D);
-  ok = chol_reg<D>(R1, d, S3, &ld) && ok;  // R1 = L
-  rm_stage<D>(R1, S0);
-  team_sync();
-  gemm<D, false, false, false, U>(R2, S1, S0);  // J L
-  rm_stage<D>(R2, S2);
-  team_sync();
-  gemm<D, true, false, false, U>(R2, S0, S2);  // L' J L
-  AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) R2.t[q][r] += 1.0;
-  ok = spd_inv<D>(R2, d, S3, &ld) && ok;  // W^{-1}
-  const double ldW = ld;
-  rm_stage<D>(R2, S2);
-  team_sync();
-  gemm<D, false, false, false, U>(R1, S0, S2);  // L W^{-1}
-  rm_stage<D>(R1, S3);
-  team_sync();
-  gemm<D, false, true, false, U>(R2, S3, S0);  // M
-  matvec<D, false>(vc, S1, vm);             // J m
-  team_sync();
-  rm_stage<D>(R2, S2);  // S2 = M
-  if (tid < D) vc[tid] = el[EL::eta + tid] - vc[tid];
-  rm_stage<D>(Ae, S3);  // S3 = A
-  team_sync();
-  matvec<D, false>(vw, S2, vc);              // M (eta - J m)
-  if (lcout) {
-    const double q = team_sum<D>(
-        tid < D ? vm[tid] * (el[EL::eta + tid] + vc[tid]) + vc[tid] * vw[tid] : 0.0, red);
-    if (tid == 0) *lcout = *lcin + el[EL::lc] - 0.5 * ldW + 0.5 * q;
+  if constexpr (D <= 32) {
+    wave_moment<D>(M, Pin, min_, el, Pout, mout, status, fail_bit, lcin, lcout);
+  } else {
+    using C = Cfg<D>;
+    using EL = ElemLayout<D>;
+    extern __shared__ double lds[];
+    double* S0 = lds;
+    double* S1 = S0 + C::MAT;
+    double* S2 = S1 + C::MAT;
+    double* S3 = S2 + C::MAT;
+    double* vm = S3 + C::MAT;
+    double* vc = vm + D;
+    double* vz = vc + D;
+    double* vw = vz + D;
+    double* red = vw + D;
+    const int tid = threadIdx.x, d = M.d;
+    bool ok = true;
+    double ld;
+    RM<D> R1, R2, Ae, Ce;
+    rm_load<D>(R1, Pin, D, d);
+    lds_load_pad<D>(S1, el + EL::J);
+    if (tid < D) vm[tid] = min_[tid];
+    rm_load<D>(Ae, el + EL::A, D, D);  // needed after the factorisations
+    rm_load<D>(Ce, el + EL::C, D, D);
+    ok = chol_reg<D>(R1, d, S3, &ld) && ok;  // R1 = L
+    rm_stage<D>(R1, S0);
+    team_sync();
+    gemm<D, false, false, false, U>(R2, S1, S0);  // J L
+    rm_stage<D>(R2, S2);
+    team_sync();
+    gemm<D, true, false, false, U>(R2, S0, S2);  // L' J L
+    AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) R2.t[q][r] += 1.0;
+    ok = spd_inv<D>(R2, d, S3, &ld) && ok;  // W^{-1}
+    const double ldW = ld;
+    rm_stage<D>(R2, S2);
+    team_sync();
+    gemm<D, false, false, false, U>(R1, S0, S2);  // L W^{-1}
+    rm_stage<D>(R1, S3);
+    team_sync();
+    gemm<D, false, true, false, U>(R2, S3, S0);  // M
+    matvec<D, false>(vc, S1, vm);             // J m
+    team_sync();
+    rm_stage<D>(R2, S2);  // S2 = M
+    if (tid < D) vc[tid] = el[EL::eta + tid] - vc[tid];
+    rm_stage<D>(Ae, S3);  // S3 = A
+    team_sync();
+    matvec<D, false>(vw, S2, vc);              // M (eta - J m)
+    if (lcout) {
+      const double q = team_sum<D>(
+          tid < D ? vm[tid] * (el[EL::eta + tid] + vc[tid]) + vc[tid] * vw[tid] : 0.0, red);
+      if (tid == 0) *lcout = *lcin + el[EL::lc] - 0.5 * ldW + 0.5 * q;
+    }
+    gemm<D, false, false, false, U>(R1, S3, S2);  // A M
+    rm_stage<D>(R1, S0);
+    team_sync();
+    if (tid < D) vw[tid] += vm[tid];
+    gemm<D, false, true, false, U>(R2, S0, S3);  // A M A'
+    rm_axpy<D>(R2, 1.0, Ce);
+    team_sync();
+    matvec<D, false>(vz, S3, vw);
+    if (tid < D) mout[tid] = vz[tid] + el[EL::b + tid];
+    rm_symmetrise<D>(R2, S1);
+    rm_store<D>(R2, Pout, D, D);
+    if (!ok && tid == 0) flag_status(status, fail_bit);
   }
-  gemm<D, false, false, false, U>(R1, S3, S2);  // A M
-  rm_stage<D>(R1, S0);
-  team_sync();
-  if (tid < D) vw[tid] += vm[tid];
-  gemm<D, false, true, false, U>(R2, S0, S3);  // A M A'
-  rm_axpy<D>(R2, 1.0, Ce);
-  team_sync();
-  matvec<D, false>(vz, S3, vw);
-  if (tid < D) mout[tid] = vz[tid] + el[EL::b + tid];
-  rm_symmetrise<D>(R2, S1);
-  rm_store<D>(R2, Pout, D, D);
-  if (!ok && tid == 0) flag_status(status, fail_bit);
 }
 
 
@@ -1170,18 +1143,16 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_down(KModel M, TreeArgs T
 // Writes m^f_t, P^f_t (when requested) and ell_t.
 // ---------------------------------------------------------------------------
 template <int D, int OBS, int U = 4>
-__device__ __forceinline__ void filter_final_body(const KModel& M, const FilterArgs& P, int item) {
+__device__ __forceinline__ void filter_final_impl(const KModel& M, const FilterArgs& P, int item) {
   using C = Cfg<D>;
   using PL = PrefLayout<D>;
-  constexpr bool GH = (OBS == OBS_GH);
-  static_assert(!GH || D <= 32, "general observation matrices need D <= 32");
+  static_assert(D == 64 && OBS != OBS_GH, "narrower teams are one wave (akf_wave.hpp)");
   extern __shared__ double lds[];
   double* sF = lds;
   double* B1 = sF + C::MAT;
   double* B2 = B1 + C::MAT;
   double* B3 = B2 + C::MAT;
-  double* sH = B3 + C::MAT;  // GH only
-  double* vm = sH + (GH ? C::MAT : 0);
+  double* vm = B3 + C::MAT;
   double* vmp = vm + D;
   double* vw = vmp + D;
   double* vs = vw + D;
@@ -1190,8 +1161,6 @@ __device__ __forceinline__ void filter_final_body(const KModel& M, const FilterA
   const int blk = item, tid = threadIdx.x, d = M.d;
   const int s0 = blk * P.B, s1 = min(M.N, s0 + P.B);
   if (!P.Ft) lds_load_mat<D>(sF, M.F, d);
-  if (GH) lds_load_rect<D>(sH, P.Ho, P.dyo, d);
-  const int dobs = GH ? P.dyo : d;
   RM<D> Pm, Pp, T, R2;
   if (s0 > 0) {
     if (P.pre_elem) {
@@ -1262,40 +1231,27 @@ __device__ __forceinline__ void filter_final_body(const KModel& M, const FilterA
       continue;
     }
     rm_stage<D>(Pp, B1);
-    if constexpr (GH) {
-      team_sync();
-      gemm<D, false, false, false, U>(T, sH, B1);  // H Pp
-      team_sync();
-      rm_stage<D>(T, B1);
-      team_sync();
-      gemm<D, false, true, false, U>(R2, B1, sH);
-      rm_add_load<D>(R2, P.Ro, P.dyo, P.dyo);
-      matvec<D, false>(vw, sH, vmp);
-      team_sync();
-      if (tid < D) vw[tid] = (tid < P.dyo) ? P.yo[(int64_t)t * P.dyo + tid] - vw[tid] : 0.0;
+    R2 = Pp;
+    if (P.Omd) {
+      rm_add_load<D>(R2, P.Omd, d, d);
     } else {
-      R2 = Pp;
-      if (P.Omd) {
-        rm_add_load<D>(R2, P.Omd, d, d);
-      } else {
-        const double* Om = P.Om + (int64_t)t * d;
-        AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) R2.t[q][r] += Om[i];
-      }
-      if (tid < D) vw[tid] = (tid < d) ? P.om[(int64_t)t * d + tid] - vmp[tid] : 0.0;
+      const double* Om = P.Om + (int64_t)t * d;
+      AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) R2.t[q][r] += Om[i];
     }
+    if (tid < D) vw[tid] = (tid < d) ? P.om[(int64_t)t * d + tid] - vmp[tid] : 0.0;
     double logdet;
-    ok = spd_inv<D>(R2, dobs, B2, &logdet) && ok;
+    ok = spd_inv<D>(R2, d, B2, &logdet) && ok;
     rm_stage<D>(R2, B3);
     team_sync();
-    gemm<D, false, false, false, U>(T, B3, B1);  // S^{-1} Mo
+    gemm<D, false, false, false, U>(T, B3, B1);  // S^{-1} Pp
     matvec<D, false>(vs, B3, vw);
     team_sync();
     rm_stage<D>(T, B2);
     const double rr = team_sum<D>(tid < D ? vw[tid] * vs[tid] : 0.0, red);
-    gemm<D, true, false, false, U>(Pm, B1, B2);  // Mo' S^{-1} Mo
-    rm_rsub<D>(Pm, Pp);  // P^f = Pp - Mo' S^{-1} Mo
-    matvec<D, true>(vm, B1, vs, vmp);  // m^f = m^p + Mo' S^{-1} w
-    if (tid == 0) P.ell[t] = -0.5 * (dobs * LOG2PI + logdet + rr);
+    gemm<D, true, false, false, U>(Pm, B1, B2);  // Mo' S^{-1} Pp
+    rm_rsub<D>(Pm, Pp);  // P^f = Pp - Mo' S^{-1} Pp
+    matvec<D, true>(vm, B1, vs, vmp);  // m^f = m^p + Pp S^{-1} w
+    if (tid == 0) P.ell[t] = -0.5 * (d * LOG2PI + logdet + rr);
     rm_symmetrise<D>(Pm, B2);
     if (P.mf) {
       if (tid < d) P.mf[(int64_t)t * P.ldm + tid] = vm[tid];
@@ -1303,6 +1259,14 @@ __device__ __forceinline__ void filter_final_body(const KModel& M, const FilterA
     }
   }
   if (!ok && tid == 0) flag_status(P.status, P.fail_bit);
+}
+
+template <int D, int OBS, int U = 4>
+__device__ __forceinline__ void filter_final_body(const KModel& M, const FilterArgs& P, int item) {
+  if constexpr (D <= 32)
+    wave_final<D, OBS>(M, P, item);
+  else
+    filter_final_impl<D, OBS, U>(M, P, item);
 }
 
 template <int D, int OBS>
@@ -1319,7 +1283,7 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_final(KModel M, FilterArg
 // Terminal step: E = 0, U = m^f + chol(P^f) xi.
 // ---------------------------------------------------------------------------
 template <int D, int U = 4>
-__device__ __forceinline__ void samp_build_body(const KModel& M, const SampArgs& S, int item) {
+__device__ __forceinline__ void samp_build_impl(const KModel& M, const SampArgs& S, int item) {
   // two LDS matrices (X, Y), so that two teams share a CU: both buffers serve
   // the inverse as scratch, and G = F P^f is formed again after it
   using C = Cfg<D>;
@@ -1405,6 +1369,14 @@ __device__ __forceinline__ void samp_build_body(const KModel& M, const SampArgs&
     }
   }
   if (!ok && tid == 0) flag_status(S.status, ST_FWD_NOT_PD);
+}
+
+template <int D, int U = 4>
+__device__ __forceinline__ void samp_build_body(const KModel& M, const SampArgs& S, int item) {
+  if constexpr (D <= 32)
+    wave_sbuild<D>(M, S, item);
+  else
+    samp_build_impl<D, U>(M, S, item);
 }
 
 template <int D>
@@ -1675,12 +1647,14 @@ __global__ void __launch_bounds__(256) k_mh_select(int64_t n, const double* __re
 // Host-side launch helpers (templated on D), used by akf_capi.cpp
 // ---------------------------------------------------------------------------
 template <int D>
-size_t lds_bytes_filter(bool gh = false) {
-  return (size_t)((gh ? 5 : 4) * Cfg<D>::MAT + 12 * D + 16) * sizeof(double);
+size_t lds_bytes_filter() {
+  if (D <= 32) return wave_lds_bytes<D>();
+  return (size_t)(4 * Cfg<D>::MAT + 12 * D + 16) * sizeof(double);
 }
 // the sampler element build: two matrices and four vectors (two teams per CU)
 template <int D>
 size_t lds_bytes_samp_build() {
+  if (D <= 32) return wave_lds_bytes<D>();
   return (size_t)(2 * Cfg<D>::MAT + 4 * D) * sizeof(double);
 }
 template <int D>
@@ -1691,7 +1665,7 @@ size_t lds_bytes_samp2() {
 template <int D, int OBS>
 hipError_t launch_filter(const KModel& M, FilterArgs P, TreeArgs* lv_up, TreeArgs* lv_down,
                          int n_levels, hipStream_t st) {
-  const size_t lds = lds_bytes_filter<D>(OBS == OBS_GH);
+  const size_t lds = lds_bytes_filter<D>();
   const int nb = (M.N + P.B - 1) / P.B;
   timing_mark(FAM_FILTER_FOLD, 1, st);
   hipLaunchKernelGGL((k_filter_fold<D, OBS>), dim3(nb), dim3(Cfg<D>::NT), lds, st, M, P);
@@ -1717,7 +1691,7 @@ hipError_t launch_filter(const KModel& M, FilterArgs P, TreeArgs* lv_up, TreeArg
 template <int D, int OBS>
 hipError_t launch_filter_scan(const KModel& M, FilterArgs P, const HsArgs* lv, int n_levels,
                               hipStream_t st) {
-  const size_t lds = lds_bytes_filter<D>(OBS == OBS_GH);
+  const size_t lds = lds_bytes_filter<D>();
   const int nb = (M.N + P.B - 1) / P.B;
   timing_mark(FAM_FILTER_FOLD, 1, st);
   hipLaunchKernelGGL((k_filter_fold<D, OBS>), dim3(nb), dim3(Cfg<D>::NT), lds, st, M, P);
@@ -1750,7 +1724,7 @@ static int compute_units() {
 template <int D, int OBS>
 hipError_t launch_filter_logz(const KModel& M, FilterArgs P, const TreeArgs* up, int n_levels,
                               hipStream_t st) {
-  const size_t lds = lds_bytes_filter<D>(OBS == OBS_GH);
+  const size_t lds = lds_bytes_filter<D>();
   const int nb = (M.N + P.B - 1) / P.B;
   timing_mark(FAM_FILTER_FOLD, 1, st);
   hipLaunchKernelGGL((k_filter_fold<D, OBS>), dim3(nb), dim3(Cfg<D>::NT), lds, st, M, P);

@@ -1,0 +1,800 @@
+// akf_wave.hpp -- one-wave (D = 16 and 32) bodies of the filter and sampler
+// kernels, with every matrix operand in registers.
+//
+// A lone wave holding whole matrices needs no staging for its products: in the
+// accumulator layout (akf_team.hpp) a tile's registers are its own B fragments
+// and the A fragments of its transpose, so x' y takes its operands as they
+// are.  Every product of the filter and the sampler is written in that form,
+// with the constant F kept as F'; the transposes that remain (one tile to
+// mirror a symmetric result, the diagonal tiles of a symmetrisation) go
+// through a 16 x 17 LDS tile.  Symmetric results form their upper tiles only.
+// A wave's LDS operations complete in order, so no barrier is needed; LDS per
+// team is a few KB, and the registers alone decide how many waves share a
+// SIMD.  With operands staged through LDS instead (a store, a wait and two
+// loads around each product) a fold step of a lone wave took 10.8k cycles at
+// D = 16 and 38k at D = 32.
+#pragma once
+#include "akf_internal.h"
+#include "akf_team.hpp"
+
+namespace akf {
+
+// ---------------------------------------------------------------------------
+// tiles and products
+// ---------------------------------------------------------------------------
+template <int D>
+constexpr int wave_scr() {  // doubles of LDS scratch: one padded tile per tile of a matrix
+  return Cfg<D>::TPW * 16 * 17;
+}
+
+// LDS bytes of every one-wave body: scratch tiles and eight vectors
+template <int D>
+constexpr size_t wave_lds_bytes() {
+  return (size_t)(wave_scr<D>() + 8 * D) * sizeof(double);
+}
+
+// transpose of a tile through 16 x 17 doubles of LDS
+__device__ __forceinline__ dbl4 tile_t(const dbl4& t, double* s) {
+  const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) s[lc * 17 + 4 * r + lg] = t[r];
+  wave_lds_fence();
+  dbl4 o;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) o[r] = s[(4 * r + lg) * 17 + lc];
+  wave_lds_fence();
+  return o;
+}
+
+template <int D>
+__device__ __forceinline__ RM<D> rm_t(const RM<D>& a, double* scr) {
+  constexpr int TS = Cfg<D>::TS;
+  RM<D> o;
+#pragma unroll
+  for (int ti = 0; ti < TS; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < TS; ++tj)
+      o.t[tj * TS + ti] = tile_t(a.t[ti * TS + tj], scr + (ti * TS + tj) * 16 * 17);
+  return o;
+}
+
+// c + a' b of one tile
+__device__ __forceinline__ dbl4 tile_tn(const dbl4& a, const dbl4& b, dbl4 c) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
+  return c;
+}
+
+// c += x' y over the first KT tile rows of x and y, result tile rows < RT and
+// columns < CT; UP: only the tiles on and above the diagonal.
+template <int D, bool UP = false, int KT = Cfg<D>::TS, int RT = Cfg<D>::TS, int CT = Cfg<D>::TS>
+__device__ __forceinline__ void tn(RM<D>& c, const RM<D>& x, const RM<D>& y) {
+  constexpr int TS = Cfg<D>::TS;
+#pragma unroll
+  for (int k = 0; k < KT; ++k)
+#pragma unroll
+    for (int ti = 0; ti < RT; ++ti)
+#pragma unroll
+      for (int tj = UP ? ti : 0; tj < CT; ++tj)
+        c.t[ti * TS + tj] = tile_tn(x.t[k * TS + ti], y.t[k * TS + tj], c.t[ti * TS + tj]);
+}
+
+// c = x' y (same parameters)
+template <int D, bool UP = false, int KT = Cfg<D>::TS, int RT = Cfg<D>::TS, int CT = Cfg<D>::TS>
+__device__ __forceinline__ RM<D> tn0(const RM<D>& x, const RM<D>& y) {
+  RM<D> c;
+  rm_zero<D>(c);
+  tn<D, UP, KT, RT, CT>(c, x, y);
+  return c;
+}
+
+// lower tiles from the upper ones
+template <int D>
+__device__ __forceinline__ void mirror(RM<D>& c, double* scr) {
+  if constexpr (D == 32) c.t[2] = tile_t(c.t[1], scr);
+}
+
+// the same with the diagonal tiles averaged with their transposes
+template <int D>
+__device__ __forceinline__ void symm(RM<D>& c, double* scr) {
+  constexpr int TS = Cfg<D>::TS;
+  dbl4 o[TS];
+#pragma unroll
+  for (int k = 0; k < TS; ++k) o[k] = tile_t(c.t[k * TS + k], scr + k * 16 * 17);
+  if constexpr (D == 32) c.t[2] = tile_t(c.t[1], scr + 2 * 16 * 17);
+#pragma unroll
+  for (int k = 0; k < TS; ++k) c.t[k * TS + k] = 0.5 * (c.t[k * TS + k] + o[k]);
+}
+
+// a_ij = G[j*ld + i] for i < rows, j < cols, zero elsewhere
+template <int D>
+__device__ __forceinline__ void rm_load_t(RM<D>& a, const double* __restrict__ g, int ld, int rows,
+                                          int cols) {
+  AKF_RM_FOR(D, q, r, i, j) a.t[q][r] = (i < rows && j < cols) ? g[(size_t)j * ld + i] : 0.0;
+}
+
+// ---------------------------------------------------------------------------
+// vectors: in LDS, and in registers by row (element 16 ti + 4 r + l/16)
+// ---------------------------------------------------------------------------
+template <int D>
+struct RV {
+  double v[Cfg<D>::TS][4];
+};
+
+template <int D>
+__device__ __forceinline__ RV<D> rv(const double* s) {
+  const int lg = (threadIdx.x & 63) >> 4;
+  RV<D> o;
+#pragma unroll
+  for (int ti = 0; ti < Cfg<D>::TS; ++ti)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o.v[ti][r] = s[16 * ti + 4 * r + lg];
+  return o;
+}
+
+// s plus the values of the other lanes with the same l%16 (two half exchanges
+// in the vector unit; a lane permute through LDS takes 83 cycles each)
+__device__ __forceinline__ double sum_groups(double s) {
+  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+  auto both = [](u2 lo, u2 hi) {
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+  };
+  uint64_t u = __builtin_bit_cast(uint64_t, s);
+  uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  s = both(__builtin_amdgcn_permlane16_swap(lo, lo, false, false),
+           __builtin_amdgcn_permlane16_swap(hi, hi, false, false));
+  u = __builtin_bit_cast(uint64_t, s);
+  lo = (uint32_t)u;
+  hi = (uint32_t)(u >> 32);
+  return both(__builtin_amdgcn_permlane32_swap(lo, lo, false, false),
+              __builtin_amdgcn_permlane32_swap(hi, hi, false, false));
+}
+
+// lane (l + N) of the row of 16
+template <int N>
+__device__ __forceinline__ double row_ror(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + N, 0xF, 0xF, true);
+  const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + N, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// sum over the wave, to every lane
+__device__ __forceinline__ double wave_total(double v) {
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  v += row_ror<1>(v);
+  return sum_groups(v);
+}
+
+// lane l < D: (x' v)_l (plus add, a value of that lane); other lanes: unspecified
+template <int D, int KT = Cfg<D>::TS>
+__device__ __forceinline__ double mv(const RM<D>& x, const RV<D>& v) {
+  constexpr int TS = Cfg<D>::TS;
+  double s[TS];
+#pragma unroll
+  for (int tj = 0; tj < TS; ++tj) {
+    double a = 0.0, b = 0.0;
+#pragma unroll
+    for (int ti = 0; ti < KT; ++ti) {
+      a = fma(x.t[ti * TS + tj][0], v.v[ti][0], a);
+      b = fma(x.t[ti * TS + tj][1], v.v[ti][1], b);
+      a = fma(x.t[ti * TS + tj][2], v.v[ti][2], a);
+      b = fma(x.t[ti * TS + tj][3], v.v[ti][3], b);
+    }
+    s[tj] = sum_groups(a + b);
+  }
+  if constexpr (TS == 1) return s[0];
+  else return (threadIdx.x & 16) ? s[1] : s[0];
+}
+
+// the value of lane l < D into s[l]
+template <int D>
+__device__ __forceinline__ void vec_put(double* s, double v) {
+  const int l = threadIdx.x;
+  if (l < D) s[l] = v;
+  wave_lds_fence();
+}
+
+// ---------------------------------------------------------------------------
+// factorisations
+// ---------------------------------------------------------------------------
+template <int D>
+__device__ __forceinline__ void rm_mask(RM<D>& a, int d) {
+  AKF_RM_FOR(D, q, r, i, j) if (i >= d || j >= d) a.t[q][r] = 0.0;
+}
+
+__device__ __forceinline__ dbl4 tile_of(const double p[4]) { return dbl4{p[0], p[1], p[2], p[3]}; }
+
+// In-place inverse of a symmetric positive definite matrix (zero outside the
+// leading d x d block) by 2 x 2 blocks of tiles [[a, b], [b', c]]: with
+// P = a^{-1}, X = P b and S = c - b' X,
+//   inverse = [[P + X S^{-1} X', -X S^{-1}], [-S^{-1} X', S^{-1}]].
+// Reads the diagonal and upper tiles; the result's lower tile mirrors its
+// upper one.  KT = 1: d <= 16, the first tile alone (the others are not
+// touched).  Pivots, failure and ld as in spd_inv.
+template <int D, int KT = Cfg<D>::TS>
+__device__ __forceinline__ bool wave_inv(RM<D>& A, int d, double* scr, LogDet& ld) {
+  bool ok = true;
+  double p[4], dummy[4];
+  tile_regs(A.t[0], p);
+  tile_sweep16<false, KT == 1>(p, d, dummy, ld, ok);
+  if constexpr (KT == 1) {
+    A.t[0] = tile_of(p);
+    const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (4 * r + lg >= d || lc >= d) A.t[0][r] = 0.0;
+  } else {
+    const dbl4 z = {0.0, 0.0, 0.0, 0.0};
+    const dbl4 P = tile_of(p);
+    const dbl4 X = tile_tn(P, A.t[1], z);           // P b
+    const dbl4 Z = tile_t(X, scr);                  // X'
+    const dbl4 S = A.t[3] - tile_tn(A.t[1], X, z);  // c - b' X
+    tile_regs(S, p);
+    tile_sweep16<false, true>(p, d - 16, dummy, ld, ok);
+    const dbl4 Si = tile_of(p);
+    const dbl4 Wt = tile_tn(Si, Z, z);  // S^{-1} X'
+    A.t[0] = tile_tn(Z, Wt, P);         // P + X S^{-1} X'
+    A.t[2] = -Wt;
+    A.t[1] = tile_t(A.t[2], scr + 16 * 17);
+    A.t[3] = Si;
+    rm_mask<D>(A, d);
+  }
+  return ok;
+}
+
+// Lower Cholesky factor L of a symmetric positive definite matrix (diagonal
+// and upper tiles read) and its transpose LT.
+template <int D>
+__device__ __forceinline__ bool wave_chol(const RM<D>& A, RM<D>& L, RM<D>& LT, int d, double* scr) {
+  const dbl4 z = {0.0, 0.0, 0.0, 0.0};
+  bool ok = true;
+  LogDet ld;
+  double p[4], Lk[4];
+  tile_regs(A.t[0], p);
+  tile_sweep16<true, D == 16>(p, d, Lk, ld, ok);
+  L.t[0] = tile_of(Lk);
+  if constexpr (D == 32) {
+    double G[4];
+    chol_tile_rinv(p, Lk, G);  // L_00^{-T}
+    const dbl4 g = tile_of(G);
+    LT.t[1] = tile_tn(g, A.t[1], z);  // (L_10)'
+    L.t[1] = z;
+    L.t[2] = tile_tn(A.t[1], g, z);  // A_10 L_00^{-T}
+    const dbl4 S = A.t[3] - tile_tn(LT.t[1], LT.t[1], z);
+    tile_regs(S, p);
+    tile_sweep16<true, true>(p, d - 16, Lk, ld, ok);
+    L.t[3] = tile_of(Lk);
+  }
+  AKF_RM_FOR(D, q, r, i, j) if (j > i || i >= d) L.t[q][r] = 0.0;
+  LT.t[0] = tile_t(L.t[0], scr);
+  if constexpr (D == 32) {
+    LT.t[2] = z;
+    LT.t[3] = tile_t(L.t[3], scr + 16 * 17);
+    AKF_RM_FOR(D, q, r, i, j) if (i >= d || j >= d) LT.t[q][r] = 0.0;
+  }
+  return ok;
+}
+
+// x_ij *= v_i
+template <int D>
+__device__ __forceinline__ void scale_rows(RM<D>& x, const RV<D>& v) {
+  constexpr int TS = Cfg<D>::TS;
+#pragma unroll
+  for (int q = 0; q < Cfg<D>::TPW; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x.t[q][r] *= v.v[q / TS][r];
+}
+
+template <int D>
+__device__ __forceinline__ void add_eye(RM<D>& x, int d) {
+  AKF_RM_FOR(D, q, r, i, j) if (i == j && i < d) x.t[q][r] += 1.0;
+}
+
+// ---------------------------------------------------------------------------
+// Filter, block fold (the recursion above filter_fold_impl)
+// ---------------------------------------------------------------------------
+// The general-observation update with KT tile rows of observations (dobs <= 16
+// needs one): with Mo = H Pp, N = Mo' and Mt = H T, S = H N + R,
+//   C = Pp - Mo' S^{-1} Mo, A = T - Mo' S^{-1} Mt, J += Mt' S^{-1} Mt.
+template <int D, int KT, bool FIRST>
+__device__ __forceinline__ bool wave_update_gh(const FilterArgs& P, int t, const RM<D>& HT,
+                                               const RM<D>& Pp, const RM<D>& T, RM<D>& A, RM<D>& Cc,
+                                               RM<D>& J, double* vb, double* veta, double* vmu,
+                                               double* vs, double* scr, LogDet& ld, double& q_part) {
+  constexpr int TS = Cfg<D>::TS;
+  const int l = threadIdx.x, m = P.dyo;
+  const double y = l < m ? P.yo[(int64_t)t * m + l] : 0.0;
+  const RM<D> Mo = tn0<D, false, TS, KT>(HT, Pp);
+  RM<D> N;
+#pragma unroll
+  for (int ti = 0; ti < KT; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < TS; ++tj)
+      N.t[tj * TS + ti] = tile_t(Mo.t[ti * TS + tj], scr + (ti * TS + tj) * 16 * 17);
+  RM<D> S;
+  rm_load<D>(S, P.Ro, m, m);
+  tn<D, true, TS, KT, KT>(S, N, HT);  // Mo H' + R
+  const double hm = mv<D>(HT, rv<D>(vmu));  // H mu
+  const double vw = l < m ? y - hm : 0.0;
+  const bool ok = wave_inv<D, KT>(S, m, scr, ld);
+  vec_put<D>(vs, vw);
+  const double si = mv<D, KT>(S, rv<D>(vs));  // S^{-1} w
+  q_part += l < D ? vw * si : 0.0;
+  vec_put<D>(vs, l < m ? si : 0.0);
+  const RV<D> rs = rv<D>(vs);
+  RM<D> U = tn0<D, false, KT, KT>(S, Mo);
+  Cc = tn0<D, true, KT>(Mo, U);
+  rm_rsub<D>(Cc, Pp);
+  const double b = mv<D, KT>(Mo, rs);
+  if constexpr (!FIRST) {
+    const RM<D> Mt = tn0<D, false, TS, KT>(HT, T);
+    U = tn0<D, false, KT, KT>(S, Mt);
+    tn<D, true, KT>(J, Mt, U);
+    A = tn0<D, false, KT>(Mo, U);
+    rm_rsub<D>(A, T);
+    const double e = mv<D, KT>(Mt, rs);
+    if (l < D) veta[l] += e;
+  }
+  if (l < D) vb[l] = vmu[l] + b;
+  wave_lds_fence();
+  return ok;
+}
+
+template <int D, int OBS, bool FIRST>
+__device__ __forceinline__ void wave_fold(const KModel& M, const FilterArgs& P, int item) {
+  constexpr bool GH = (OBS == OBS_GH);
+  extern __shared__ double lds[];
+  double* scr = lds;
+  double* vb = scr + wave_scr<D>();
+  double* veta = vb + D;
+  double* vmu = veta + D;
+  double* vs = vmu + D;
+  double* vom = vs + D;
+  const int l = threadIdx.x, d = M.d;
+  const int s0 = item * P.B, s1 = min(M.N, s0 + P.B);
+  const int dobs = GH ? P.dyo : d;
+  RM<D> FT, HT, A, Cc, J;
+  if (!P.Ft) rm_load_t<D>(FT, M.F, d, d, d);
+  if constexpr (GH) rm_load_t<D>(HT, P.Ho, d, d, P.dyo);
+  rm_zero<D>(Cc);
+  rm_zero<D>(J);
+  rm_zero<D>(A);
+  if (l < D) vb[l] = veta[l] = 0.0;
+  wave_lds_fence();
+  LogDet ld;
+  double q_part = 0.0;
+  bool ok = true;
+  // this step's omega_t and Omega_t, fetched one step ahead
+  const bool in = l < d;
+  double om_n = 0.0, Om_n = 0.0;
+  if (OBS != OBS_GH && in) {
+    om_n = P.om[(int64_t)s0 * d + l];
+    if (OBS == OBS_DIAG || !P.Omd) Om_n = P.Om[(int64_t)s0 * d + l];
+  }
+  for (int t = s0; t < s1; ++t) {
+    const double om = om_n, Om = Om_n;
+    if (OBS != OBS_GH && in && t + 1 < s1) {
+      om_n = P.om[(int64_t)(t + 1) * d + l];
+      if (OBS == OBS_DIAG || !P.Omd) Om_n = P.Om[(int64_t)(t + 1) * d + l];
+    }
+    RM<D> Pp, T;
+    double mu = 0.0;
+    if (t == 0) {
+      rm_load<D>(Pp, M.P0, d, d);
+      mu = in ? M.m0[l] : 0.0;
+    } else {
+      rm_load<D>(Pp, M.Q, d, d);
+      const double* F = P.Ft ? P.Ft + (int64_t)t * d * d : M.F;
+      const double* bt = P.Ft ? P.bt + (int64_t)t * d : M.b;
+      mu = (in && bt) ? bt[l] : 0.0;
+      if (!FIRST && t == s0) {  // A = I, C = 0, b = 0
+        rm_load<D>(T, F, d, d);
+      } else {
+        if (P.Ft) rm_load_t<D>(FT, F, d, d, d);
+        const RM<D> V = tn0<D>(Cc, FT);  // C F'
+        if constexpr (!FIRST) T = tn0<D>(FT, A);
+        tn<D, true>(Pp, FT, V);  // Q + F C F'
+        mirror<D>(Pp, scr);
+        mu += mv<D>(FT, rv<D>(vb));
+      }
+    }
+    if constexpr (GH) {
+      vec_put<D>(vmu, mu);
+      if (D == 16 || P.dyo <= 16)
+        ok = wave_update_gh<D, 1, FIRST>(P, t, HT, Pp, T, A, Cc, J, vb, veta, vmu, vs, scr, ld,
+                                         q_part) && ok;
+      else
+        ok = wave_update_gh<D, Cfg<D>::TS, FIRST>(P, t, HT, Pp, T, A, Cc, J, vb, veta, vmu, vs, scr,
+                                                  ld, q_part) && ok;
+      symm<D>(Cc, scr);
+      continue;
+    }
+    const double w = in ? om - mu : 0.0;
+    RM<D> S = Pp;
+    const bool diag = OBS == OBS_DIAG || !P.Omd;
+    vec_put<D>(vom, Om);
+    vec_put<D>(vs, w);
+    const RV<D> rom = rv<D>(vom);
+    if (diag) {
+      constexpr int TS = Cfg<D>::TS;
+      AKF_RM_FOR(D, q, r, i, j) if (i == j) S.t[q][r] += rom.v[q / TS][r];
+    } else {
+      rm_add_load<D>(S, P.Omd, d, d);
+    }
+    ok = wave_inv<D>(S, d, scr, ld) && ok;  // S^{-1}
+    const double si = mv<D>(S, rv<D>(vs));  // S^{-1} w
+    q_part += l < D ? w * si : 0.0;
+    vec_put<D>(vs, si);
+    RM<D> R;
+    if constexpr (OBS == OBS_DIAG) {
+      // I - Pp S^{-1} = Omega S^{-1}: products only, nothing cancels
+      Cc = tn0<D, true>(S, Pp);
+      scale_rows<D>(Cc, rom);
+      symm<D>(Cc, scr);
+      if constexpr (!FIRST) {
+        R = tn0<D>(S, T);
+        tn<D, true>(J, T, R);
+        A = R;
+        scale_rows<D>(A, rom);
+      }
+      vec_put<D>(vb, in ? om - Om * si : 0.0);
+    } else {
+      R = tn0<D>(S, Pp);
+      Cc = tn0<D, true>(Pp, R);
+      rm_rsub<D>(Cc, Pp);
+      symm<D>(Cc, scr);
+      const double b = mv<D>(Pp, rv<D>(vs));
+      if constexpr (!FIRST) {
+        R = tn0<D>(S, T);
+        tn<D, true>(J, T, R);
+        A = tn0<D>(Pp, R);
+        rm_rsub<D>(A, T);
+      }
+      vec_put<D>(vb, mu + b);
+    }
+    if constexpr (!FIRST) {
+      const double e = mv<D>(T, rv<D>(vs));
+      if (l < D) veta[l] += e;
+      wave_lds_fence();
+    }
+  }
+  if (!ok && l == 0) atomicOr(P.status, P.fail_bit);
+  symm<D>(J, scr);
+  using EL = ElemLayout<D>;
+  double* out = P.elem + (int64_t)item * EL::SIZE;
+  rm_store<D>(A, out + EL::A, D, D);
+  rm_store<D>(Cc, out + EL::C, D, D);
+  rm_store<D>(J, out + EL::J, D, D);
+  if (l < D) {
+    out[EL::b + l] = vb[l];
+    out[EL::eta + l] = veta[l];
+  }
+  const double q = wave_total(q_part);
+  if (l == 0)
+    out[EL::lc] = -0.5 * ((s1 - s0) * dobs * 1.8378770664093454835606594728112 + ld.value() + q);
+}
+
+// ---------------------------------------------------------------------------
+// Filter combine (the formulas above filter_combine); SIDE as there
+// ---------------------------------------------------------------------------
+// M = (I + C J)^{-1} C from L, L' (C = L L') and J; log det (I + C J) into ld
+template <int D>
+__device__ __forceinline__ bool wave_M(RM<D>& Mm, const RM<D>& L, const RM<D>& LT, const RM<D>& J,
+                                       int d, double* scr, LogDet& ld) {
+  const RM<D> R = tn0<D>(J, L);      // J L
+  RM<D> Wm = tn0<D, true>(L, R);     // L' J L
+  add_eye<D>(Wm, d);
+  const bool ok = wave_inv<D>(Wm, d, scr, ld);
+  const RM<D> K = tn0<D>(Wm, LT);  // W^{-1} L'
+  Mm = tn0<D, true>(LT, K);        // L W^{-1} L'
+  mirror<D>(Mm, scr);
+  return ok;
+}
+
+template <int D, int SIDE>
+__device__ __forceinline__ void wave_combine(const KModel& M, const double* __restrict__ ei,
+                                             const double* __restrict__ ej,
+                                             double* __restrict__ out, int* status, int fail_bit) {
+  using EL = ElemLayout<D>;
+  extern __shared__ double lds[];
+  double* scr = lds;
+  double* va = scr + wave_scr<D>();
+  const int l = threadIdx.x, d = M.d;
+  const bool in = l < D;
+  RM<D> Ci, Jj, Ai, Ji, AjT, Cj;
+  rm_load<D>(Ci, ei + EL::C, D, D);
+  rm_load<D>(Jj, ej + EL::J, D, D);
+  const double bi = in ? ei[EL::b + l] : 0.0, etaj = in ? ej[EL::eta + l] : 0.0;
+  // needed after the factorisations
+  if constexpr (SIDE != 2) {
+    rm_load<D>(Ai, ei + EL::A, D, D);
+    rm_load<D>(Ji, ei + EL::J, D, D);
+  }
+  rm_load_t<D>(AjT, ej + EL::A, D, D, D);
+  if constexpr (SIDE != 1) rm_load<D>(Cj, ej + EL::C, D, D);
+  RM<D> L, LT, Mm;
+  LogDet ld;
+  bool ok = wave_chol<D>(Ci, L, LT, d, scr);
+  ok = wave_M<D>(Mm, L, LT, Jj, d, scr, ld) && ok;
+  vec_put<D>(va, bi);
+  const double c = etaj - mv<D>(Jj, rv<D>(va));  // c = eta_j - J_j b_i
+  vec_put<D>(va + D, c);
+  const double w = mv<D>(Mm, rv<D>(va + D));  // M c
+  vec_put<D>(va + 2 * D, w);
+  if constexpr (SIDE != 2) {
+    const double k = c - mv<D>(Jj, rv<D>(va + 2 * D));  // c - J_j M c
+    vec_put<D>(va, k);
+    const RM<D> Pm = tn0<D>(Jj, Ai);  // P = J_j A_i
+    RM<D> Z = tn0<D>(Mm, Pm);
+    rm_rsub<D>(Z, Ai);  // Z = A_i - M P
+    const double e = mv<D>(Ai, rv<D>(va));
+    if (in) out[EL::eta + l] = ei[EL::eta + l] + e;
+    tn<D, true>(Ji, Z, Pm);  // Z' P + J_i
+    symm<D>(Ji, scr);
+    rm_store<D>(Ji, out + EL::J, D, D);
+    const RM<D> An = tn0<D>(AjT, Z);
+    rm_store<D>(An, out + EL::A, D, D);
+  }
+  if constexpr (SIDE != 1) {
+    const RM<D> V = tn0<D>(Mm, AjT);  // M A_j'
+    tn<D, true>(Cj, AjT, V);          // A_j M A_j' + C_j
+    vec_put<D>(va + 3 * D, w + bi);
+    const double b = mv<D>(AjT, rv<D>(va + 3 * D));
+    symm<D>(Cj, scr);
+    rm_store<D>(Cj, out + EL::C, D, D);
+    if (in) out[EL::b + l] = b + ej[EL::b + l];
+    const double q = wave_total(in ? bi * (etaj + c) + c * w : 0.0);
+    if (l == 0) out[EL::lc] = ei[EL::lc] + ej[EL::lc] - 0.5 * ld.value() + 0.5 * q;
+  }
+  if (!ok && l == 0) atomicOr(status, fail_bit);
+}
+
+// Moment pair (x) element (the formulas above moment_combine)
+template <int D>
+__device__ __forceinline__ void wave_moment(const KModel& M, const double* Pin, const double* min_,
+                                            const double* el, double* Pout, double* mout,
+                                            int* status, int fail_bit, const double* lcin,
+                                            double* lcout) {
+  using EL = ElemLayout<D>;
+  extern __shared__ double lds[];
+  double* scr = lds;
+  double* va = scr + wave_scr<D>();
+  const int l = threadIdx.x, d = M.d;
+  const bool in = l < D;
+  RM<D> Ci, Jj, AT, Ce;
+  rm_load<D>(Ci, Pin, D, D);
+  rm_load<D>(Jj, el + EL::J, D, D);
+  rm_load_t<D>(AT, el + EL::A, D, D, D);
+  rm_load<D>(Ce, el + EL::C, D, D);
+  const double m = in ? min_[l] : 0.0, eta = in ? el[EL::eta + l] : 0.0;
+  const double be = in ? el[EL::b + l] : 0.0;
+  RM<D> L, LT, Mm;
+  LogDet ld;
+  bool ok = wave_chol<D>(Ci, L, LT, d, scr);
+  ok = wave_M<D>(Mm, L, LT, Jj, d, scr, ld) && ok;
+  vec_put<D>(va, m);
+  const double c = eta - mv<D>(Jj, rv<D>(va));
+  vec_put<D>(va + D, c);
+  const double w = mv<D>(Mm, rv<D>(va + D));
+  if (lcout) {
+    const double q = wave_total(in ? m * (eta + c) + c * w : 0.0);
+    if (l == 0) *lcout = *lcin + el[EL::lc] - 0.5 * ld.value() + 0.5 * q;
+  }
+  const RM<D> V = tn0<D>(Mm, AT);
+  tn<D, true>(Ce, AT, V);
+  vec_put<D>(va + 2 * D, w + m);
+  const double z = mv<D>(AT, rv<D>(va + 2 * D));
+  if (in) mout[l] = z + be;
+  symm<D>(Ce, scr);
+  rm_store<D>(Ce, Pout, D, D);
+  if (!ok && l == 0) atomicOr(status, fail_bit);
+}
+
+// ---------------------------------------------------------------------------
+// Filter, block re-scan (the recursion above filter_final_body)
+// ---------------------------------------------------------------------------
+template <int D, int KT>
+__device__ __forceinline__ bool wave_final_gh(const FilterArgs& P, int t, const RM<D>& HT,
+                                              const RM<D>& Pp, RM<D>& Pm, double* vm, double* vmp,
+                                              double* vs, double* scr, LogDet& ld, double& q) {
+  constexpr int TS = Cfg<D>::TS;
+  const int l = threadIdx.x, m = P.dyo;
+  const double y = l < m ? P.yo[(int64_t)t * m + l] : 0.0;
+  const RM<D> Mo = tn0<D, false, TS, KT>(HT, Pp);
+  RM<D> N;
+#pragma unroll
+  for (int ti = 0; ti < KT; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < TS; ++tj)
+      N.t[tj * TS + ti] = tile_t(Mo.t[ti * TS + tj], scr + (ti * TS + tj) * 16 * 17);
+  RM<D> S;
+  rm_load<D>(S, P.Ro, m, m);
+  tn<D, true, TS, KT, KT>(S, N, HT);
+  const double hm = mv<D>(HT, rv<D>(vmp));  // H m^p
+  const double vw = l < m ? y - hm : 0.0;
+  const bool ok = wave_inv<D, KT>(S, m, scr, ld);
+  vec_put<D>(vs, vw);
+  const double si = mv<D, KT>(S, rv<D>(vs));
+  q = l < D ? vw * si : 0.0;
+  vec_put<D>(vs, l < m ? si : 0.0);
+  const RM<D> U = tn0<D, false, KT, KT>(S, Mo);
+  Pm = tn0<D, true, KT>(Mo, U);
+  rm_rsub<D>(Pm, Pp);
+  const double b = mv<D, KT>(Mo, rv<D>(vs));
+  vec_put<D>(vm, l < D ? vmp[l] + b : 0.0);
+  return ok;
+}
+
+template <int D, int OBS>
+__device__ __forceinline__ void wave_final(const KModel& M, const FilterArgs& P, int item) {
+  constexpr bool GH = (OBS == OBS_GH);
+  using EL = ElemLayout<D>;
+  using PL = PrefLayout<D>;
+  extern __shared__ double lds[];
+  double* scr = lds;
+  double* vm = scr + wave_scr<D>();
+  double* vmp = vm + D;
+  double* vs = vmp + D;
+  double* vom = vs + D;
+  const int l = threadIdx.x, d = M.d;
+  const int s0 = item * P.B, s1 = min(M.N, s0 + P.B);
+  const int dobs = GH ? P.dyo : d;
+  const bool in = l < d;
+  RM<D> FT, HT, Pm;
+  if (!P.Ft) rm_load_t<D>(FT, M.F, d, d, d);
+  if constexpr (GH) rm_load_t<D>(HT, P.Ho, d, d, P.dyo);
+  if (s0 > 0) {
+    const double* pin = P.pre_elem ? P.pre_elem + (int64_t)(item - 1) * EL::SIZE
+                                   : P.pre + (int64_t)item * PL::SIZE;
+    rm_load<D>(Pm, pin + (P.pre_elem ? (int)EL::C : (int)PL::P), D, D);
+    vec_put<D>(vm, l < D ? pin[(P.pre_elem ? (int)EL::b : (int)PL::m) + l] : 0.0);
+  }
+  double om_n = 0.0, Om_n = 0.0;
+  if (OBS != OBS_GH && in) {
+    om_n = P.om[(int64_t)s0 * d + l];
+    if (OBS == OBS_DIAG || !P.Omd) Om_n = P.Om[(int64_t)s0 * d + l];
+  }
+  bool ok = true;
+  for (int t = s0; t < s1; ++t) {
+    const double om = om_n, Om = Om_n;
+    if (OBS != OBS_GH && in && t + 1 < s1) {
+      om_n = P.om[(int64_t)(t + 1) * d + l];
+      if (OBS == OBS_DIAG || !P.Omd) Om_n = P.Om[(int64_t)(t + 1) * d + l];
+    }
+    RM<D> Pp;
+    double mp = 0.0;
+    if (t == 0) {
+      rm_load<D>(Pp, M.P0, d, d);
+      mp = in ? M.m0[l] : 0.0;
+    } else {
+      rm_load<D>(Pp, M.Q, d, d);
+      const double* bt = P.Ft ? P.bt + (int64_t)t * d : M.b;
+      mp = (in && bt) ? bt[l] : 0.0;
+      if (P.Ft) rm_load_t<D>(FT, P.Ft + (int64_t)t * d * d, d, d, d);
+      const RM<D> V = tn0<D>(Pm, FT);
+      tn<D, true>(Pp, FT, V);
+      mirror<D>(Pp, scr);
+      mp += mv<D>(FT, rv<D>(vm));
+    }
+    LogDet ld;
+    double q;
+    if constexpr (GH) {
+      vec_put<D>(vmp, mp);
+      if (D == 16 || P.dyo <= 16)
+        ok = wave_final_gh<D, 1>(P, t, HT, Pp, Pm, vm, vmp, vs, scr, ld, q) && ok;
+      else
+        ok = wave_final_gh<D, Cfg<D>::TS>(P, t, HT, Pp, Pm, vm, vmp, vs, scr, ld, q) && ok;
+    } else {
+      const double w = in ? om - mp : 0.0;
+      RM<D> S = Pp;
+      vec_put<D>(vom, Om);
+      vec_put<D>(vs, w);
+      const RV<D> rom = rv<D>(vom);
+      if (OBS == OBS_DIAG || !P.Omd) {
+        constexpr int TS = Cfg<D>::TS;
+        AKF_RM_FOR(D, qq, r, i, j) if (i == j) S.t[qq][r] += rom.v[qq / TS][r];
+      } else {
+        rm_add_load<D>(S, P.Omd, d, d);
+      }
+      ok = wave_inv<D>(S, d, scr, ld) && ok;
+      const double si = mv<D>(S, rv<D>(vs));
+      q = l < D ? w * si : 0.0;
+      if constexpr (OBS == OBS_DIAG) {
+        if (P.Sinv) {  // kept transposed; S^{-1} is symmetric
+          rm_store<D>(S, P.Sinv + (int64_t)t * D * D, D, D);
+          if (l == 0) P.ldS[t] = ld.value();
+        }
+        Pm = tn0<D, true>(S, Pp);
+        scale_rows<D>(Pm, rom);
+        vec_put<D>(vm, in ? om - Om * si : 0.0);
+      } else {
+        vec_put<D>(vs, si);
+        const RM<D> R = tn0<D>(S, Pp);
+        Pm = tn0<D, true>(Pp, R);
+        rm_rsub<D>(Pm, Pp);
+        const double b = mv<D>(Pp, rv<D>(vs));
+        vec_put<D>(vm, mp + b);
+      }
+    }
+    q = wave_total(q);
+    if (l == 0) P.ell[t] = -0.5 * (dobs * 1.8378770664093454835606594728112 + ld.value() + q);
+    symm<D>(Pm, scr);
+    if (P.mf) {
+      if (in) P.mf[(int64_t)t * P.ldm + l] = vm[l];
+      rm_store<D>(Pm, P.Pf + (int64_t)t * P.ldm * P.ldm, P.ldm, d);
+    }
+  }
+  if (!ok && l == 0) atomicOr(P.status, P.fail_bit);
+}
+
+// ---------------------------------------------------------------------------
+// Sampler, element build (the formulas above samp_build_body)
+// ---------------------------------------------------------------------------
+template <int D>
+__device__ __forceinline__ void wave_sbuild(const KModel& M, const SampArgs& S, int t) {
+  extern __shared__ double lds[];
+  double* scr = lds;
+  double* va = scr + wave_scr<D>();
+  double* vxi = va + D;
+  const int l = threadIdx.x, d = M.d;
+  const bool in = l < d;
+  RM<D> Pf, L, LT;
+  rm_load<D>(Pf, S.Pf + (int64_t)t * S.ldm * S.ldm, S.ldm, d);
+  const double m = in ? S.mf[(int64_t)t * S.ldm + l] : 0.0;
+  vec_put<D>(va, m);
+  vec_put<D>(vxi, in ? S.xi_x[(int64_t)t * d + l] : 0.0);
+  bool ok = true;
+  double g = m;
+  if (t == M.N - 1) {
+    ok = wave_chol<D>(Pf, L, LT, d, scr);
+    RM<D> Z;
+    rm_zero<D>(Z);
+    rm_store<D>(Z, S.E + (int64_t)t * D * D, D, D);
+    if (S.Et) rm_store<D>(Z, S.Et + (int64_t)t * D * D, D, D);
+  } else {
+    // the transition into step t + 1
+    RM<D> FT, Pp, X;
+    rm_load_t<D>(FT, S.Ft ? S.Ft + (int64_t)(t + 1) * d * d : M.F, d, d, d);
+    rm_load<D>(Pp, M.Q, d, d);
+    const double* bt = S.Ft ? S.bt + (int64_t)(t + 1) * d : M.b;
+    const double mp = ((in && bt) ? bt[l] : 0.0) + mv<D>(FT, rv<D>(va));
+    RM<D> G;
+    {
+      const RM<D> GT = tn0<D>(Pf, FT);  // P^f F' = G'
+      tn<D, true>(Pp, FT, GT);          // Q + F P^f F'
+      mirror<D>(Pp, scr);
+      G = rm_t<D>(GT, scr);
+    }
+    X = Pp;
+    LogDet ld;
+    ok = wave_inv<D>(X, d, scr, ld);
+    {  // Newton-Schulz step X + X (I - P^p X): P^p inherits the conditioning of Q
+      RM<D> R = tn0<D>(Pp, X);
+      AKF_RM_FOR(D, q, r, i, j) R.t[q][r] = ((i == j && i < d) ? 1.0 : 0.0) - R.t[q][r];
+      const RM<D> Xo = X;
+      tn<D>(X, Xo, R);
+    }
+    const RM<D> ET = tn0<D>(X, G);  // E' = (P^p)^{-1} G
+    {
+      const RM<D> E = rm_t<D>(ET, scr);
+      rm_store<D>(E, S.E + (int64_t)t * D * D, D, D);
+    }
+    if (S.Et) rm_store<D>(ET, S.Et + (int64_t)t * D * D, D, D);
+    vec_put<D>(va, mp);
+    g = m - mv<D>(ET, rv<D>(va));  // m^f - E m^p
+    RM<D> Lm = tn0<D, true>(G, ET);  // E G
+    rm_rsub<D>(Lm, Pf);              // L_t = P^f - E G
+    symm<D>(Lm, scr);
+    ok = wave_chol<D>(Lm, L, LT, d, scr) && ok;
+  }
+  if (S.Lc) rm_store<D>(LT, S.Lc + (int64_t)t * D * D, D, D);  // chol(L_t), kept transposed
+  const double u = g + mv<D>(LT, rv<D>(vxi));
+  if (l < D) S.U[(int64_t)t * D + l] = u;
+  if (!ok && l == 0) atomicOr(S.status, ST_FWD_NOT_PD);
+}
+
+}  // namespace akf

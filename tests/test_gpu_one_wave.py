@@ -1,0 +1,92 @@
+"""The one-wave filter and sampler bodies (widths 16 and 32) at the edges of
+their tiles: d and d_y on either side of a tile, blocks of one step, a single
+time step.  Compared with the FP64 oracle; models are well conditioned (cond
+below 1e3), so 64-bit recursions agree to 1e-9 (the bound of the parity tests).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2303_00301_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-9
+
+
+@pytest.fixture(scope="module")
+def S():
+    from paper_2303_00301_amd import sampler
+    return sampler
+
+
+def T(a):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda")
+
+
+def N_(t):
+    return t.detach().cpu().numpy()
+
+
+def _rel(a, b):
+    return np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300)
+
+
+def _model(rng, d):
+    A = rng.standard_normal((d, d))
+    return (rng.standard_normal(d), np.eye(d) + 0.1 * np.ones((d, d)),
+            W.random_stable_F(rng, d, 0.9), 0.1 * rng.standard_normal(d),
+            A @ A.T / d + 0.2 * np.eye(d))
+
+
+@pytest.mark.parametrize("d", [1, 15, 16, 17, 31, 32])
+@pytest.mark.parametrize("N,block", [(1, 0), (6, 1), (29, 4)])
+def test_filter_and_sampler(S, d, N, block):
+    rng = np.random.default_rng(100 * d + N)
+    m0, P0, F, b, Q = _model(rng, d)
+    om, Om = rng.standard_normal((N, d)), rng.uniform(0.1, 2.0, size=(N, d))
+    xi = rng.standard_normal((N, d))
+    ref = oracle.kf(m0, P0, F, Q, np.eye(d), np.stack([np.diag(o) for o in Om]), om, b=b,
+                    R_per_t=True)
+    x_ref, rc = oracle.rts_sample(F, ref["mf"], ref["Pf"], ref["mp"], ref["Pp"], xi)
+    assert ref["rc"] == 0 and rc == 0
+    M = S.DeviceModel.from_arrays(N, m0, P0, F, Q, 1, b=b)
+    mf, Pf, ell, st = S.aux_filter(M, T(om), T(Om), block=block)
+    x, st2 = S.rts_sample(M, mf, Pf, T(xi), block=block)
+    assert int(st[0]) == 0 and int(st2[0]) == 0
+    for got, want in ((mf, ref["mf"]), (Pf, ref["Pf"]), (ell, ref["ell"]), (x, x_ref)):
+        assert _rel(N_(got), want) < TOL
+
+
+@pytest.mark.parametrize("d,dy", [(16, 3), (17, 17), (32, 5)])
+def test_dense_gaussian_step(S, d, dy):
+    """Order 2 with Gaussian emissions: the dense constant Omega."""
+    rng = np.random.default_rng(d + dy)
+    N = 21
+    m0, P0, F, b, Q = _model(rng, d)
+    H, R = rng.standard_normal((dy, d)) / np.sqrt(d), 0.5 * np.eye(dy) + 0.1 * np.ones((dy, dy))
+    y, x = rng.standard_normal((N, dy)), rng.standard_normal((N, d))
+    xi = rng.standard_normal((2, N, d))
+    kw = dict(m0=m0, P0=P0, F=F, Q=Q, b=b, H=H, R=R)
+    r = oracle.mh_step(oracle.Model(emit=W.EMIT_GAUSSIAN, **kw), y, x, 0.5, 2, xi[0], xi[1], 0.4)
+    M = S.DeviceModel.from_arrays(N, emit=S.EMIT_GAUSSIAN, **kw)
+    out = S.mh_step(M, T(y), T(x), 0.5, 2, T(xi), T([0.4]), block=4)
+    assert int(out["status"][0]) == 0 and int(out["accepted"][0]) == 1
+    assert _rel(N_(out["logZ_fwd"])[0], r["logZ_fwd"]) < TOL
+    assert _rel(N_(out["logZ_rev"])[0], r["logZ_rev"]) < TOL
+    assert _rel(N_(out["x_out"]), r["x_out"]) < TOL
+
+
+@pytest.mark.parametrize("dx,dy", [(16, 16), (17, 16), (16, 17), (5, 32), (32, 1), (32, 17)])
+@pytest.mark.parametrize("N,block", [(1, 0), (23, 4)])
+def test_general_observations(S, dx, dy, N, block):
+    """Log-likelihood (general H, R) on either side of one tile of observations."""
+    pw = W.lgssm_params(N=N, dx=dx, dy=dy, seed=dx + dy)
+    t = pw.theta0
+    ref = oracle.kf(pw.m0, pw.P0, t.F, np.diag(np.exp(t.logq)), t.H, np.diag(np.exp(t.logr)), pw.y)
+    model = S.LGSSM(pw.m0, pw.P0, pw.y)
+    ll, ell, st, _ = S.lgssm_loglik(model, T(t.F), T(t.logq), T(t.H), T(t.logr), block=block,
+                                    ell=True)
+    assert int(st[0]) == 0
+    assert _rel(N_(ell), ref["ell"]) < TOL
+    assert abs(float(ll[0]) - ref["ell"].sum()) < TOL * max(1.0, abs(ref["ell"].sum()))
