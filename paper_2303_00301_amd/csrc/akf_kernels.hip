@@ -1504,22 +1504,26 @@ __global__ void __launch_bounds__(64) k_samp_down(KModel M, TreeArgs T) {
 template <int D>
 __device__ __forceinline__ void samp_final_body(const KModel& M, const SampArgs& S, int item) {
   __shared__ double vx[64];
-  __shared__ double vn[64];
-  const int blk = item, tid = threadIdx.x, d = M.d;
-  const int s0 = blk * S.B, s1 = min(M.N, s0 + S.B);
-  if (tid < D) vx[tid] = S.xin[(int64_t)blk * D + tid];
-  __syncthreads();
-  for (int t = s1 - 1; t >= s0; --t) {
-    const double* Et = S.E + (int64_t)t * D * D;
-    if (tid < D) {
-      double s = S.U[(int64_t)t * D + tid];
-      for (int j = 0; j < D; ++j) s = fma(Et[tid * D + j], vx[j], s);
-      vn[tid] = s;
+  const int blk = item, tid = threadIdx.x;
+  if constexpr (D <= 32) {
+    wave_path<D>(M, S, blk, S.xin[(int64_t)blk * D + tid % D], vx);
+  } else {
+    __shared__ double vn[64];
+    const int d = M.d, s0 = blk * S.B, s1 = min(M.N, s0 + S.B);
+    if (tid < D) vx[tid] = S.xin[(int64_t)blk * D + tid];
+    __syncthreads();
+    for (int t = s1 - 1; t >= s0; --t) {
+      const double* Et = S.E + (int64_t)t * D * D;
+      if (tid < D) {
+        double s = S.U[(int64_t)t * D + tid];
+        for (int j = 0; j < D; ++j) s = fma(Et[tid * D + j], vx[j], s);
+        vn[tid] = s;
+      }
+      __syncthreads();
+      if (tid < D) vx[tid] = vn[tid];
+      if (tid < d) S.xs[(int64_t)t * d + tid] = vn[tid];
+      __syncthreads();
     }
-    __syncthreads();
-    if (tid < D) vx[tid] = vn[tid];
-    if (tid < d) S.xs[(int64_t)t * d + tid] = vn[tid];
-    __syncthreads();
   }
 }
 
@@ -1527,6 +1531,24 @@ template <int D>
 __global__ void __launch_bounds__(64) k_samp_final(KModel M, SampArgs S) {
   if (gate_shut(M.gate)) return;
   samp_final_body<D>(M, S, blockIdx.x);
+}
+
+// One chain, D <= 32: the scan over the aggregates (one launch per level of
+// more than kPathRadix nodes) and the final pass that starts from it.
+template <int D>
+__global__ void __launch_bounds__(64 * kPathRadix) k_path_scan(KModel M, double* agg, int n,
+                                                               int64_t str) {
+  if (gate_shut(M.gate)) return;
+  path_scan<D>(agg, n, str, blockIdx.x);
+}
+
+template <int D>
+__global__ void __launch_bounds__(64) k_path_final(KModel M, SampArgs S, const double* root,
+                                                   int nb) {
+  if (gate_shut(M.gate)) return;
+  __shared__ double vx[D];
+  const double x = path_entry<D>(S.agg, nb, root, blockIdx.x, vx);
+  wave_path<D>(M, S, blockIdx.x, x, vx);
 }
 
 // ---------------------------------------------------------------------------
@@ -1751,21 +1773,36 @@ hipError_t launch_samp_scan(const KModel& M, SampArgs S, TreeArgs* lv_up, TreeAr
   timing_mark(FAM_SAMP_FOLD, 1, st);
   hipLaunchKernelGGL(k_samp_fold<D>, dim3(nb), dim3(Cfg<D>::NT), lds_bytes_samp2<D>(), st, M, S);
   timing_mark(FAM_SAMP_FOLD, 0, st);
-  for (int l = 0; l < n_levels; ++l) {
-    timing_mark(FAM_SAMP_UP, 1, st);
-    hipLaunchKernelGGL(k_samp_up<D>, dim3(lv_up[l].n_dst), dim3(Cfg<D>::NT), lds_bytes_samp2<D>(),
-                       st, M, lv_up[l]);
-    timing_mark(FAM_SAMP_UP, 0, st);
+  if constexpr (D <= 32) {
+    const double* root = n_levels > 0 ? lv_down[n_levels - 1].pre_src : S.xin;
+    int64_t str = 1;
+    for (int n = nb; n > kPathRadix; n = (n + kPathRadix - 1) / kPathRadix, str *= kPathRadix) {
+      timing_mark(FAM_SAMP_UP, 1, st);
+      hipLaunchKernelGGL(k_path_scan<D>, dim3((n + kPathRadix - 1) / kPathRadix),
+                         dim3(64 * kPathRadix), path_scan_lds_bytes<D>(), st, M, S.agg, n, str);
+      timing_mark(FAM_SAMP_UP, 0, st);
+    }
+    timing_mark(FAM_SAMP_FINAL, 1, st);
+    hipLaunchKernelGGL(k_path_final<D>, dim3(nb), dim3(64), 0, st, M, S, root, nb);
+    timing_mark(FAM_SAMP_FINAL, 0, st);
+    return hipGetLastError();
+  } else {
+    for (int l = 0; l < n_levels; ++l) {
+      timing_mark(FAM_SAMP_UP, 1, st);
+      hipLaunchKernelGGL(k_samp_up<D>, dim3(lv_up[l].n_dst), dim3(Cfg<D>::NT), lds_bytes_samp2<D>(),
+                         st, M, lv_up[l]);
+      timing_mark(FAM_SAMP_UP, 0, st);
+    }
+    for (int l = n_levels - 1; l >= 0; --l) {
+      timing_mark(FAM_SAMP_DOWN, 1, st);
+      hipLaunchKernelGGL(k_samp_down<D>, dim3(lv_down[l].n_src), dim3(64), 0, st, M, lv_down[l]);
+      timing_mark(FAM_SAMP_DOWN, 0, st);
+    }
+    timing_mark(FAM_SAMP_FINAL, 1, st);
+    hipLaunchKernelGGL(k_samp_final<D>, dim3(nb), dim3(64), 0, st, M, S);
+    timing_mark(FAM_SAMP_FINAL, 0, st);
+    return hipGetLastError();
   }
-  for (int l = n_levels - 1; l >= 0; --l) {
-    timing_mark(FAM_SAMP_DOWN, 1, st);
-    hipLaunchKernelGGL(k_samp_down<D>, dim3(lv_down[l].n_src), dim3(64), 0, st, M, lv_down[l]);
-    timing_mark(FAM_SAMP_DOWN, 0, st);
-  }
-  timing_mark(FAM_SAMP_FINAL, 1, st);
-  hipLaunchKernelGGL(k_samp_final<D>, dim3(nb), dim3(64), 0, st, M, S);
-  timing_mark(FAM_SAMP_FINAL, 0, st);
-  return hipGetLastError();
 }
 
 template <int D>
@@ -1810,6 +1847,11 @@ hipError_t set_lds_limits() {
                        (const void*)k_filter_hs<D>};
   for (const void* f : fns)
     if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lf)) != hipSuccess)
+      return e;
+  if constexpr (D <= 32)
+    if ((e = hipFuncSetAttribute((const void*)k_path_scan<D>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)path_scan_lds_bytes<D>())) != hipSuccess)
       return e;
   if ((e = hipFuncSetAttribute((const void*)k_filter_up<D>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, lf)) != hipSuccess)

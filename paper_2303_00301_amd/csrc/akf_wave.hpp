@@ -132,24 +132,28 @@ __device__ __forceinline__ RV<D> rv(const double* s) {
   return o;
 }
 
-// s plus the values of the other lanes with the same l%16 (two half exchanges
-// in the vector unit; a lane permute through LDS takes 83 cycles each)
-__device__ __forceinline__ double sum_groups(double s) {
-  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-  auto both = [](u2 lo, u2 hi) {
-    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
-           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
-  };
-  uint64_t u = __builtin_bit_cast(uint64_t, s);
-  uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
-  s = both(__builtin_amdgcn_permlane16_swap(lo, lo, false, false),
-           __builtin_amdgcn_permlane16_swap(hi, hi, false, false));
-  u = __builtin_bit_cast(uint64_t, s);
-  lo = (uint32_t)u;
-  hi = (uint32_t)(u >> 32);
-  return both(__builtin_amdgcn_permlane32_swap(lo, lo, false, false),
-              __builtin_amdgcn_permlane32_swap(hi, hi, false, false));
+// s plus the value of the lane 16 (32) on in the wave's exchange order: a half
+// exchange in the vector unit (a lane permute through LDS takes 83 cycles)
+__device__ __forceinline__ double half_sum(uint32_t lo0, uint32_t hi0, uint32_t lo1, uint32_t hi1) {
+  return __builtin_bit_cast(double, ((uint64_t)hi0 << 32) | lo0) +
+         __builtin_bit_cast(double, ((uint64_t)hi1 << 32) | lo1);
 }
+__device__ __forceinline__ double sum_x16(double s) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, s);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return half_sum(a[0], b[0], a[1], b[1]);
+}
+__device__ __forceinline__ double sum_x32(double s) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, s);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return half_sum(a[0], b[0], a[1], b[1]);
+}
+// sum over the lanes with the same l%16
+__device__ __forceinline__ double sum_groups(double s) { return sum_x32(sum_x16(s)); }
 
 // lane (l + N) of the row of 16
 template <int N>
@@ -795,6 +799,163 @@ __device__ __forceinline__ void wave_sbuild(const KModel& M, const SampArgs& S, 
   const double u = g + mv<D>(LT, rv<D>(vxi));
   if (l < D) S.U[(int64_t)t * D + l] = u;
   if (!ok && l == 0) atomicOr(S.status, ST_FWD_NOT_PD);
+}
+
+// ---------------------------------------------------------------------------
+// Sampler, scan over the block aggregates and final pass.  Only the path is
+// wanted, so once every aggregate is a suffix product of its group the state
+// entering a block is a short chain of matrix-vector products, formed by the
+// block's own wave before its steps.  kPathRadix aggregates are scanned in one
+// workgroup, a wave each, in log2 steps through LDS; a tree of pairs took one
+// launch per level up and one down (16 launches of 2.3 - 3.4 us at 256 blocks
+// of width 16).
+// ---------------------------------------------------------------------------
+constexpr int kPathRadix = 16;
+
+template <int D>
+constexpr size_t path_scan_lds_bytes() {
+  return (size_t)kPathRadix * (Cfg<D>::MAT + D) * sizeof(double);
+}
+
+// Node j of the level (an aggregate, str apart) becomes node j o ... o the
+// last of its group of kPathRadix, in place.  The group's first node is then
+// its total, the group's node one level up (str * kPathRadix).
+template <int D>
+__device__ __forceinline__ void path_scan(double* agg, int n, int64_t str, int group) {
+  using SL = SampLayout<D>;
+  extern __shared__ double lds[];
+  constexpr int SLOT = Cfg<D>::MAT + D;
+  const int l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cnt = min(kPathRadix, n - group * kPathRadix);
+  const bool on = w < cnt;
+  double* my = lds + w * SLOT;
+  double* el = agg + (int64_t)(group * kPathRadix + w) * str * SL::SIZE;
+  RM<D> ET;  // the node's E transposed: x' y of a right neighbour's E with it is (E E_r)'
+  double u = 0.0;
+  if (on) {
+    RM<D> X;
+    rm_load<D>(X, el + SL::E, D, D);
+    u = el[SL::U + l % D];
+    rm_stage<D>(X, my);
+    if (l < D) my[Cfg<D>::MAT + l] = u;
+    wave_lds_fence();
+    AKF_RM_FOR(D, q, r, i, j) ET.t[q][r] = my[j * Cfg<D>::LD + i];
+  }
+#pragma unroll 1
+  for (int s = 1; s < kPathRadix; s <<= 1) {
+    __syncthreads();
+    const bool go = w + s < cnt;
+    RM<D> c;
+    double un = 0.0;
+    if (go) {
+      const double* nb = my + s * SLOT;
+      RM<D> X;
+      rm_unstage<D>(X, nb);
+      un = u + mv<D>(ET, rv<D>(nb + Cfg<D>::MAT));
+      c = tn0<D>(X, ET);
+    }
+    __syncthreads();
+    if (go) {
+      ET = c;
+      u = un;
+      rm_stage_t<D>(ET, my);
+      if (l < D) my[Cfg<D>::MAT + l] = u;
+    }
+  }
+  if (w + 1 < cnt) {  // the last node of a group is unchanged
+    wave_lds_fence();
+    RM<D> X;
+    rm_unstage<D>(X, my);
+    rm_store<D>(X, el + SL::E, D, D);
+    if (l < D) el[SL::U + l] = u;
+  }
+}
+
+// Row l % D of a D x D matrix in global memory, a part of its columns per lane
+template <int D>
+struct PathRow {
+  double e[D * D / 64];
+  double u;
+};
+template <int D>
+__device__ __forceinline__ PathRow<D> path_row(const double* __restrict__ E,
+                                               const double* __restrict__ U) {
+  constexpr int JL = D * D / 64;
+  const int l = threadIdx.x & 63;
+  PathRow<D> o;
+#pragma unroll
+  for (int m = 0; m < JL; ++m) o.e[m] = E[(l % D) * D + (l / D) * JL + m];
+  o.u = U[l % D];
+  return o;
+}
+// E x + U for the lane's row; x by lane (l % D), exchanged through vx
+template <int D>
+__device__ __forceinline__ double path_apply(const PathRow<D>& R, double x, double* vx) {
+  constexpr int JL = D * D / 64;
+  const int l = threadIdx.x & 63;
+  vec_put<D>(vx, x);
+  double a = 0.0, b = 0.0;
+#pragma unroll
+  for (int m = 0; m < JL; m += 2) {
+    a = fma(R.e[m], vx[(l / D) * JL + m], a);
+    b = fma(R.e[m + 1], vx[(l / D) * JL + m + 1], b);
+  }
+  wave_lds_fence();
+  a += b;
+  return R.u + (D == 16 ? sum_groups(a) : sum_x32(a));
+}
+
+// x* just after block k, from the state `root` after the last block and the n
+// scanned aggregates (path_scan on every level of more than kPathRadix nodes)
+template <int D>
+__device__ __forceinline__ double path_entry(const double* agg, int n, const double* root, int k,
+                                             double* vx) {
+  using SL = SampLayout<D>;
+  auto row = [&](int64_t j) {
+    const double* el = agg + j * SL::SIZE;
+    return path_row<D>(el + SL::E, el + SL::U);
+  };
+  int64_t str = 1;
+  int top = n;
+  while (top > kPathRadix) {
+    top = (top + kPathRadix - 1) / kPathRadix;
+    str *= kPathRadix;
+  }
+  double x = root[threadIdx.x % D];
+  const int jt = (int)(k / str);
+  if (top - 1 > jt) {
+    PathRow<D> nx = row((top - 1) * str);
+    for (int j = top - 1; j > jt; --j) {
+      const PathRow<D> cur = nx;
+      if (j - 1 > jt) nx = row((j - 1) * str);
+      x = path_apply<D>(cur, x, vx);
+    }
+  }
+  while (str > 1) {
+    str /= kPathRadix;
+    const int64_t j = k / str + 1, nl = (n + str - 1) / str;
+    if (j % kPathRadix != 0 && j < nl) x = path_apply<D>(row(j * str), x, vx);
+  }
+  return x;
+}
+
+// x*_t = E_t x*_{t+1} + U_t inside block `item`, x = x* just after it
+template <int D>
+__device__ __forceinline__ void wave_path(const KModel& M, const SampArgs& S, int item, double x,
+                                          double* vx) {
+  const int l = threadIdx.x & 63, d = M.d;
+  const int s0 = item * S.B, s1 = min(M.N, s0 + S.B);
+  auto row = [&](int t) {
+    return path_row<D>(S.E + (int64_t)t * D * D, S.U + (int64_t)t * D);
+  };
+  PathRow<D> nx = row(s1 - 1);
+  for (int t = s1 - 1; t >= s0; --t) {
+    const PathRow<D> cur = nx;
+    if (t > s0) nx = row(t - 1);
+    x = path_apply<D>(cur, x, vx);
+    if (l < d) S.xs[(int64_t)t * d + l] = x;
+  }
 }
 
 }  // namespace akf

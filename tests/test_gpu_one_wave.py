@@ -90,3 +90,19 @@ def test_general_observations(S, dx, dy, N, block):
     assert int(st[0]) == 0
     assert _rel(N_(ell), ref["ell"]) < TOL
     assert abs(float(ll[0]) - ref["ell"].sum()) < TOL * max(1.0, abs(ref["ell"].sum()))
+
+
+@pytest.mark.parametrize("N,d,block", [(17, 4, 1), (300, 3, 1), (260, 17, 1), (4200, 2, 1)])
+def test_path_scan_levels(S, N, d, block):
+    """Path sampler with one, two and three levels over the block aggregates."""
+    rng = np.random.default_rng(N + d)
+    m0, P0, F, b, Q = _model(rng, d)
+    om, Om = rng.standard_normal((N, d)), rng.uniform(0.1, 2.0, size=(N, d))
+    xi = rng.standard_normal((N, d))
+    ref = oracle.kf(m0, P0, F, Q, np.eye(d), np.stack([np.diag(o) for o in Om]), om, b=b,
+                    R_per_t=True)
+    x_ref, rc = oracle.rts_sample(F, ref["mf"], ref["Pf"], ref["mp"], ref["Pp"], xi)
+    M = S.DeviceModel.from_arrays(N, m0, P0, F, Q, 1, b=b)
+    x, st = S.rts_sample(M, T(ref["mf"]), T(ref["Pf"]), T(xi), block=block)
+    assert rc == 0 and int(st[0]) == 0
+    assert _rel(N_(x), x_ref) < TOL
