@@ -625,11 +625,10 @@ akf_status akf_lgssm_loglik_grad(const akf_lgssm* m, const double* ll_bar, doubl
   Mv.d = D;
   if ((s = hip_check(launch_samp_scan_any(D, Mv, S, up, down, Lo.L, st), "mbar scan")) != AKF_OK)
     return s;
-  // G_t in place of Cm, then Pbar: (E, L) scan
-  if ((s = hip_check(launch_adj_G_any(D, G, m->N, st), "adjoint G")) != AKF_OK) return s;
-  if ((s = run_egl(Lo, ws, nullptr, G.Pbar, nullptr, D, D, st)) != AKF_OK) return s;
-  // Gradient blocks: at width 32 a one-wave team of k_adj_grad fits three to a
-  // CU, so blocks of at least Lo.B steps are made long enough that all of them
+  // Pbar: (E, L) scan with L_t = G_t = Cm_t + sym((mbar_t - h_t) h_t')
+  if ((s = run_egl(Lo, ws, nullptr, G.Pbar, nullptr, D, D, st, G.mbar, G.U)) != AKF_OK) return s;
+  // Gradient blocks: at width 32 a one-wave team of k_adj_grad holds a SIMD's
+  // registers, four to a CU, so blocks of at least Lo.B steps are made long enough that all of them
   // run at once (there are then no more of them than the layout's partial
   // sums hold)
   int nblk = Lo.nb;
@@ -639,7 +638,7 @@ akf_status akf_lgssm_loglik_grad(const akf_lgssm* m, const double* ll_bar, doubl
     if ((s = hip_check(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev),
                        "CU count query")) != AKF_OK)
       return s;
-    const int slots = 3 * (ncu > 0 ? ncu : 1);
+    const int slots = 4 * (ncu > 0 ? ncu : 1);
     const int Bg = std::max(Lo.B, (m->N + slots - 1) / slots);
     G.B = Bg;
     nblk = (m->N + Bg - 1) / Bg;

@@ -256,6 +256,9 @@ struct EglArgs {
   double* outL;  // [N*ldo*ldo]
   double* outg;  // [N*ldo] or nullptr
   int ldo, dout;
+  // D <= 32: sym((mb_t - h_t) h_t') is added to L_t as it is read ([N*D] each,
+  // or nullptr)
+  const double *mb, *h;
 };
 
 struct EglTree {
@@ -361,7 +364,6 @@ hipError_t launch_smooth_build_any(int D, const KModel& M, SmoothArgs S, hipStre
 hipError_t launch_lgssm_prep(LgArgs G, hipStream_t st);
 hipError_t launch_sum(const double* a, int n, double* out, const int* status, hipStream_t st);
 hipError_t launch_adj_build_any(int D, const KModel& M, LgArgs G, hipStream_t st);
-hipError_t launch_adj_G_any(int D, LgArgs G, int N, hipStream_t st);
 hipError_t launch_adj_finish_any(int D, const KModel& M, LgArgs G, int nblk, const double* ll_bar,
                                  hipStream_t st);
 hipError_t launch_zero(double* p, int64_t n, hipStream_t st);

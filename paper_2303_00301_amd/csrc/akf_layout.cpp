@@ -28,13 +28,12 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 int pick_D(int d) { return d <= 16 ? 16 : (d <= 32 ? 32 : (d <= 64 ? 64 : 0)); }
 
 // Default scan block: enough blocks to give every CU (256) its resident teams
-// and no more, so that the fold runs in one round (LDS-limited: 1 team of 4
-// waves at D = 64; at D = 32 four single-wave teams, three with a general
-// observation matrix, whose fold holds a fifth matrix; eight at D = 16), and at
+// and no more, so that the fold runs in one round (register-limited: 1 team of
+// 4 waves at D = 64, four single-wave teams at D = 32, eight at D = 16), and at
 // least 4 steps per block so that small problems do not pay for a deep tree of
 // tiny launches.
-int auto_block(int N, int D, bool general_obs) {
-  const int teams_per_cu = D == 64 ? 1 : (D == 32 ? (general_obs ? 3 : 4) : 8);
+int auto_block(int N, int D) {
+  const int teams_per_cu = D == 64 ? 1 : (D == 32 ? 4 : 8);
   const int target = 256 * teams_per_cu;
   int B = (N + target - 1) / target;
   if (B < 4) B = 4;
@@ -48,7 +47,7 @@ void make_layout(Layout& Lo, int N, int d, int dy, int block, int kind, bool dyn
   Lo.dy = dy;
   Lo.D = pick_D(d);
   const int D = Lo.D;
-  Lo.B = block > 0 ? (block > N ? N : block) : auto_block(N, D, kind == LAYOUT_LGSSM);
+  Lo.B = block > 0 ? (block > N ? N : block) : auto_block(N, D);
   Lo.nb = (N + Lo.B - 1) / Lo.B;
   Lo.n_lvl[0] = Lo.nb;
   Lo.L_hs = 0;
@@ -465,7 +464,7 @@ void fill_egl_tree(const Layout& Lo, void* ws, EglTree* up, EglTree* down) {
 
 // Suffix (E, g, L) scan over E = ws.E, L = ws.Lm, g (nullable); writes outL/outg.
 akf_status run_egl(const Layout& Lo, void* ws, const double* g, double* outL, double* outg,
-                   int ldo, int dout, hipStream_t st) {
+                   int ldo, int dout, hipStream_t st, const double* mb, const double* h) {
   const int D = Lo.D;
   akf_status s;
   // the suffix state entering the last block is zero (it meets E = 0)
@@ -484,6 +483,8 @@ akf_status run_egl(const Layout& Lo, void* ws, const double* g, double* outL, do
   A.outg = outg;
   A.ldo = ldo;
   A.dout = dout;
+  A.mb = mb;
+  A.h = h;
   EglTree up[kMaxLevels], down[kMaxLevels];
   fill_egl_tree(Lo, ws, up, down);
   return hip_check(launch_egl_scan_any(D, A, up, down, Lo.L, st), "(E,g,L) scan launch");

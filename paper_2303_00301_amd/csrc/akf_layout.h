@@ -61,7 +61,7 @@ T* at(void* ws, size_t off) {
 
 akf_status fail(akf_status s, const char* fmt, ...);
 int pick_D(int d);
-int auto_block(int N, int D, bool general_obs);
+int auto_block(int N, int D);
 void make_layout(Layout& Lo, int N, int d, int dy, int block, int kind, bool dyn = false,
                  bool fixed = false);
 // workspace layout of akf_lgssm_loglik / akf_lgssm_loglik_grad (filtering
@@ -94,7 +94,8 @@ akf_status run_sampler(const Layout& Lo, const KModel& M, void* ws, const double
                        double* Lc = nullptr, double* Et = nullptr);
 void fill_egl_tree(const Layout& Lo, void* ws, EglTree* up, EglTree* down);
 akf_status run_egl(const Layout& Lo, void* ws, const double* g, double* outL, double* outg,
-                   int ldo, int dout, hipStream_t st);
+                   int ldo, int dout, hipStream_t st, const double* mb = nullptr,
+                   const double* h = nullptr);
 const char* last_error();
 
 }  // namespace akf

@@ -106,6 +106,13 @@ __device__ __forceinline__ void symm(RM<D>& c, double* scr) {
   for (int k = 0; k < TS; ++k) c.t[k * TS + k] = 0.5 * (c.t[k * TS + k] + o[k]);
 }
 
+// a_ij = G[i*ld + j] for i < rows, j < cols, zero elsewhere
+template <int D>
+__device__ __forceinline__ void rm_load_rect(RM<D>& a, const double* __restrict__ g, int ld,
+                                             int rows, int cols) {
+  AKF_RM_FOR(D, q, r, i, j) a.t[q][r] = (i < rows && j < cols) ? g[(size_t)i * ld + j] : 0.0;
+}
+
 // a_ij = G[j*ld + i] for i < rows, j < cols, zero elsewhere
 template <int D>
 __device__ __forceinline__ void rm_load_t(RM<D>& a, const double* __restrict__ g, int ld, int rows,

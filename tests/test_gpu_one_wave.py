@@ -80,14 +80,19 @@ def test_dense_gaussian_step(S, d, dy):
 @pytest.mark.parametrize("dx,dy", [(16, 16), (17, 16), (16, 17), (5, 32), (32, 1), (32, 17)])
 @pytest.mark.parametrize("N,block", [(1, 0), (23, 4)])
 def test_general_observations(S, dx, dy, N, block):
-    """Log-likelihood (general H, R) on either side of one tile of observations."""
+    """Log-likelihood and gradient (general H, R) on either side of one tile of
+    observations; the gradient within the adjoint tests' bound."""
     pw = W.lgssm_params(N=N, dx=dx, dy=dy, seed=dx + dy)
     t = pw.theta0
     ref = oracle.kf(pw.m0, pw.P0, t.F, np.diag(np.exp(t.logq)), t.H, np.diag(np.exp(t.logr)), pw.y)
     model = S.LGSSM(pw.m0, pw.P0, pw.y)
-    ll, ell, st, _ = S.lgssm_loglik(model, T(t.F), T(t.logq), T(t.H), T(t.logr), block=block,
-                                    ell=True)
-    assert int(st[0]) == 0
+    th = (T(t.F), T(t.logq), T(t.H), T(t.logr))
+    ll, ell, st, ws = S.lgssm_loglik(model, *th, block=block, ell=True)
+    g = S.lgssm_loglik_grad(model, *th, ws, block=block)
+    assert int(st[0]) == 0 and int(g[4][0]) == 0
+    _, *g_ref = oracle.fisher_score(pw.m0, pw.P0, t.F, t.logq, t.H, t.logr, pw.y)
+    for got, want in zip(g[:4], g_ref):
+        assert np.linalg.norm(N_(got) - want) < 1e-8 * max(1.0, np.linalg.norm(want))
     assert _rel(N_(ell), ref["ell"]) < TOL
     assert abs(float(ll[0]) - ref["ell"].sum()) < TOL * max(1.0, abs(ref["ell"].sum()))
 
