@@ -37,6 +37,7 @@
 #include "../../include/akf.h"
 #include "akf_internal.h"
 #include "akf_layout.h"
+#include "akf_team.hpp"
 
 namespace akf {
 namespace sq {
@@ -135,21 +136,39 @@ __device__ __forceinline__ void cp_mat(T* dst, const T* src) {
 }
 
 // C = op(A) op(B) (+ Cadd, which may be C itself); C must not alias A or B.
+// Thread (ti, tj) forms the elements (ti + 16 u, tj + 16 v), each a chain over
+// ascending k.
 template <class T, int D, bool TA, bool TB>
 __device__ __forceinline__ void mm(T* __restrict__ C, const T* __restrict__ A, const T* __restrict__ B, int d,
                    const T* Cadd = nullptr, T sign = T(1)) {
-  constexpr int L = Dm<D>::LM;
-  for (int e = threadIdx.x; e < D * D; e += NT) {
-    const int i = e / D, j = e % D;
-    T acc = T(0);
+  constexpr int L = Dm<D>::LM, NB = D / 16;
+  const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
+  T acc[NB][NB];
 #pragma unroll
-    for (int k = 0; k < D; ++k) {  // the zero padding makes the padded width exact
-      const T a = TA ? A[k * L + i] : A[i * L + k];
-      const T b = TB ? B[j * L + k] : B[k * L + j];
-      acc = fma(a, b, acc);
+  for (int u = 0; u < NB; ++u)
+#pragma unroll
+    for (int v = 0; v < NB; ++v) acc[u][v] = T(0);
+#pragma unroll
+  for (int k = 0; k < D; ++k) {  // the zero padding makes the padded width exact
+    T a[NB], b[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int i = ti + 16 * u, j = tj + 16 * u;
+      a[u] = TA ? A[k * L + i] : A[i * L + k];
+      b[u] = TB ? B[j * L + k] : B[k * L + j];
     }
-    C[i * L + j] = (Cadd ? Cadd[i * L + j] : T(0)) + sign * acc;
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+#pragma unroll
+      for (int v = 0; v < NB; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
   }
+#pragma unroll
+  for (int u = 0; u < NB; ++u)
+#pragma unroll
+    for (int v = 0; v < NB; ++v) {
+      const int e = (ti + 16 * u) * L + tj + 16 * v;
+      C[e] = (Cadd ? Cadd[e] : T(0)) + sign * acc[u][v];
+    }
   __syncthreads();
 }
 
@@ -168,64 +187,82 @@ __device__ __forceinline__ void mv(T* __restrict__ y, const T* __restrict__ A, c
   __syncthreads();
 }
 
-// Lanes per column of a triangular solve over ncols columns: a power of two,
-// at most one wave, with all columns' groups fitting in the team.
-__device__ __forceinline__ int solve_group(int ncols) {
-  int g = 64;
-  while (g > 1 && g * ncols > NT) g >>= 1;
-  return g;
+// Lane OWNER of every group of GS lanes (8 or 16) to the whole group, by row
+// broadcasts in the vector unit (a shuffle goes through LDS).
+template <int K>
+__device__ __forceinline__ float bcast16(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x150 + K, 0xF, 0xF, true));
+}
+template <int K>
+__device__ __forceinline__ double bcast16(double v) {
+  return row_bcast<K>(v);
+}
+template <int OWNER, int GS, class T>
+__device__ __forceinline__ T group_bcast(T v) {
+  static_assert(GS == 8 || GS == 16, "group of half a row or a row");
+  if constexpr (GS == 16) {
+    return bcast16<OWNER>(v);
+  } else {
+    const T a = bcast16<OWNER>(v), b = bcast16<OWNER + 8>(v);
+    return (threadIdx.x & 8) ? b : a;
+  }
 }
 
-// X <- L^{-1} X over ncols columns of X (entry (i, j) at X[i*rs + j*cs]); L lower
-// (LDS, stride LM).  Forward substitution by columns of L: each column of X has
-// a group of lanes, lane r owning the rows i = r mod group; x_i is formed by its
-// owner, broadcast across the group by a shuffle, and every lane updates its
-// rows below i.  Returns false on a non-positive pivot.
+// Triangular solves over ncols columns of X (entry (i, j) at X[i*rs + j*cs]); L
+// lower (LDS, stride LM).  Substitution by columns of L: each column of X has
+// a group of NT / D lanes that holds it in registers, lane r owning the rows
+// r + m NT / D; x_i is formed by its owner, broadcast across the group, and
+// every lane updates its remaining rows.  Bound by that chain (a division and
+// a broadcast a row); with X updated in LDS a row took 350 cycles.
+// UP = false: X <- L^{-1} X (forward); UP = true: X <- L^{-T} X (backward).
+// Returns false on a non-positive pivot.
+template <class T, int D, bool UP>
+__device__ __forceinline__ bool solve_t(T* X, int rs, int cs, const T* L, int ncols, int d) {
+  constexpr int LM = Dm<D>::LM, GS = NT / D, RP = D / GS;
+  const int tid = threadIdx.x, j = tid / GS, r = tid % GS;
+  const bool on = j < ncols;
+  T x[RP];
+#pragma unroll
+  for (int m = 0; m < RP; ++m) {
+    const int k = r + GS * m;
+    x[m] = (on && k < d) ? X[k * rs + j * cs] : T(0);
+  }
+  bool ok = true;
+  auto row = [&](auto ic) {
+    constexpr int i = UP ? D - 1 - decltype(ic)::value : decltype(ic)::value;
+    constexpr int mi = i / GS, owner = i % GS;
+    if (i < d) {
+      const T p = L[i * LM + i];
+      ok = ok && (p > T(0));
+      const T q = x[mi] / p;
+      x[mi] = (r == owner) ? q : x[mi];
+      const T xi = group_bcast<owner, GS>(q);
+#pragma unroll
+      for (int m = UP ? 0 : mi; m < (UP ? mi + 1 : RP); ++m) {
+        const int k = r + GS * m;
+        const T n = fma(-(UP ? L[i * LM + k] : L[k * LM + i]), xi, x[m]);
+        x[m] = (m != mi || (UP ? r < owner : r > owner)) ? n : x[m];
+      }
+    }
+  };
+  static_for<0, D>(row);
+  if (on) {
+#pragma unroll
+    for (int m = 0; m < RP; ++m) {
+      const int k = r + GS * m;
+      if (k < d) X[k * rs + j * cs] = x[m];
+    }
+  }
+  return __syncthreads_and(ok);
+}
 template <class T, int D>
 __device__ __forceinline__ bool solve_l(T* X, int rs, int cs, const T* L, int ncols, int d) {
-  constexpr int LM = Dm<D>::LM;
-  const int gs = solve_group(ncols), tid = threadIdx.x, j = tid / gs, r = tid % gs;
-  bool ok = true;
-  if (j < ncols) {
-    for (int i = 0; i < d; ++i) {
-      T xi = T(0);
-      if (r == i % gs) {
-        const T p = L[i * LM + i];
-        ok = ok && (p > T(0));
-        xi = X[i * rs + j * cs] / p;
-        X[i * rs + j * cs] = xi;
-      }
-      xi = __shfl(xi, i % gs, gs);
-      for (int k = i + 1 + ((r - i - 1) % gs + gs) % gs; k < d; k += gs)
-        X[k * rs + j * cs] = fma(-L[k * LM + i], xi, X[k * rs + j * cs]);
-    }
-  }
-  __syncthreads();
-  return __syncthreads_and(ok);
+  return solve_t<T, D, false>(X, rs, cs, L, ncols, d);
 }
-
-// X <- L^{-T} X over ncols columns (backward substitution with the upper L^T),
-// laid out as solve_l.
 template <class T, int D>
 __device__ __forceinline__ bool solve_lt(T* X, int rs, int cs, const T* L, int ncols, int d) {
-  constexpr int LM = Dm<D>::LM;
-  const int gs = solve_group(ncols), tid = threadIdx.x, j = tid / gs, r = tid % gs;
-  bool ok = true;
-  if (j < ncols) {
-    for (int i = d - 1; i >= 0; --i) {
-      T xi = T(0);
-      if (r == i % gs) {
-        const T p = L[i * LM + i];
-        ok = ok && (p > T(0));
-        xi = X[i * rs + j * cs] / p;
-        X[i * rs + j * cs] = xi;
-      }
-      xi = __shfl(xi, i % gs, gs);
-      for (int k = r; k < i; k += gs) X[k * rs + j * cs] = fma(-L[i * LM + k], xi, X[k * rs + j * cs]);
-    }
-  }
-  __syncthreads();
-  return __syncthreads_and(ok);
+  return solve_t<T, D, true>(X, rs, cs, L, ncols, d);
 }
 
 // Rows of X (D x D in LDS): X <- X L^{-T} and X <- X L^{-1}.
@@ -264,61 +301,109 @@ __device__ __forceinline__ double dot(const T* x, const T* y, int d, double* red
 // reflections by one product and a Cholesky with two barriers per column.
 // The factorisation is for a positive semi-definite matrix: a pivot <= 0 (an
 // exactly singular direction, e.g. a zero block, or its rounding) gives a zero
-// column.  Each thread keeps its 4 x 4 share of the Gram matrix in registers
-// until every thread has read M, then writes it over M.
+// column.
+//
+// The Gram matrix is formed by lower 16 x 16 tiles on the four waves' f64
+// matrix cores; the factorisation goes by panels of 16 columns: one wave holds
+// the panel with a row per lane and eliminates column by column (a lane read
+// per multiplier, no barrier), then all waves update the trailing tiles by
+// matrix instructions.  A matrix instruction accumulates its four products as
+// a chain of fused multiply-adds over ascending k (measured on gfx950), so every
+// element sees the operations of the unblocked right-looking elimination in
+// the same order.  Bound by the panels' chain pivot - square root -
+// reciprocal - update (about 300 cycles a column); with the trailing matrix
+// updated in LDS by all threads, two barriers a column, a filter step at
+// d = 30 took 147 us.
 // ---------------------------------------------------------------------------
 template <int D>
 __device__ __forceinline__ void tria(double* W, int r, int c, double* dv) {
-  constexpr int LW = Dm<D>::LW, R = 2 * D, NB = R / 16;
-  const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
-  // Gram matrix: thread (ti, tj) accumulates rows ti + 16 u and columns
-  // tj + 16 v (consecutive threads read consecutive rows: no bank conflicts)
-  double gv[NB][NB];
+  constexpr int LW = Dm<D>::LW, R = 2 * D, MT = R / 16;
+  constexpr int PW = (MT * (MT + 1) / 2 + NT / 64 - 1) / (NT / 64);  // tiles a wave
+  static_assert(R <= 64, "a panel has a row per lane");
+  const int tid = threadIdx.x, l = tid & 63, lg = l >> 4, lc = l & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nt = (r + 15) / 16, ks = (c + 3) / 4;
+  // lower tile q of a triangle of tiles: (I, J), J <= I
+  auto tile = [](int q, int& I, int& J) {
+    I = 0;
+    while ((I + 1) * (I + 2) / 2 <= q) ++I;
+    J = q - I * (I + 1) / 2;
+  };
+  dbl4 g[PW];
 #pragma unroll
-  for (int u = 0; u < NB; ++u)
-#pragma unroll
-    for (int v = 0; v < NB; ++v) gv[u][v] = 0.0;
-#pragma unroll 2
-  for (int k = 0; k < c; ++k) {
-    double a[NB], b[NB];
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      a[u] = (ti + 16 * u < r) ? W[(ti + 16 * u) * LW + k] : 0.0;
-      b[u] = (tj + 16 * u < r) ? W[(tj + 16 * u) * LW + k] : 0.0;
+  for (int u = 0; u < PW; ++u) {
+    int I, J;
+    tile(w + (NT / 64) * u, I, J);
+    g[u] = dbl4{0.0, 0.0, 0.0, 0.0};
+    if (I < nt) {
+      const bool ia = 16 * I + lc < r, jb = 16 * J + lc < r;
+      const double *pa = W + (16 * I + lc) * LW + lg, *pb = W + (16 * J + lc) * LW + lg;
+#pragma unroll 4
+      for (int k = 0; k < ks; ++k) {
+        const bool in = 4 * k + lg < c;
+        const double a = (ia && in) ? pa[4 * k] : 0.0, b = (jb && in) ? pb[4 * k] : 0.0;
+        g[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, g[u], 0, 0, 0);
+      }
     }
-#pragma unroll
-    for (int u = 0; u < NB; ++u)
-#pragma unroll
-      for (int v = 0; v < NB; ++v) gv[u][v] = fma(a[u], b[v], gv[u][v]);
   }
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < NB; ++u)
+  for (int u = 0; u < PW; ++u) {
+    int I, J;
+    tile(w + (NT / 64) * u, I, J);
+    if (I < nt) {
 #pragma unroll
-    for (int v = 0; v < NB; ++v) {
-      const int i = ti + 16 * u, j = tj + 16 * v;
-      if (i < r && j < r) W[i * LW + j] = (j <= i) ? gv[u][v] : 0.0;
+      for (int q = 0; q < 4; ++q) {
+        const int i = 16 * I + 4 * q + lg, j = 16 * J + lc;
+        if (i < r && j < r) W[i * LW + j] = (j <= i) ? g[u][q] : 0.0;
+        const int iu = 16 * J + 4 * q + lg, ju = 16 * I + lc;
+        if (I != J && iu < r && ju < r) W[iu * LW + ju] = 0.0;
+      }
     }
+  }
   __syncthreads();
-  // right-looking Cholesky; thread (ti, tj) updates rows ti + 16 a and
-  // columns tj + 16 b of the trailing block
-  for (int k = 0; k < r; ++k) {
-    const double p = W[k * LW + k];
-    const double dk = (p > 0.0) ? sqrt(p) : 0.0;
-    const double inv = (dk > 0.0) ? 1.0 / dk : 0.0;
-    for (int i = k + 1 + tid; i < r; i += NT) W[i * LW + k] *= inv;
-    __syncthreads();
-    if (tid == 0) W[k * LW + k] = dk;
+  for (int kb = 0; kb < nt; ++kb) {
+    const int c0 = 16 * kb;
+    if (w == 0) {
+      double p[16];
 #pragma unroll
-    for (int a = 0; a < R / 16; ++a) {
-      const int i = k + 1 + ti + 16 * a;
-      if (i < r) {
-        const double lik = W[i * LW + k];
+      for (int j = 0; j < 16; ++j)
+        p[j] = (l < r && c0 + j < r && l >= c0 + j) ? W[l * LW + c0 + j] : 0.0;
 #pragma unroll
-        for (int b = 0; b < R / 16; ++b) {
-          const int j = k + 1 + tj + 16 * b;
-          if (j <= i) W[i * LW + j] = fma(-lik, W[j * LW + k], W[i * LW + j]);
+      for (int k = 0; k < 16; ++k) {
+        if (c0 + k < r) {
+          const double pv = lane_bcast(p[k], c0 + k);
+          const double dk = (pv > 0.0) ? sqrt(pv) : 0.0;
+          const double inv = (dk > 0.0) ? 1.0 / dk : 0.0;
+          const double lk = (l == c0 + k) ? dk : p[k] * inv;
+          p[k] = lk;
+#pragma unroll
+          for (int j = k + 1; j < 16; ++j) p[j] = fma(-lk, lane_bcast(lk, c0 + j), p[j]);
         }
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (l < r && c0 + j < r && l >= c0 + j) W[l * LW + c0 + j] = p[j];
+    }
+    __syncthreads();
+    const int m = nt - 1 - kb;  // trailing tile rows
+    for (int q = w; q < m * (m + 1) / 2; q += NT / 64) {
+      int I, J;
+      tile(q, I, J);
+      I += kb + 1;
+      J += kb + 1;
+      const double *pa = W + (16 * I + lc) * LW + c0 + lg, *pb = W + (16 * J + lc) * LW + c0 + lg;
+      double* pc = W + (16 * I + lg) * LW + 16 * J + lc;
+      dbl4 t;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = pc[4 * e * LW];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        t = __builtin_amdgcn_mfma_f64_16x16x4f64(-pa[4 * k], pb[4 * k], t, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = 16 * I + 4 * e + lg, j = 16 * J + lc;
+        if (i < r && j <= i) pc[4 * e * LW] = t[e];
       }
     }
     __syncthreads();
@@ -330,18 +415,19 @@ __device__ __forceinline__ void tria(double* W, int r, int c, double* dv) {
 template <class T, int D, bool TR>
 __device__ __forceinline__ void to_w(double* W, int roff, int coff, const T* M, int d) {
   constexpr int LW = Dm<D>::LW, LM = Dm<D>::LM;
-  for (int e = threadIdx.x; e < d * d; e += NT) {
-    const int i = e / d, j = e % d;
-    W[(roff + i) * LW + coff + j] = (double)(TR ? M[j * LM + i] : M[i * LM + j]);
+#pragma unroll
+  for (int e = threadIdx.x; e < D * D; e += NT) {
+    const int i = e / D, j = e % D;
+    if (i < d && j < d) W[(roff + i) * LW + coff + j] = (double)(TR ? M[j * LM + i] : M[i * LM + j]);
   }
 }
 
 template <int D>
 __device__ __forceinline__ void w_fill(double* W, int roff, int coff, int d, double diag) {
   constexpr int LW = Dm<D>::LW;
-  for (int e = threadIdx.x; e < d * d; e += NT) {
-    const int i = e / d, j = e % d;
-    W[(roff + i) * LW + coff + j] = (i == j) ? diag : 0.0;
+  for (int e = threadIdx.x; e < D * D; e += NT) {
+    const int i = e / D, j = e % D;
+    if (i < d && j < d) W[(roff + i) * LW + coff + j] = (i == j) ? diag : 0.0;
   }
 }
 
@@ -363,9 +449,9 @@ template <class T, int D>
 __device__ __forceinline__ bool sqrt_update(double* W, double* dv, const T* Up, const double* Om_t, int d, T* P11,
                             T* P21, T* Uo, T* vs, const T* vmp, const double* om_t, double* red,
                             double* lpred) {
-  for (int e = threadIdx.x; e < d * d; e += NT) {
-    const int i = e / d, j = e % d;
-    W[i * Dm<D>::LW + j] = (i == j) ? sqrt(Om_t[i]) : 0.0;
+  for (int e = threadIdx.x; e < D * D; e += NT) {
+    const int i = e / D, j = e % D;
+    if (i < d && j < d) W[i * Dm<D>::LW + j] = (i == j) ? sqrt(Om_t[i]) : 0.0;
   }
   to_w<T, D, false>(W, 0, d, Up, d);
   w_fill<D>(W, d, 0, d, 0.0);
@@ -415,9 +501,9 @@ __device__ __forceinline__ bool chol_lds(double* A, int d) {
     __syncthreads();
     for (int i = k + 1 + threadIdx.x; i < d; i += NT) A[i * LM + k] /= A[k * LM + k];
     __syncthreads();
-    for (int e = threadIdx.x; e < d * d; e += NT) {
-      const int i = e / d, j = e % d;
-      if (j > k && i >= j) A[i * LM + j] -= A[i * LM + k] * A[j * LM + k];
+    for (int e = threadIdx.x; e < D * D; e += NT) {
+      const int i = e / D, j = e % D;
+      if (i < d && j > k && i >= j) A[i * LM + j] -= A[i * LM + k] * A[j * LM + k];
     }
     __syncthreads();
   }
@@ -431,21 +517,19 @@ __global__ void k_sq_init(int* status) {
 template <class T, int D>
 __global__ void __launch_bounds__(NT) k_sq_prep(SqArgs<T> P) {
   __shared__ double A[Dm<D>::MAT];
-  const int d = P.d;
-  for (int which = 0; which < 2; ++which) {
-    ld_mat<double, D>(A, which ? P.P0 : P.Q, d, d);
-    const bool ok = chol_lds<D>(A, d);
-    if (!ok && threadIdx.x == 0) flag(P.status);
-    T* out = which ? P.L0 : P.LQ;
+  const int d = P.d, which = blockIdx.x;  // a workgroup per factor
+  if (which == 0)
     for (int e = threadIdx.x; e < D * D; e += NT) {
       const int i = e / D, j = e % D;
-      out[e] = (i < d && j <= i) ? (T)A[i * Dm<D>::LM + j] : T(0);
+      P.Fs[e] = (i < d && j < d) ? (T)P.F[i * d + j] : T(0);
     }
-    __syncthreads();
-  }
+  ld_mat<double, D>(A, which ? P.P0 : P.Q, d, d);
+  const bool ok = chol_lds<D>(A, d);
+  if (!ok && threadIdx.x == 0) flag(P.status);
+  T* out = which ? P.L0 : P.LQ;
   for (int e = threadIdx.x; e < D * D; e += NT) {
     const int i = e / D, j = e % D;
-    P.Fs[e] = (i < d && j < d) ? (T)P.F[i * d + j] : T(0);
+    out[e] = (i < d && j <= i) ? (T)A[i * Dm<D>::LM + j] : T(0);
   }
 }
 
@@ -823,12 +907,26 @@ __global__ void __launch_bounds__(NT) k_sq_pscan(SqArgs<T> P) {
   const int d = P.d, tid = threadIdx.x;
   if (tid < D) x[tid] = T(0);
   __syncthreads();
-  for (int k = P.nb - 1; k >= 0; --k) {
+  // the next block's aggregate is fetched while this one's is applied
+  constexpr int PER = D * D / NT;
+  T pe[PER], pu = T(0);
+  auto fetch = [&](int k) {
     const T* a = P.agg + (int64_t)k * (D * D + D);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) pe[u] = a[tid + u * NT];
+    if (tid < D) pu = a[D * D + tid];
+  };
+  fetch(P.nb - 1);
+  for (int k = P.nb - 1; k >= 0; --k) {
     if (tid < D) P.xin[(int64_t)k * D + tid] = x[tid];
-    ld_mat<T, D>(Ea, a, D, D);
-    if (tid < D) ua[tid] = a[D * D + tid];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + u * NT;
+      Ea[(e / D) * Dm<D>::LM + e % D] = pe[u];
+    }
+    if (tid < D) ua[tid] = pu;
     __syncthreads();
+    if (k > 0) fetch(k - 1);
     mv<T, D, false>(y, Ea, x, d, ua);
     if (tid < D) x[tid] = y[tid];
     __syncthreads();
@@ -961,7 +1059,7 @@ akf_status run(const akf_model* m, const SqLayout& L, const double* om, const do
   P.status = atp<int>(ws, L.status);
   akf_status s;
   k_sq_init<<<dim3(1), dim3(64), 0, st>>>(P.status);
-  k_sq_prep<T, D><<<dim3(1), dim3(NT), 0, st>>>(P);
+  k_sq_prep<T, D><<<dim3(2), dim3(NT), 0, st>>>(P);
   P.el_out = atp<T>(ws, L.el[0]);
   P.lc_out = atp<double>(ws, L.lc[0]);
   k_sq_fold<T, D><<<dim3(L.nb), dim3(NT), Carve<T, D>::bytes(FOLD_M, FOLD_V), st>>>(P);
