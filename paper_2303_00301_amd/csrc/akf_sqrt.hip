@@ -232,21 +232,28 @@ __device__ __forceinline__ bool solve_t(T* X, int rs, int cs, const T* L, int nc
   auto row = [&](auto ic) {
     constexpr int i = UP ? D - 1 - decltype(ic)::value : decltype(ic)::value;
     constexpr int mi = i / GS, owner = i % GS;
-    if (i < d) {
-      const T p = L[i * LM + i];
-      ok = ok && (p > T(0));
-      const T q = x[mi] / p;
-      x[mi] = (r == owner) ? q : x[mi];
-      const T xi = group_bcast<owner, GS>(q);
+    // padded rows (zero in X and L) divide by one
+    const T pd = L[i * LM + i], p = i < d ? pd : T(1);
+    ok = ok && (p > T(0));
+    const T q = x[mi] / p;
+    x[mi] = (r == owner) ? q : x[mi];
+    const T xi = group_bcast<owner, GS>(q);
 #pragma unroll
-      for (int m = UP ? 0 : mi; m < (UP ? mi + 1 : RP); ++m) {
-        const int k = r + GS * m;
-        const T n = fma(-(UP ? L[i * LM + k] : L[k * LM + i]), xi, x[m]);
-        x[m] = (m != mi || (UP ? r < owner : r > owner)) ? n : x[m];
-      }
+    for (int m = UP ? 0 : mi; m < (UP ? mi + 1 : RP); ++m) {
+      const int k = r + GS * m;
+      const T n = fma(-(UP ? L[i * LM + k] : L[k * LM + i]), xi, x[m]);
+      x[m] = (m != mi || (UP ? r < owner : r > owner)) ? n : x[m];
     }
   };
-  static_for<0, D>(row);
+  // eight rows to a branch, so that their loads of L are issued together
+  auto rows8 = [&](auto gc) {
+    constexpr int g = decltype(gc)::value;
+    if (8 * (UP ? D / 8 - 1 - g : g) < d) {
+      auto one = [&](auto ic) { row(std::integral_constant<int, 8 * g + decltype(ic)::value>{}); };
+      static_for<0, 8>(one);
+    }
+  };
+  static_for<0, D / 8>(rows8);
   if (on) {
 #pragma unroll
     for (int m = 0; m < RP; ++m) {
@@ -290,10 +297,33 @@ __device__ __forceinline__ double dot(const T* x, const T* y, int d, double* red
   return team_sum(v, red);
 }
 
+// d = sqrt(p) and r = 1 / d, correctly rounded (zero for p <= 0), for finite p:
+// scaled by a power of four into [1/4, 1), Goldschmidt's iteration from the
+// hardware estimates with Markstein's final corrections.  Half the length of
+// the library's square root followed by its division, and no branch, so that
+// the steps around it can be scheduled into its chain.
+__device__ __forceinline__ void sqrt_and_rcp(double p, double& d, double& r) {
+  const int e = __builtin_amdgcn_frexp_exp(p) & ~1;
+  const double q = ldexp(p, -e);
+  double y = __builtin_amdgcn_rsq(q);
+  double s = q * y, h = 0.5 * y;
+  const double c = fma(-h, s, 0.5);
+  s = fma(s, c, s);
+  h = fma(h, c, h);
+  s = fma(fma(-s, s, q), h, s);
+  s = fma(fma(-s, s, q), h, s);
+  y = __builtin_amdgcn_rcp(s);
+  y = fma(fma(-s, y, 1.0), y, y);
+  y = fma(fma(-s, y, 1.0), y, y);
+  y = fma(fma(-s, y, 1.0), y, y);
+  d = (p > 0.0) ? ldexp(s, e >> 1) : 0.0;
+  r = (p > 0.0) ? ldexp(y, -(e >> 1)) : 0.0;
+}
+
 // ---------------------------------------------------------------------------
 // tria: in-place triangularisation of the r x c block M (c >= r) at the top
-// left of W (double, row stride LW).  On return W[0:r][0:r] is the lower-
-// triangular L with non-negative diagonal and L L^T = M M^T.  L is computed in
+// left of W (double, row stride LW).  On return the lower triangle of W[0:r][0:r]
+// is L with non-negative diagonal and L L^T = M M^T (above it W is unspecified).  L is computed in
 // double as the Cholesky factor of the Gram matrix M M^T, itself formed in
 // double: for matrices held in FP32 this is as accurate as a Householder
 // reduction (the squared condition number of M, at most ~1e8 on these models,
@@ -311,79 +341,104 @@ __device__ __forceinline__ double dot(const T* x, const T* y, int d, double* red
 // a chain of fused multiply-adds over ascending k (measured on gfx950), so every
 // element sees the operations of the unblocked right-looking elimination in
 // the same order.  Bound by the panels' chain pivot - square root -
-// reciprocal - update (about 300 cycles a column); with the trailing matrix
-// updated in LDS by all threads, two barriers a column, a filter step at
-// d = 30 took 147 us.
+// reciprocal - update (about 400 cycles a column): 60 x 60 in 40k cycles.  With
+// the trailing matrix updated in LDS by all threads, two barriers a column, a
+// filter and sample at d = 30, T = 250 took 2.07 ms, now 0.81.
 // ---------------------------------------------------------------------------
 template <int D>
 __device__ __forceinline__ void tria(double* W, int r, int c, double* dv) {
   constexpr int LW = Dm<D>::LW, R = 2 * D, MT = R / 16;
-  constexpr int PW = (MT * (MT + 1) / 2 + NT / 64 - 1) / (NT / 64);  // tiles a wave
-  static_assert(R <= 64, "a panel has a row per lane");
+  static_assert(MT <= NT / 64 && R <= 64, "a tile row per wave, a row per lane");
   const int tid = threadIdx.x, l = tid & 63, lg = l >> 4, lc = l & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nt = (r + 15) / 16, ks = (c + 3) / 4;
+  const int nt = (r + 15) / 16;
   // lower tile q of a triangle of tiles: (I, J), J <= I
   auto tile = [](int q, int& I, int& J) {
     I = 0;
     while ((I + 1) * (I + 2) / 2 <= q) ++I;
     J = q - I * (I + 1) / 2;
   };
-  dbl4 g[PW];
+  // wave w forms tile row w; its own rows' fragments serve every tile of the
+  // row.  Rows beyond r are not masked (they reach no valid entry), columns
+  // beyond c are.
+  dbl4 g[MT];
+  auto gram_row = [&](auto rc) {
+    constexpr int I = decltype(rc)::value;
+    if constexpr (I < MT) {
+      const double* pw = W + lc * LW + lg;
 #pragma unroll
-  for (int u = 0; u < PW; ++u) {
-    int I, J;
-    tile(w + (NT / 64) * u, I, J);
-    g[u] = dbl4{0.0, 0.0, 0.0, 0.0};
-    if (I < nt) {
-      const bool ia = 16 * I + lc < r, jb = 16 * J + lc < r;
-      const double *pa = W + (16 * I + lc) * LW + lg, *pb = W + (16 * J + lc) * LW + lg;
-#pragma unroll 4
-      for (int k = 0; k < ks; ++k) {
-        const bool in = 4 * k + lg < c;
-        const double a = (ia && in) ? pa[4 * k] : 0.0, b = (jb && in) ? pb[4 * k] : 0.0;
-        g[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, g[u], 0, 0, 0);
-      }
+      for (int J = 0; J <= I; ++J) g[J] = dbl4{0.0, 0.0, 0.0, 0.0};
+      auto group = [&](int k0, bool tail) {
+        double x[I + 1][4];
+#pragma unroll
+        for (int J = 0; J <= I; ++J)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) x[J][k] = pw[16 * J * LW + 4 * (k0 + k)];
+        if (tail) {
+#pragma unroll
+          for (int J = 0; J <= I; ++J)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[J][k] = (4 * (k0 + k) + lg < c) ? x[J][k] : 0.0;
+        }
+#pragma unroll
+        for (int J = 0; J <= I; ++J)
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            g[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[I][k], x[J][k], g[J], 0, 0, 0);
+      };
+      int k0 = 0;
+      for (; 4 * k0 + 16 <= c; k0 += 4) group(k0, false);
+      if (4 * k0 < c) group(k0, true);
     }
-  }
+  };
+  auto gram_store = [&](auto rc) {
+    constexpr int I = decltype(rc)::value;
+    if constexpr (I < MT) {
+#pragma unroll
+      for (int J = 0; J <= I; ++J)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = 16 * I + 4 * q + lg, j = 16 * J + lc;
+          if (I != J || j <= i) W[i * LW + j] = g[J][q];
+        }
+    }
+  };
+  auto of_wave = [&](auto& f) {
+    if (w >= nt) return;
+    if (w == 0) f(std::integral_constant<int, 0>{});
+    if (w == 1) f(std::integral_constant<int, 1>{});
+    if (w == 2) f(std::integral_constant<int, 2>{});
+    if (w == 3) f(std::integral_constant<int, 3>{});
+  };
+  of_wave(gram_row);
   __syncthreads();
-#pragma unroll
-  for (int u = 0; u < PW; ++u) {
-    int I, J;
-    tile(w + (NT / 64) * u, I, J);
-    if (I < nt) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = 16 * I + 4 * q + lg, j = 16 * J + lc;
-        if (i < r && j < r) W[i * LW + j] = (j <= i) ? g[u][q] : 0.0;
-        const int iu = 16 * J + 4 * q + lg, ju = 16 * I + lc;
-        if (I != J && iu < r && ju < r) W[iu * LW + ju] = 0.0;
-      }
-    }
-  }
+  of_wave(gram_store);
   __syncthreads();
   for (int kb = 0; kb < nt; ++kb) {
     const int c0 = 16 * kb;
     if (w == 0) {
       double p[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
-        p[j] = (l < r && c0 + j < r && l >= c0 + j) ? W[l * LW + c0 + j] : 0.0;
+      for (int j = 0; j < 16; ++j) p[j] = W[min(l, R - 1) * LW + c0 + j];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) p[j] = (l < r && c0 + j < r && l >= c0 + j) ? p[j] : 0.0;
+      // the next pivot's column is updated first, by lane reads; the others take
+      // their multipliers from LDS while its square root and reciprocal are formed
+      double pv = lane_bcast(p[0], c0);
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
-        if (c0 + k < r) {
-          const double pv = lane_bcast(p[k], c0 + k);
-          const double dk = (pv > 0.0) ? sqrt(pv) : 0.0;
-          const double inv = (dk > 0.0) ? 1.0 / dk : 0.0;
-          const double lk = (l == c0 + k) ? dk : p[k] * inv;
-          p[k] = lk;
-#pragma unroll
-          for (int j = k + 1; j < 16; ++j) p[j] = fma(-lk, lane_bcast(lk, c0 + j), p[j]);
+        double dk, inv;
+        sqrt_and_rcp(pv, dk, inv);
+        const double lk = (l == c0 + k) ? dk : p[k] * inv;
+        if (l < r && c0 + k < r && l >= c0 + k) W[l * LW + c0 + k] = lk;
+        if (k < 15) {
+          p[k + 1] = fma(-lk, lane_bcast(lk, c0 + k + 1), p[k + 1]);
+          pv = lane_bcast(p[k + 1], c0 + k + 1);
         }
-      }
+        wave_lds_fence();
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
-        if (l < r && c0 + j < r && l >= c0 + j) W[l * LW + c0 + j] = p[j];
+        for (int j = k + 2; j < 16; ++j) p[j] = fma(-lk, W[(c0 + j) * LW + c0 + k], p[j]);
+      }
     }
     __syncthreads();
     const int m = nt - 1 - kb;  // trailing tile rows
@@ -431,13 +486,14 @@ __device__ __forceinline__ void w_fill(double* W, int roff, int coff, int d, dou
   }
 }
 
-// LDS matrix (zero padded) <- W block (roff, coff), d x d
-template <class T, int D>
+// LDS matrix (zero padded) <- W block (roff, coff), d x d; LOWER: a diagonal
+// block of tria's result, whose strict upper part holds no values
+template <class T, int D, bool LOWER = true>
 __device__ __forceinline__ void from_w(T* M, const double* W, int roff, int coff, int d) {
   constexpr int LW = Dm<D>::LW, LM = Dm<D>::LM;
   for (int e = threadIdx.x; e < D * D; e += NT) {
     const int i = e / D, j = e % D;
-    M[i * LM + j] = (i < d && j < d) ? (T)W[(roff + i) * LW + coff + j] : T(0);
+    M[i * LM + j] = (i < d && j < (LOWER ? i + 1 : d)) ? (T)W[(roff + i) * LW + coff + j] : T(0);
   }
 }
 
@@ -459,7 +515,7 @@ __device__ __forceinline__ bool sqrt_update(double* W, double* dv, const T* Up, 
   __syncthreads();
   tria<D>(W, 2 * d, 2 * d, dv);
   from_w<T, D>(P11, W, 0, 0, d);
-  from_w<T, D>(P21, W, d, 0, d);
+  from_w<T, D, false>(P21, W, d, 0, d);
   from_w<T, D>(Uo, W, d, d, d);
   if (threadIdx.x < D) vs[threadIdx.x] = (threadIdx.x < d) ? (T)(om_t[threadIdx.x]) - vmp[threadIdx.x] : T(0);
   __syncthreads();
@@ -703,7 +759,7 @@ __global__ void __launch_bounds__(NT) k_sq_hs(SqArgs<T> P) {
   __syncthreads();
   tria<D>(c.W, 2 * d, 2 * d, c.dv);
   from_w<T, D>(X11, c.W, 0, 0, d);
-  from_w<T, D>(X21, c.W, d, 0, d);
+  from_w<T, D, false>(X21, c.W, d, 0, d);
   from_w<T, D>(X22, c.W, d, d, d);
   __syncthreads();
   cp_mat<T, D>(G, Ui);
@@ -854,7 +910,7 @@ __global__ void __launch_bounds__(NT) k_sq_sbuild(SqArgs<T> P) {
   __syncthreads();
   tria<D>(c.W, 2 * d, 2 * d, c.dv);
   from_w<T, D>(sP11, c.W, 0, 0, d);
-  from_w<T, D>(sP21, c.W, d, 0, d);
+  from_w<T, D, false>(sP21, c.W, d, 0, d);
   from_w<T, D>(sX, c.W, d, d, d);
   __syncthreads();
   const bool ok = rows_times_linv<T, D>(sP21, sP11, d, d);  // E = P21 P11^{-1}
