@@ -11,8 +11,8 @@
 // of FT * S steps (S <= FS_MAX per thread), each chunk a blocked
 // reduce-then-scan:
 //   filter  : fold   -- each thread folds its S elements (A, b, C, eta, J);
-//             scan   -- inclusive scan over the FT thread elements (wave
-//                       shuffles, then the wave totals through LDS), with the
+//             scan   -- inclusive scan over the FT thread elements (lane
+//                       shifts in the vector unit, then the wave totals through LDS), with the
 //                       previous chunk's last filtering moments in front;
 //             final  -- each thread re-runs its steps from its prefix with the
 //                       sequential Kalman update: m^f_t, P^f_t and the
@@ -21,13 +21,14 @@
 //             E_t = G_t, U_t = m^f_t - G_t m^p_{t+1} + sqrt(Sigma_t) xi_t; fold
 //             per thread, suffix scan of the affine maps, then each thread
 //             walks its steps backward from the state entering from the right.
-// Filtering moments are kept coordinate-major ([dx][N]) in the workspace
-// between the filter and the sampler.
+// Filtering moments are kept between the filter and the sampler in registers
+// (one chunk) or coordinate-major ([dx][N]) in the workspace.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
 #include "akf_internal.h"
+#include "akf_wave.hpp"
 
 namespace akf {
 
@@ -48,7 +49,7 @@ struct SE {
 // Element combination (App. A, eq. parallel filter operator) for scalars;
 // `i` precedes `j` in time.
 __device__ __forceinline__ SE se_combine(const SE& i, const SE& j) {
-  const double iw = 1.0 / (1.0 + i.C * j.J);
+  const double iw = recip(1.0 + i.C * j.J);
   SE o;
   o.A = j.A * i.A * iw;
   o.b = j.A * (i.b + i.C * j.eta) * iw + j.b;
@@ -58,15 +59,46 @@ __device__ __forceinline__ SE se_combine(const SE& i, const SE& j) {
   return o;
 }
 
-__device__ __forceinline__ SE se_shfl_up(const SE& e, int s) {
-  SE o;
-  o.A = __shfl_up(e.A, s);
-  o.b = __shfl_up(e.b, s);
-  o.C = __shfl_up(e.C, s);
-  o.eta = __shfl_up(e.eta, s);
-  o.J = __shfl_up(e.J, s);
-  return o;
+// v moved across lanes by DPP control CTRL in the rows of ROWS; lanes without a
+// source get `none`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double v, double none) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v), n = __builtin_bit_cast(uint64_t, none);
+  const uint32_t lo = __builtin_amdgcn_update_dpp((int)(uint32_t)n, (int)(uint32_t)u, CTRL, ROWS, 0xF,
+                                                  false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(n >> 32), (int)(uint32_t)(u >> 32),
+                                                  CTRL, ROWS, 0xF, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ SE se_from(const SE& e) {  // the identity where there is no source
+  return SE{dpp<CTRL, ROWS>(e.A, 1.0), dpp<CTRL, ROWS>(e.b, 0.0), dpp<CTRL, ROWS>(e.C, 0.0),
+            dpp<CTRL, ROWS>(e.eta, 0.0), dpp<CTRL, ROWS>(e.J, 0.0)};
+}
+// DPP controls of a wave scan: shifts by 1, 2, 4, 8 within a row of 16, the last
+// lane of a row to the next row, lane 31 to the upper half, and a shift by one
+// lane over the whole wave
+constexpr int SHR1 = 0x111, SHR2 = 0x112, SHR4 = 0x114, SHR8 = 0x118, BC15 = 0x142, BC31 = 0x143,
+              WSHR1 = 0x138;
+
+// Inclusive scan over the wave, lower lanes first in `op(earlier lanes, lane)`.
+// In the vector unit: with LDS shuffles (83 cycles each, ten a step) the two
+// scans were a third of the kernel.
+template <typename E, typename From, typename Op>
+__device__ __forceinline__ E wave_scan(E e, From from, Op op) {
+  e = op(from.template get<SHR1, 0xF>(e), e);
+  e = op(from.template get<SHR2, 0xF>(e), e);
+  e = op(from.template get<SHR4, 0xF>(e), e);
+  e = op(from.template get<SHR8, 0xF>(e), e);
+  e = op(from.template get<BC15, 0xA>(e), e);
+  return op(from.template get<BC31, 0xC>(e), e);
+}
+struct FromSE {
+  template <int CTRL, int ROWS>
+  __device__ __forceinline__ SE get(const SE& e) const {
+    return se_from<CTRL, ROWS>(e);
+  }
+};
 
 // Affine map x -> E x + U (one backward sampling step or a composition).
 struct AM {
@@ -78,8 +110,32 @@ __device__ __forceinline__ AM am_compose(const AM& a, const AM& b) {
   return AM{a.E * b.E, a.E * b.U + a.U};
 }
 
+// from the lane below in time order (the identity where there is none)
+template <int CTRL>
+__device__ __forceinline__ AM am_from(const AM& e) {
+  return AM{dpp<CTRL, 0xF>(e.E, 1.0), dpp<CTRL, 0xF>(e.U, 0.0)};
+}
+constexpr int SHL1 = 0x101, SHL2 = 0x102, SHL4 = 0x104, SHL8 = 0x108, WSHL1 = 0x130;
+
+// e_lane o e_lane+1 o ... o e_63: within each row of 16 by lane shifts, then the
+// totals of the rows above (their first lanes) by lane reads.
+__device__ __forceinline__ AM am_suffix(AM e) {
+  e = am_compose(e, am_from<SHL1>(e));
+  e = am_compose(e, am_from<SHL2>(e));
+  e = am_compose(e, am_from<SHL4>(e));
+  e = am_compose(e, am_from<SHL8>(e));
+  const AM r1{lane_bcast(e.E, 16), lane_bcast(e.U, 16)};
+  const AM r2{lane_bcast(e.E, 32), lane_bcast(e.U, 32)};
+  const AM r3{lane_bcast(e.E, 48), lane_bcast(e.U, 48)};
+  const AM r23 = am_compose(r2, r3), r123 = am_compose(r1, r23);
+  const int row = (threadIdx.x & 63) >> 4;
+  AM up = row == 0 ? r123 : (row == 1 ? r23 : r3);
+  if (row == 3) up = AM{1.0, 0.0};
+  return am_compose(e, up);
+}
+
 __device__ __forceinline__ double block_reduce(double v, double* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = wave_total(v);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -102,6 +158,10 @@ __global__ void __launch_bounds__(FT) k_fact_scan(KModel M, FactArgs P) {
   if (S > FS_MAX) S = FS_MAX;
   const int chunk = FT * S;
   const int n_chunks = (N + chunk - 1) / chunk;
+  // with one chunk a thread keeps its steps' filtering moments for the sampler,
+  // and reads their normals with the pseudo-observations
+  const bool one = n_chunks == 1;
+  double mreg[FS_MAX], Preg[FS_MAX], xireg[FS_MAX];
   double* mfc = P.mf ? P.mf + (int64_t)i * N : nullptr;
   double* Pfc = P.Pf ? P.Pf + (int64_t)i * N : nullptr;
   bool bad = false;
@@ -119,6 +179,7 @@ __global__ void __launch_bounds__(FT) k_fact_scan(KModel M, FactArgs P) {
       if (s < cnt) {
         om[s] = P.om[(int64_t)(t0 + s) * d + i];
         Om[s] = P.Om[(int64_t)(t0 + s) * d + i];
+        if (one && P.xi_x) xireg[s] = P.xi_x[(int64_t)(t0 + s) * d + i];
       }
     }
     // fold: this thread's elements, in time order
@@ -128,10 +189,10 @@ __global__ void __launch_bounds__(FT) k_fact_scan(KModel M, FactArgs P) {
       if (s < cnt) {
         SE e;
         if (t0 + s == 0) {
-          const double iS = 1.0 / (P0 + Om[s]);
+          const double iS = recip(P0 + Om[s]);
           e = SE{0.0, m0 + P0 * (om[s] - m0) * iS, P0 * Om[s] * iS, 0.0, 0.0};
         } else {
-          const double iS = 1.0 / (Q + Om[s]);
+          const double iS = recip(Q + Om[s]);
           e = SE{F * Om[s] * iS, (Om[s] * bb + Q * om[s]) * iS, Q * Om[s] * iS,
                  F * (om[s] - bb) * iS, F * F * iS};
         }
@@ -139,15 +200,9 @@ __global__ void __launch_bounds__(FT) k_fact_scan(KModel M, FactArgs P) {
       }
     }
     // inclusive scan over the wave
-    SE inc = acc;
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
-      const SE o = se_shfl_up(inc, s);
-      if (lane >= s) inc = se_combine(o, inc);
-    }
+    const SE inc = wave_scan(acc, FromSE{}, se_combine);
     if (lane == 63) swave[w] = inc;
-    SE ex = se_shfl_up(inc, 1);
-    if (lane == 0) ex = SE{1.0, 0.0, 0.0, 0.0, 0.0};
+    const SE ex = se_from<WSHR1>(inc);
     __syncthreads();
     // prefix entering this thread: previous chunk's moments, earlier waves, earlier lanes
     SE pre = (c == 0) ? SE{1.0, 0.0, 0.0, 0.0, 0.0} : SE{0.0, cm, cP, 0.0, 0.0};
@@ -165,7 +220,7 @@ __global__ void __launch_bounds__(FT) k_fact_scan(KModel M, FactArgs P) {
         const double Pp = (t == 0) ? P0 : F * F * Pv + Q;
         const double Sv = Pp + Om[s];
         if (!(Sv > 0.0) || !(Pp >= 0.0)) bad = true;
-        const double iS = 1.0 / Sv;
+        const double iS = recip(Sv);
         const double r = om[s] - mp;
         int e2;
         sprod = frexp(sprod * Sv, &e2);
@@ -173,7 +228,10 @@ __global__ void __launch_bounds__(FT) k_fact_scan(KModel M, FactArgs P) {
         ell += -0.5 * (LOG2PI_F + r * r * iS);
         m = mp + Pp * iS * r;
         Pv = Pp * Om[s] * iS;
-        if (mfc) {
+        if (one) {
+          mreg[s] = m;
+          Preg[s] = Pv;
+        } else if (mfc) {
           mfc[t] = m;
           Pfc[t] = Pv;
         }
@@ -209,14 +267,14 @@ __global__ void __launch_bounds__(FT) k_fact_scan(KModel M, FactArgs P) {
     for (int s = 0; s < FS_MAX; ++s) {
       if (s < cnt) {
         const int t = t0 + s;
-        const double mf = mfc[t], Pf = Pfc[t];
-        const double xi = P.xi_x[(int64_t)t * d + i];
+        const double mf = one ? mreg[s] : mfc[t], Pf = one ? Preg[s] : Pfc[t];
+        const double xi = one ? xireg[s] : P.xi_x[(int64_t)t * d + i];
         if (t == N - 1) {
           if (!(Pf > 0.0)) sbad = true;
           st[s] = AM{0.0, mf + sqrt(Pf) * xi};
         } else {
           const double Pp1 = F * F * Pf + Q;
-          const double iP = 1.0 / Pp1;
+          const double iP = recip(Pp1);
           const double G = Pf * F * iP;
           const double Sig = Pf * Q * iP;
           if (!(Pp1 > 0.0) || !(Sig > 0.0)) sbad = true;
@@ -230,15 +288,9 @@ __global__ void __launch_bounds__(FT) k_fact_scan(KModel M, FactArgs P) {
     for (int s = FS_MAX - 1; s >= 0; --s)
       if (s < cnt) agg = am_compose(st[s], agg);
     // inclusive suffix scan over the wave
-    AM inc = agg;
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
-      const AM o{__shfl_down(inc.E, s), __shfl_down(inc.U, s)};
-      if (lane + s < 64) inc = am_compose(inc, o);
-    }
+    const AM inc = am_suffix(agg);
     if (lane == 0) samp[w] = inc;
-    AM ex{__shfl_down(inc.E, 1), __shfl_down(inc.U, 1)};
-    if (lane == 63) ex = AM{1.0, 0.0};
+    const AM ex = am_from<WSHL1>(inc);
     __syncthreads();
     // state entering this wave from the right, then this thread
     double xw = xr;

@@ -11,7 +11,7 @@ enum { DYN_LINEAR = 0, DYN_LORENZ63 = 1, DYN_LORENZ96 = 2 };
 enum { ST_FWD_NOT_PD = 1, ST_REV_NOT_PD = 2, ST_NONFINITE = 4 };
 
 // time steps (one wave each) per workgroup of the multivariate-t linearisation
-constexpr int kMvtWaves = 4;
+constexpr int kMvtSteps = 4;
 // time steps per workgroup of the Gaussian-emission linearisation (four waves,
 // each taking every fourth of them)
 constexpr int kGaussStepsPerBlock = 16;

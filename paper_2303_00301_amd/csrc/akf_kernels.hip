@@ -148,11 +148,28 @@ __device__ __forceinline__ void slr_override(const KModel& M, double x, EmitOut&
   o.lam = -h * h * o.cnt / den;
 }
 
+// The linearisation kernels are bound by load latency (a round trip to memory
+// is 1 - 2 us against a few hundred instructions), so what a point needs is read
+// at the start of the kernel, with the observations, not where it is used.
+struct FwdIn {
+  double x, xi;
+};
+__device__ __forceinline__ FwdIn fwd_in(const StepArgs& A, int64_t gid, bool in) {
+  return in ? FwdIn{A.x[gid], A.xi_u[gid]} : FwdIn{0.0, 0.0};
+}
+struct RevIn {
+  double xs, x, u, om, Om;
+};
+__device__ __forceinline__ RevIn rev_in(const StepArgs& A, int64_t gid, bool in) {
+  return in ? RevIn{A.xs[gid], A.x[gid], A.u[gid], A.om[gid], A.Om[gid]}
+            : RevIn{0.0, 0.0, 0.0, 0.0, 1.0};
+}
+
 // Per-(t, i) tail of the forward linearisation: draws u and writes the
 // diagonal omega/Omega from v_i and Lambda_ii (0 under order 1).
-__device__ __forceinline__ void lin_fwd_point(const StepArgs& A, int64_t gid, double x, double v,
-                                              double lam) {
-  const double u = x + sqrt(0.5 * A.delta) * A.xi_u[gid];
+__device__ __forceinline__ void lin_fwd_point(const StepArgs& A, int64_t gid, const FwdIn& I,
+                                              double v, double lam) {
+  const double u = I.x + sqrt(0.5 * A.delta) * I.xi;
   A.u[gid] = u;
   const double prec = 2.0 / A.delta - lam;
   if (!(prec > 0.0) || !isfinite(v) || !isfinite(prec)) {
@@ -162,7 +179,7 @@ __device__ __forceinline__ void lin_fwd_point(const StepArgs& A, int64_t gid, do
   } else {
     const double Om = 1.0 / prec;
     A.Om[gid] = Om;
-    A.om[gid] = Om * (2.0 / A.delta * u + v - lam * x);
+    A.om[gid] = Om * (2.0 / A.delta * u + v - lam * I.x);
   }
 }
 
@@ -174,10 +191,10 @@ __device__ __forceinline__ void lin_fwd_diag_body(const KModel& M, const StepArg
   double lh = 0.0;
   if (gid < n) {
     const int t = (int)(gid / M.d), i = (int)(gid % M.d);
-    const double x = A.x[gid];
-    EmitOut e = emit_diag(M, A.y + (int64_t)t * M.dy, x, i);
-    if (A.order == 3) slr_override(M, x, e);
-    lin_fwd_point(A, gid, x, e.v, (A.order == 1) ? 0.0 : e.lam);
+    const FwdIn in = fwd_in(A, gid, true);
+    EmitOut e = emit_diag(M, A.y + (int64_t)t * M.dy, in.x, i);
+    if (A.order == 3) slr_override(M, in.x, e);
+    lin_fwd_point(A, gid, in, e.v, (A.order == 1) ? 0.0 : e.lam);
     lh = e.lh;
   }
   // block partial of log h(x)
@@ -196,9 +213,9 @@ __global__ void __launch_bounds__(256) k_lin_fwd_diag(KModel M, StepArgs A) {
 // omega*/Omega* and returns the MH terms
 //   [(u-x)^2 - (u-x*)^2]/delta
 //   + log N(omega*_i; x_i, Omega*_i) - log N(omega_i; x*_i, Omega_i)
-__device__ __forceinline__ double lin_rev_point(const StepArgs& A, int64_t gid, double xs,
+__device__ __forceinline__ double lin_rev_point(const StepArgs& A, int64_t gid, const RevIn& I,
                                                 double v, double lam) {
-  const double x = A.x[gid], u = A.u[gid];
+  const double x = I.x, u = I.u, xs = I.xs;
   const double prec = 2.0 / A.delta - lam;
   double om2 = 0.0, Om2 = 1.0;
   if (!(prec > 0.0) || !isfinite(v) || !isfinite(prec)) {
@@ -209,7 +226,7 @@ __device__ __forceinline__ double lin_rev_point(const StepArgs& A, int64_t gid, 
   }
   A.om2[gid] = om2;
   A.Om2[gid] = Om2;
-  const double om = A.om[gid], Om = A.Om[gid];
+  const double om = I.om, Om = I.Om;
   const double a = u - x, c = u - xs;
   const double rq = om2 - x, fq = om - xs;
   return (a * a - c * c) / A.delta +
@@ -224,10 +241,10 @@ __device__ __forceinline__ void lin_rev_diag_body(const KModel& M, const StepArg
   double term = 0.0, lhs = 0.0;
   if (gid < n) {
     const int t = (int)(gid / M.d), i = (int)(gid % M.d);
-    const double xs = A.xs[gid];
-    EmitOut e = emit_diag(M, A.y + (int64_t)t * M.dy, xs, i);
-    if (A.order == 3) slr_override(M, xs, e);
-    term = lin_rev_point(A, gid, xs, e.v, (A.order == 1) ? 0.0 : e.lam);
+    const RevIn in = rev_in(A, gid, true);
+    EmitOut e = emit_diag(M, A.y + (int64_t)t * M.dy, in.xs, i);
+    if (A.order == 3) slr_override(M, in.xs, e);
+    term = lin_rev_point(A, gid, in, e.v, (A.order == 1) ? 0.0 : e.lam);
     lhs = e.lh;
   }
   __shared__ double red[8];
@@ -255,86 +272,123 @@ __global__ void __launch_bounds__(256) k_lin_rev_diag(KModel M, StepArgs A) {
 // r = y_t - x_t[site], q = r^T R r, log h = -(nu + p)/2 log(1 + q / nu) and
 // v_i = (nu + p)/(nu + q) sum_{k: site[k] = i} (R r)_k.  Its Hessian couples
 // every observed coordinate, so only first-order proposals (Lambda = 0) use it.
-// One wave per time step, MVT_WAVES waves per workgroup sharing R, which is
-// staged transposed in LDS so that lane k walks row k of R bank-conflict free.
+// A workgroup takes MVT_T time steps: R r for all of them is a matrix product on
+// the f64 matrix cores (wave w forms rows 16 w .. 16 w + 15, a column per time
+// step), so R is read once per MVT_T steps and straight into registers.  Each
+// coordinate's sites are found once per workgroup, as a first site per
+// coordinate and a next site per site.  Bound by its loads' latency; a wave per
+// time step with R staged in LDS and the site list swept per step took 11.2 us
+// at p = 64, T = 1024.
 // ---------------------------------------------------------------------------
-constexpr int MVT_WAVES = kMvtWaves;
+constexpr int MVT_T = kMvtSteps;
+static_assert(MVT_T <= 16, "a column of the matrix instruction per time step");
 
-__device__ __forceinline__ void lin_mvt_body(const KModel& M, const StepArgs& A, int rev,
-                                             int item) {
-  constexpr int LR = 65;  // odd row stride: the transposing store is conflict-free too
-  __shared__ double sRt[64 * LR];
-  __shared__ double sr[MVT_WAVES * 64];
-  __shared__ double sRr[MVT_WAVES * 64];
-  __shared__ int ssite[64];
-  __shared__ double red[2 * MVT_WAVES];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int p = M.dy, d = M.d;
-  team_move<64 * MVT_WAVES, 64 * 64>(
-      p * p, [&](int e) { return M.R[e]; },
-      [&](int e, double v) { sRt[(e % p) * LR + e / p] = v; });
-  if (tid < p) ssite[tid] = M.site[tid];
-  const int t = item * MVT_WAVES + w;
-  const bool active = t < M.N;
-  const int64_t base = (int64_t)t * d;
-  const double* xt = (rev ? A.xs : A.x) + base;
-  double r = 0.0;
-  if (active && lane < p) r = A.y[(int64_t)t * p + lane] - xt[M.site[lane]];
-  sr[w * 64 + lane] = r;
-  __syncthreads();
-  double Rr = 0.0;
-  if (active && lane < p) {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    int l = 0;
-    for (; l + 4 <= p; l += 4) {
+__global__ void __launch_bounds__(256) k_lin_mvt(KModel M, StepArgs A, int rev) {
+  constexpr int LR = 65;
+  constexpr int QT = (MVT_T + 3) / 4;  // time steps per wave
+  __shared__ double sr[16 * LR];   // r, a row per time step (rows >= MVT_T are zero)
+  __shared__ double sRr[16 * LR];  // the path's rows, then R r
+  __shared__ double sq[4][16];
+  __shared__ int first[64], nxt[64];
+  __shared__ double red[8];
+  const int tid = threadIdx.x, l = tid & 63, lg = l >> 4, lc = l & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int p = M.dy, d = M.d, t0 = blockIdx.x * MVT_T;
+  // every load of the kernel, issued together
+  double a[16], y[QT];
+  FwdIn fi[QT];
+  RevIn ri[QT];
+  const int site = l < p ? M.site[l] : -1;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] = fma(sRt[(l + u) * LR + lane], sr[w * 64 + l + u], acc[u]);
-    }
-    for (; l < p; ++l) acc[0] = fma(sRt[l * LR + lane], sr[w * 64 + l], acc[0]);
-    Rr = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  for (int q = 0; q < QT; ++q) {
+    const int u = w + 4 * q, t = t0 + u;
+    const bool on = u < MVT_T && t < M.N;
+    y[q] = (on && l < p) ? A.y[(int64_t)t * p + l] : 0.0;
+    if (rev)
+      ri[q] = rev_in(A, (int64_t)t * d + l, on && l < d);
+    else
+      fi[q] = fwd_in(A, (int64_t)t * d + l, on && l < d);
   }
-  double q = r * Rr;
-  for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
-  sRr[w * 64 + lane] = Rr;
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    const int i = 16 * w + lc, k = 4 * s + lg;
+    a[s] = (i < p && k < p) ? M.R[i * p + k] : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < QT; ++q) sRr[(w + 4 * q) * LR + l] = rev ? ri[q].xs : fi[q].x;
+  wave_lds_fence();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int u = w + 4 * q;
+    double r = 0.0;
+    if (q < QT && u < MVT_T && t0 + u < M.N && l < p) r = y[q < QT ? q : 0] - sRr[u * LR + site];
+    sr[u * LR + l] = r;
+  }
   __syncthreads();
-  const double a = M.nu + p;
+  if (w == 3) {
+    // the first site of each coordinate, and the next site of the same coordinate
+    // after each site (none unless a coordinate is observed twice)
+    first[l] = 64;
+    wave_lds_fence();
+    if (l < p) atomicMin(&first[site], l);
+    wave_lds_fence();
+    int nx = 64;
+    if (__ballot(l < p && first[l < p ? site : 0] != l)) {
+      for (int k = p - 1; k > 0; --k)
+        nx = (k > l && __builtin_amdgcn_readlane(site, k) == site) ? k : nx;
+    }
+    nxt[l] = nx;
+  }
+  dbl4 c = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+    c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], sr[lc * LR + 4 * s + lg], c, 0, 0, 0);
+  double q4 = 0.0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int k = 16 * w + 4 * e + lg;
+    sRr[lc * LR + k] = c[e];
+    q4 = fma(sr[lc * LR + k], c[e], q4);
+  }
+  q4 = sum_groups(q4);
+  if (lg == 0) sq[w][lc] = q4;
+  __syncthreads();
+  const double nup = M.nu + p;
   double lh = 0.0, term = 0.0;
-  if (active) {
-    lh = -0.5 * a * log1p(q / M.nu);
-    if (lane < d) {
-      double sv = 0.0;
-#pragma unroll 8
-      for (int k = 0; k < p; ++k) sv += (ssite[k] == lane) ? sRr[w * 64 + k] : 0.0;
-      const double v = a / (M.nu + q) * sv;
-      if (rev)
-        term = lin_rev_point(A, base + lane, xt[lane], v, 0.0);
-      else
-        lin_fwd_point(A, base + lane, xt[lane], v, 0.0);
+#pragma unroll
+  for (int q = 0; q < QT; ++q) {
+    const int u = w + 4 * q, t = t0 + u;
+    if (u < MVT_T && t < M.N) {
+      const double qt = (sq[0][u] + sq[1][u]) + (sq[2][u] + sq[3][u]);
+      if (l == 0) lh += -0.5 * nup * log1p(qt / M.nu);
+      if (l < d) {
+        double sv = 0.0;
+        for (int k = first[l]; k < 64; k = nxt[k]) sv += sRr[u * LR + k];
+        const double v = nup / (M.nu + qt) * sv;
+        const int64_t g = (int64_t)t * d + l;
+        if (rev)
+          term += lin_rev_point(A, g, ri[q], v, 0.0);
+        else
+          lin_fwd_point(A, g, fi[q], v, 0.0);
+      }
     }
   }
-  for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o);
-  if (lane == 0) {
+  term = wave_total(term);
+  if (l == 0) {
     red[w] = lh;
-    red[MVT_WAVES + w] = term;
+    red[4 + w] = term;
   }
   __syncthreads();
   if (tid == 0) {
-    double sl = 0.0, st = 0.0;
-    for (int k = 0; k < MVT_WAVES; ++k) {
-      sl += red[k];
-      st += red[MVT_WAVES + k];
-    }
+    const double sl = (red[0] + red[1]) + (red[2] + red[3]);
+    const double st = (red[4] + red[5]) + (red[6] + red[7]);
     if (rev) {
-      A.part_lh_xs[item] = sl;
-      A.part_terms[item] = st;
+      A.part_lh_xs[blockIdx.x] = sl;
+      A.part_terms[blockIdx.x] = st;
     } else {
-      A.part_lh_x[item] = sl;
+      A.part_lh_x[blockIdx.x] = sl;
     }
   }
-}
-
-__global__ void __launch_bounds__(64 * MVT_WAVES) k_lin_mvt(KModel M, StepArgs A, int rev) {
-  lin_mvt_body(M, A, rev, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1612,26 +1666,72 @@ __global__ void __launch_bounds__(256) k_mh_finalize(KModel M, StepArgs A, Final
 // same sums in the same order, hence the same decision; workgroup 0 writes the
 // outputs and clears the next step's status word; each workgroup writes its
 // slice of x_out = accept ? x* : x.
-__global__ void __launch_bounds__(256) k_mh_decide(KModel M, StepArgs A, FinalArgs F,
-                                                   const double* __restrict__ x,
-                                                   double* __restrict__ x_out, int64_t n,
-                                                   int64_t per_block) {
-  __shared__ double red[4];
+//
+// Its time is load latency: the sums' loads are all issued before the first
+// reduction, by kDecideThreads threads (six reductions one after the other by 256
+// threads took 5 to 14 us).
+constexpr int kDecideThreads = 1024;
+__global__ void __launch_bounds__(kDecideThreads) k_mh_decide(KModel M, StepArgs A, FinalArgs F,
+                                                              const double* x, double* x_out,
+                                                              int64_t n,
+                                                              int64_t per_block) {
+  constexpr int NS = 6, NWV = kDecideThreads / 64;
+  __shared__ double red[NS][NWV];
   __shared__ int sacc;
   const int n_ell = F.n_ell > 0 ? F.n_ell : M.N;
-  const double lzf = block_sum(A.ell, n_ell, red);
-  const double lzr = F.lz_rev ? *F.lz_rev : block_sum(A.ell2, n_ell, red);
-  const double terms = block_sum(A.part_terms, F.n_part_rev, red);
-  const double lhx = block_sum(A.part_lh_x, F.n_part_fwd, red);
-  const double lhs = block_sum(A.part_lh_xs, F.n_part_rev, red);
-  const double dyn = F.part_dyn ? block_sum(F.part_dyn, F.n_part_dyn, red) : 0.0;
+  const double* src[NS] = {A.ell, A.ell2, A.part_terms, A.part_lh_x, A.part_lh_xs, F.part_dyn};
+  const int cnt[NS] = {n_ell, F.lz_rev ? 0 : n_ell, F.n_part_rev, F.n_part_fwd, F.n_part_rev,
+                       F.part_dyn ? F.n_part_dyn : 0};
+  const int nmax = max(max(cnt[0], cnt[2]), max(cnt[3], cnt[5]));
+  // this thread's elements of the copy and the scalars of the decision
+  const int64_t i0 = (int64_t)blockIdx.x * per_block;
+  const int64_t i1 = i0 + per_block < n ? i0 + per_block : n;
+  constexpr int PC = 2;
+  double xo[PC], xn[PC];
+#pragma unroll
+  for (int u = 0; u < PC; ++u) {
+    const int64_t i = i0 + threadIdx.x + u * kDecideThreads;
+    xo[u] = i < i1 ? x[i] : 0.0;
+    xn[u] = i < i1 ? A.xs[i] : 0.0;
+  }
+  const int st0 = *A.status;
+  const double unif = F.unif[0], lz_rev = F.lz_rev ? *F.lz_rev : 0.0;
+  double s[NS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < nmax; i += 2 * kDecideThreads) {
+    double v[NS][2];
+#pragma unroll
+    for (int a = 0; a < NS; ++a)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int e = i + u * kDecideThreads;
+        v[a][u] = e < cnt[a] ? src[a][e] : 0.0;
+      }
+#pragma unroll
+    for (int a = 0; a < NS; ++a) s[a] += v[a][0] + v[a][1];
+  }
+#pragma unroll
+  for (int a = 0; a < NS; ++a) {
+    s[a] = wave_total(s[a]);
+    if ((threadIdx.x & 63) == 0) red[a][threadIdx.x >> 6] = s[a];
+  }
+  __syncthreads();
+  double tot[NS];
   if (threadIdx.x == 0) {
-    int st = *A.status;
+#pragma unroll
+    for (int a = 0; a < NS; ++a) {
+      tot[a] = 0.0;
+      for (int k = 0; k < NWV; ++k) tot[a] += red[a][k];
+    }
+  }
+  const double lzf = tot[0], lzr = F.lz_rev ? lz_rev : tot[1], terms = tot[2], lhx = tot[3],
+               lhs = tot[4], dyn = tot[5];
+  if (threadIdx.x == 0) {
+    int st = st0;
     if (st & ST_FWD_NOT_PD) st = ST_FWD_NOT_PD;
     double lr = terms + (lhs - lhx) + (lzf - lzr) + dyn;
     if (st == 0 && !isfinite(lr)) st |= ST_NONFINITE;
     if (st != 0) lr = -INFINITY;
-    const int acc = (st == 0) && (log(F.unif[0]) < lr);
+    const int acc = (st == 0) && (log(unif) < lr);
     sacc = acc;
     if (blockIdx.x == 0) {
       *A.accept_flag = acc;  // for callers that read the decision back
@@ -1645,9 +1745,11 @@ __global__ void __launch_bounds__(256) k_mh_decide(KModel M, StepArgs A, FinalAr
   }
   __syncthreads();
   const bool acc = sacc != 0;
-  const int64_t i0 = (int64_t)blockIdx.x * per_block;
-  const int64_t i1 = i0 + per_block < n ? i0 + per_block : n;
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) x_out[i] = acc ? A.xs[i] : x[i];
+#pragma unroll
+  for (int u = 0; u < PC; ++u) {
+    const int64_t i = i0 + threadIdx.x + u * kDecideThreads;
+    if (i < i1) x_out[i] = acc ? xn[u] : xo[u];
+  }
 }
 
 __device__ __forceinline__ void mh_select_body(int64_t n, const double* __restrict__ x,
@@ -1968,9 +2070,9 @@ hipError_t launch_lin(const KModel& M, StepArgs A, int rev, int* n_part, hipStre
     if (!rev) hipLaunchKernelGGL(k_gauss_prep, dim3(1), dim3(256), 0, st, M, A);
     hipLaunchKernelGGL(k_lin_gauss, dim3(nblk), dim3(64 * GL_WAVES), 0, st, M, A, rev);
   } else if (M.emit == EMIT_MVT) {
-    const int nblk = (M.N + MVT_WAVES - 1) / MVT_WAVES;
+    const int nblk = (M.N + MVT_T - 1) / MVT_T;
     *n_part = nblk;
-    hipLaunchKernelGGL(k_lin_mvt, dim3(nblk), dim3(64 * MVT_WAVES), 0, st, M, A, rev);
+    hipLaunchKernelGGL(k_lin_mvt, dim3(nblk), dim3(256), 0, st, M, A, rev);
   } else {
     const int64_t n = (int64_t)M.N * M.d;
     const int nblk = (int)((n + 255) / 256);
@@ -2011,10 +2113,11 @@ hipError_t launch_step_init(int* status, double* root_flag, double* root_xin, in
 hipError_t launch_finalize(const KModel& M, StepArgs A, FinalArgs F, const double* x,
                            double* x_out, hipStream_t st) {
   const int64_t n = (int64_t)M.N * M.d;
-  const int64_t per_block = 2048;
+  const int64_t per_block = 2 * kDecideThreads;  // a workgroup copies two elements a thread
   const unsigned grid = (unsigned)((n + per_block - 1) / per_block);
   timing_mark(FAM_MH, 1, st);
-  hipLaunchKernelGGL(k_mh_decide, dim3(grid), dim3(256), 0, st, M, A, F, x, x_out, n, per_block);
+  hipLaunchKernelGGL(k_mh_decide, dim3(grid), dim3(kDecideThreads), 0, st, M, A, F, x, x_out, n,
+                     per_block);
   timing_mark(FAM_MH, 0, st);
   return hipGetLastError();
 }

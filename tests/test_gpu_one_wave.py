@@ -111,3 +111,25 @@ def test_path_scan_levels(S, N, d, block):
     x, st = S.rts_sample(M, T(ref["mf"]), T(ref["Pf"]), T(xi), block=block)
     assert rc == 0 and int(st[0]) == 0
     assert _rel(N_(x), x_ref) < TOL
+
+
+@pytest.mark.parametrize("N,d,dy", [(1, 5, 3), (17, 64, 64), (9, 20, 33), (40, 64, 17)])
+@pytest.mark.parametrize("repeat", [False, True])
+def test_multivariate_t_sites(S, N, d, dy, repeat):
+    """Multivariate-t linearisation with time steps, sites and coordinates short of
+    a tile, and with coordinates observed by several sites (dy > d needs them)."""
+    rng = np.random.default_rng(N + d + dy)
+    site = rng.integers(0, d, size=dy) if repeat or dy > d else rng.permutation(d)[:dy]
+    A = rng.standard_normal((dy, dy))
+    m0, P0, F, b, Q = _model(rng, d)
+    kw = dict(m0=m0, P0=P0, F=F, Q=Q, b=b, R=A @ A.T / dy + np.eye(dy),
+              site=site.astype(np.int32), nu=2.0)
+    y, x = rng.standard_normal((N, dy)), rng.standard_normal((N, d))
+    xi = rng.standard_normal((2, N, d))
+    r = oracle.mh_step(oracle.Model(emit=W.EMIT_MVT, **kw), y, x, 0.05, 1, xi[0], xi[1], 1e-9)
+    M = S.DeviceModel.from_arrays(N, emit=S.EMIT_MVT, **kw)
+    out = S.mh_step(M, T(y), T(x), 0.05, 1, T(xi), T([1e-9]))
+    assert int(out["status"][0]) == r["status"] and int(out["accepted"][0]) == r["accepted"]
+    for k in ("logZ_fwd", "logZ_rev", "log_ratio"):
+        assert abs(float(out[k][0]) - r[k]) < 1e-9 * N * d * max(1.0, abs(r["logZ_fwd"]))
+    assert _rel(N_(out["x_out"]), r["x_out"]) < TOL
