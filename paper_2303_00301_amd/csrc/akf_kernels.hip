@@ -699,6 +699,8 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
   const int blk = item, tid = threadIdx.x, d = M.d;
   const int s0 = blk * P.B, s1 = min(M.N, s0 + P.B);
   constexpr bool first = FIRST;
+  // fully unrolled products where the register budget allows them
+  constexpr int UF = OBS == OBS_DIAG ? D / 4 : U;
   // lc: log of the normaliser, the sum over the block's steps of the
   // x_prev-independent part of log N(omega_t; T x_prev + mu, S),
   // -(d log 2 pi + log det S + w' S^{-1} w) / 2; log det S and this thread's
@@ -728,19 +730,25 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
         bt = P.bt + (int64_t)t * d;
       }
       rm_load<D>(Pp, M.Q, d, d);  // issued early: its latency overlaps F C
-      rm_stage<D>(Cc, B1);
-      team_sync();
-      gemm<D, false, false, false, U>(R1, sF, B1);  // F C
-      team_sync();
-      rm_stage<D>(R1, B1);
-      team_sync();
-      gemm<D, false, true, true, U>(Pp, B1, sF);  // Q + (F C) F'
-      matvec<D, false>(vmu, sF, vb);
-      if (tid < d && bt) vmu[tid] += bt[tid];
-      if (!first) {
-        rm_stage<D>(A, B1);
+      if (!first && t == s0) {  // A = I, C = 0, b = 0
         team_sync();
-        gemm<D, false, false, false, U>(T, sF, B1);  // T = F A
+        rm_unstage<D>(T, sF);
+        if (tid < D) vmu[tid] = (tid < d && bt) ? bt[tid] : 0.0;
+      } else {
+        rm_stage<D>(Cc, B1);
+        team_sync();
+        gemm<D, false, false, false, UF>(R1, sF, B1);  // F C
+        team_sync();
+        rm_stage<D>(R1, B1);
+        team_sync();
+        gemm<D, false, true, true, UF>(Pp, B1, sF);  // Q + (F C) F'
+        matvec<D, false>(vmu, sF, vb);
+        if (tid < d && bt) vmu[tid] += bt[tid];
+        if (!first) {
+          rm_stage<D>(A, B1);
+          team_sync();
+          gemm<D, false, false, false, UF>(T, sF, B1);  // T = F A
+        }
       }
       team_sync();
     }
@@ -768,7 +776,7 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
       if (first || !PAIR2)
         gemm<D, false, false, false, U>(Cc, B2, B1);  // S^{-1} Pp
       else
-        gemm2<D, false, false, U>(Cc, R1, B2, B1, B3);  // S^{-1} Pp, S^{-1} T
+        gemm2<D, false, false, UF>(Cc, R1, B2, B1, B3);  // S^{-1} Pp, S^{-1} T
       AKF_RM_FOR(D, q, r, i, j) Cc.t[q][r] *= vom[i];
       matvec<D, false>(vs, B2, vw);  // S^{-1} w (ends synchronised: B1 is free)
       ld_sum += logdet;
@@ -777,8 +785,7 @@ __device__ __forceinline__ void filter_fold_impl(const KModel& M, const FilterAr
         if (!PAIR2) gemm<D, false, false, false, U>(R1, B2, B3);  // S^{-1} T
         rm_stage<D>(R1, B1);
         team_sync();
-        // fully unrolled where the register budget still allows it
-        gemm<D, true, false, true, D / 4>(J, B3, B1);  // J += T' S^{-1} T
+        gemm<D, true, false, true, UF>(J, B3, B1);  // J += T' S^{-1} T
         AKF_RM_FOR(D, q, r, i, j) A.t[q][r] = vom[i] * R1.t[q][r];
         matvec<D, true>(veta, B3, vs, veta);  // eta += T' S^{-1} w
       }
@@ -861,9 +868,8 @@ __device__ __forceinline__ void filter_fold_body(const KModel& M, const FilterAr
 
 template <int D, int OBS>
 __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_fold(KModel M, FilterArgs P) {
-  // k-steps per unrolled GEMM iteration: the most that fits the register budget
-  // without spills (the D = 64 diagonal fold holds 512 registers per lane)
-  constexpr int U = OBS == OBS_DIAG ? 8 : 4;
+  // k-steps per unrolled GEMM iteration (the dense fold's budget takes four)
+  constexpr int U = OBS == OBS_DIAG ? D / 4 : 4;
   if (gate_shut(M.gate)) return;
   filter_fold_body<D, OBS, U>(M, P, blockIdx.x);
 }

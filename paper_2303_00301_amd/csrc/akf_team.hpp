@@ -66,6 +66,47 @@ __device__ __forceinline__ void team_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// s plus the value of the lane 16 (32) on in the wave's exchange order: a half
+// exchange in the vector unit (a lane permute through LDS takes 83 cycles)
+__device__ __forceinline__ double half_sum(uint32_t lo0, uint32_t hi0, uint32_t lo1, uint32_t hi1) {
+  return __builtin_bit_cast(double, ((uint64_t)hi0 << 32) | lo0) +
+         __builtin_bit_cast(double, ((uint64_t)hi1 << 32) | lo1);
+}
+__device__ __forceinline__ double sum_x16(double s) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, s);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return half_sum(a[0], b[0], a[1], b[1]);
+}
+__device__ __forceinline__ double sum_x32(double s) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, s);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return half_sum(a[0], b[0], a[1], b[1]);
+}
+// sum over the lanes with the same l%16
+__device__ __forceinline__ double sum_groups(double s) { return sum_x32(sum_x16(s)); }
+
+// lane (l + N) of the row of 16
+template <int N>
+__device__ __forceinline__ double row_ror(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + N, 0xF, 0xF, true);
+  const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + N, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// sum over the wave, to every lane
+__device__ __forceinline__ double wave_total(double v) {
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  v += row_ror<1>(v);
+  return sum_groups(v);
+}
+
 template <int D>
 struct RM {
   dbl4 t[Cfg<D>::TPW];
@@ -582,14 +623,21 @@ __device__ bool spd_inv(RM<D>& A, int d, double* scr, double* logdet) {
       };
       double pv[4], dummy[4];
       brow(kb, pv);
+      // the row's other tiles are fetched while the pivot tile is swept
+      double bR[C::TS][4], bC[C::TS][4];
+#pragma unroll
+      for (int t = 0; t < C::TS; ++t) {
+        brow(R0 + t, bR[t]);
+        brow(C0 + t, bC[t]);
+      }
       tile_sweep16<false, D == 16>(pv, d - 16 * kb, dummy, ld, ok);  // pv = P^{-1}
       const dbl4 z = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int ti = 0; ti < C::TS; ++ti) {
         const int TI = R0 + ti;
         const double sI = (TI < kb) ? -1.0 : 1.0;
-        double bi[4], xa[4];
-        brow(TI, bi);
+        const double(&bi)[4] = bR[ti];
+        double xa[4];
         if (TI != kb) {
           const dbl4 xr = mfma16(pv, bi, z);  // P^{-1} A_KI
 #pragma unroll
@@ -602,16 +650,12 @@ __device__ bool spd_inv(RM<D>& A, int d, double* scr, double* logdet) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) A.t[q][r] = pv[r];
           } else if (TI == kb) {
-            double bj[4];
-            brow(TJ, bj);
-            A.t[q] = mfma16(pv, bj, z);  // P^{-1} A_KJ
+            A.t[q] = mfma16(pv, bC[tj], z);  // P^{-1} A_KJ
           } else if (TJ == kb) {
             const dbl4 y = mfma16(bi, pv, z);  // A_KI' P^{-1}
             A.t[q] = -sI * y;
           } else {
-            double bj[4];
-            brow(TJ, bj);
-            A.t[q] = mfma16(xa, bj, A.t[q]);  // A_IJ - s_I (P^{-1} A_KI)' A_KJ
+            A.t[q] = mfma16(xa, bC[tj], A.t[q]);  // A_IJ - s_I (P^{-1} A_KI)' A_KJ
           }
         }
       }
@@ -718,7 +762,7 @@ __device__ bool chol_reg(RM<D>& A, int d, double* scr, double* logdet) {
 // y[i] = add[i] + sum_j op(A)[i][j] x[j] for i < D (LDS matrix; add may be
 // null, may alias y, and may live in global memory; x must not alias y).
 // Every wave takes D / NW rows and splits each row over 64 / (D / NW) lanes,
-// reduced by lane shuffles, so the dependent chain is 16 (D >= 32) or 4 FMAs
+// reduced by half exchanges, so the dependent chain is 8 (D >= 32) or 2 FMAs
 // long.  Team-wide; ends with a barrier, after which y is visible to all.
 template <int D, bool TA>
 __device__ __forceinline__ void matvec(double* y, const double* sA, const double* x,
@@ -729,14 +773,13 @@ __device__ __forceinline__ void matvec(double* y, const double* sA, const double
   constexpr int JL = D / P;     // columns per lane
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int i = w * R + (l % R), j0 = (l / R) * JL;
-  double s = 0.0;
+  double a[2] = {0.0, 0.0};
 #pragma unroll
   for (int jj = 0; jj < JL; ++jj) {
     const int j = j0 + jj;
-    s = fma(TA ? sA[j * C::LD + i] : sA[i * C::LD + j], x[j], s);
+    a[jj & 1] = fma(TA ? sA[j * C::LD + i] : sA[i * C::LD + j], x[j], a[jj & 1]);
   }
-#pragma unroll
-  for (int m = R; m < 64; m <<= 1) s += __shfl_xor(s, m);
+  const double s = R == 16 ? sum_groups(a[0] + a[1]) : sum_x32(a[0] + a[1]);
   if (l < R) y[i] = (add ? add[i] : 0.0) + s;
   team_sync();
 }
@@ -745,8 +788,7 @@ __device__ __forceinline__ void matvec(double* y, const double* sA, const double
 template <int D>
 __device__ __forceinline__ double team_sum(double v, double* sRed) {
   using C = Cfg<D>;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = wave_total(v);
   const int tid = threadIdx.x;
   if ((tid & 63) == 0) sRed[tid >> 6] = v;
   team_sync();

@@ -139,47 +139,6 @@ __device__ __forceinline__ RV<D> rv(const double* s) {
   return o;
 }
 
-// s plus the value of the lane 16 (32) on in the wave's exchange order: a half
-// exchange in the vector unit (a lane permute through LDS takes 83 cycles)
-__device__ __forceinline__ double half_sum(uint32_t lo0, uint32_t hi0, uint32_t lo1, uint32_t hi1) {
-  return __builtin_bit_cast(double, ((uint64_t)hi0 << 32) | lo0) +
-         __builtin_bit_cast(double, ((uint64_t)hi1 << 32) | lo1);
-}
-__device__ __forceinline__ double sum_x16(double s) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, s);
-  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
-  const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-  return half_sum(a[0], b[0], a[1], b[1]);
-}
-__device__ __forceinline__ double sum_x32(double s) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, s);
-  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
-  const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  return half_sum(a[0], b[0], a[1], b[1]);
-}
-// sum over the lanes with the same l%16
-__device__ __forceinline__ double sum_groups(double s) { return sum_x32(sum_x16(s)); }
-
-// lane (l + N) of the row of 16
-template <int N>
-__device__ __forceinline__ double row_ror(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + N, 0xF, 0xF, true);
-  const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + N, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// sum over the wave, to every lane
-__device__ __forceinline__ double wave_total(double v) {
-  v += row_ror<8>(v);
-  v += row_ror<4>(v);
-  v += row_ror<2>(v);
-  v += row_ror<1>(v);
-  return sum_groups(v);
-}
-
 // lane l < D: (x' v)_l (plus add, a value of that lane); other lanes: unspecified
 template <int D, int KT = Cfg<D>::TS>
 __device__ __forceinline__ double mv(const RM<D>& x, const RV<D>& v) {
