@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_dnc_up(KModel M, DncArgs A, int 
   gemm<D, false, false, false, D / 4>(R, B3, B4);  // G T1
   rm_rsub<D>(R, L2);                        // V = L2 - G E1 L2
   rm_symmetrise<D>(R, B2);
-  ok = chol_reg<D>(R, d, scr, &ld) && ok;
+  ok = chol_reg<D>(R, d, scr) && ok;
   rm_store<D>(R, A.Vc + (int64_t)l * D * D, D, D);
   if (!ok && tid == 0) atomicOr(A.status, ST_FWD_NOT_PD);
 }
@@ -213,7 +213,7 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_dnc_root(KModel M, DncArgs A) {
   RM<D> R;
   double ld;
   rm_load<D>(R, A.Pf + (int64_t)T * A.ldm * A.ldm, A.ldm, d);
-  bool ok = chol_reg<D>(R, d, scr, &ld);
+  bool ok = chol_reg<D>(R, d, scr);
   rm_stage<D>(R, B1);
   if (tid < D) vt[tid] = (tid < d) ? A.xi[(int64_t)T * d + tid] : 0.0;
   team_sync();
@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_dnc_root(KModel M, DncArgs A) {
     const double* Lp = (leaf ? A.Llf : A.Lno) + (int64_t)(leaf ? 0 : T / 2) * D * D;
     const double* gp = (leaf ? A.glf : A.gno) + (int64_t)(leaf ? 0 : T / 2) * D;
     rm_load<D>(R, Lp, D, D);
-    ok = chol_reg<D>(R, d, scr, &ld) && ok;
+    ok = chol_reg<D>(R, d, scr) && ok;
     team_sync();
     load_pad<D>(B2, Ep);
     rm_stage<D>(R, B1);

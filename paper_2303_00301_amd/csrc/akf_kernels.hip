@@ -928,7 +928,7 @@ __device__ __forceinline__ void filter_combine(const KModel& M, const double* __
     rm_load<D>(Ji, ei + EL::J, D, D);
     rm_load<D>(Aj, ej + EL::A, D, D);
     rm_load<D>(Cj, ej + EL::C, D, D);
-    ok = chol_reg<D>(R1, d, S3, &ld) && ok;  // R1 = L
+    ok = chol_reg<D>(R1, d, S3) && ok;  // R1 = L
     rm_stage<D>(R1, S0);                        // S0 = L
     team_sync();
     gemm<D, false, false, false, U>(R2, S1, S0);  // J_j L
@@ -1088,7 +1088,7 @@ __device__ __forceinline__ void moment_combine(const KModel& M, const double* Pi
     if (tid < D) vm[tid] = min_[tid];
     rm_load<D>(Ae, el + EL::A, D, D);  // needed after the factorisations
     rm_load<D>(Ce, el + EL::C, D, D);
-    ok = chol_reg<D>(R1, d, S3, &ld) && ok;  // R1 = L
+    ok = chol_reg<D>(R1, d, S3) && ok;  // R1 = L
     rm_stage<D>(R1, S0);
     team_sync();
     gemm<D, false, false, false, U>(R2, S1, S0);  // J L
@@ -1364,7 +1364,7 @@ __device__ __forceinline__ void samp_build_impl(const KModel& M, const SampArgs&
   bool ok = true;
   double ld;
   if (t == M.N - 1) {
-    ok = chol_reg<D>(Pf, d, X, &ld);
+    ok = chol_reg<D>(Pf, d, X);
     if (S.Lc) rm_store_t<D>(Pf, S.Lc + (int64_t)t * D * D, D);
     rm_stage<D>(Pf, Y);
     team_sync();
@@ -1418,7 +1418,7 @@ __device__ __forceinline__ void samp_build_impl(const KModel& M, const SampArgs&
     matvec<D, false>(vg, X, vmp);
     if (tid < D) vg[tid] = vm[tid] - vg[tid];  // g = m^f - E m^p
     rm_symmetrise<D>(R2, Y);
-    ok = chol_reg<D>(R2, d, X, &ld) && ok;
+    ok = chol_reg<D>(R2, d, X) && ok;
     if (S.Lc) rm_store_t<D>(R2, S.Lc + (int64_t)t * D * D, D);
     rm_stage<D>(R2, Y);
     team_sync();

@@ -13,12 +13,10 @@
 //  * Runtime size d <= D: padded rows/columns are zero in every matrix
 //    (factors and inverses included).
 //
-// GEMMs run on the f64 matrix cores.  Inverses of SPD matrices (block
-// Gauss-Jordan) and Cholesky factors (blocked, right-looking) are computed in
-// registers: each 16 x 16 pivot tile is swept inside one wave (lane
-// broadcasts, no LDS), the pivot block row or column is staged through a
-// double-buffered LDS panel (one barrier per panel), and every other product
-// is an MFMA chain.
+// GEMMs run on the f64 matrix cores.  Inverses and Cholesky factors of SPD
+// matrices go by 2 x 2 blocks, two levels deep at D = 64: each 16 x 16 pivot
+// tile is swept inside one wave (lane broadcasts, no LDS), and every product is
+// an MFMA chain on tiles.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -39,7 +37,7 @@ struct Cfg {
   static constexpr int TPW = TS * TS;
   static constexpr int NB = D / 16;
   static constexpr int LD = D + 1;
-  static constexpr int MAT = D * LD;
+  static constexpr int MAT = D * LD;  // entries of an LDS matrix
 };
 
 __device__ __forceinline__ double lane_bcast(double v, int src) {
@@ -340,31 +338,6 @@ __device__ __forceinline__ void gemm2(RM<D>& c1, RM<D>& c2, const double* sA, co
   }
 }
 
-// element (ti, tj, r) of a register matrix with a runtime tile index ti or tj
-// (TS <= 2).  Both candidates are read as values before the select: a select
-// between two element lvalues would index the register array at run time and
-// push it to scratch memory.
-template <int D>
-__device__ __forceinline__ double rm_pick_row(const RM<D>& A, int ti, int tj, int r) {
-  if constexpr (Cfg<D>::TS == 1) {
-    return A.t[0][r];
-  } else {
-    const double a = static_cast<double>(A.t[tj][r]);
-    const double b = static_cast<double>(A.t[Cfg<D>::TS + tj][r]);
-    return ti ? b : a;
-  }
-}
-template <int D>
-__device__ __forceinline__ double rm_pick_col(const RM<D>& A, int ti, int tj, int r) {
-  if constexpr (Cfg<D>::TS == 1) {
-    return A.t[0][r];
-  } else {
-    const double a = static_cast<double>(A.t[ti * Cfg<D>::TS][r]);
-    const double b = static_cast<double>(A.t[ti * Cfg<D>::TS + 1][r]);
-    return tj ? b : a;
-  }
-}
-
 // 16 x 16 x 16 tile product on one wave: c + A B with the operands given as
 // per-k-step fragments: a[s] = A[l%16][4s + l/16], b[s] = B[4s + l/16][l%16].
 // In the accumulator layout, register s of a tile M is M[4s + l/16][l%16], so
@@ -566,196 +539,330 @@ __device__ void inv_refine(RM<D>& X, const RM<D>& A, int d, double* s1, double* 
   team_sync();
 }
 
-// LDS scratch (doubles) needed by spd_inv and chol_reg: the staged block row
-// or column, double-buffered across waves (none at D = 16: one tile).
+// transpose of a tile through 16 x 17 doubles of LDS
+__device__ __forceinline__ dbl4 tile_t(const dbl4& t, double* s) {
+  const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) s[lc * 17 + 4 * r + lg] = t[r];
+  wave_lds_fence();
+  dbl4 o;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) o[r] = s[(4 * r + lg) * 17 + lc];
+  wave_lds_fence();
+  return o;
+}
+
+// c + a' b of one tile
+__device__ __forceinline__ dbl4 tile_tn(const dbl4& a, const dbl4& b, dbl4 c) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
+  return c;
+}
+
+template <int D>
+__device__ __forceinline__ void rm_mask(RM<D>& a, int d) {
+  AKF_RM_FOR(D, q, r, i, j) if (i >= d || j >= d) a.t[q][r] = 0.0;
+}
+
+__device__ __forceinline__ dbl4 tile_of(const double p[4]) { return dbl4{p[0], p[1], p[2], p[3]}; }
+
+// In-place inverse of a symmetric positive definite matrix held by one wave
+// (zero outside the leading d x d block) by 2 x 2 blocks of tiles
+// [[a, b], [b', c]]: with P = a^{-1}, X = P b and S = c - b' X,
+//   inverse = [[P + X S^{-1} X', -X S^{-1}], [-S^{-1} X', S^{-1}]].
+// Reads the diagonal and upper tiles; the result's lower tile mirrors its
+// upper one.  KT = 1: d <= 16, the first tile alone (the others are not
+// touched).  Returns false on a non-positive pivot (the result is then
+// unspecified); the pivots go into ld.  scr: one padded tile of LDS (D = 32).
+template <int D, int KT = Cfg<D>::TS>
+__device__ __forceinline__ bool wave_inv(RM<D>& A, int d, double* scr, LogDet& ld) {
+  bool ok = true;
+  double p[4], dummy[4];
+  tile_regs(A.t[0], p);
+  tile_sweep16<false, KT == 1>(p, d, dummy, ld, ok);
+  if constexpr (KT == 1) {
+    A.t[0] = tile_of(p);
+    const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (4 * r + lg >= d || lc >= d) A.t[0][r] = 0.0;
+  } else {
+    const dbl4 z = {0.0, 0.0, 0.0, 0.0};
+    const dbl4 P = tile_of(p);
+    const dbl4 X = tile_tn(P, A.t[1], z);           // P b
+    const dbl4 Z = tile_t(X, scr);                  // X'
+    const dbl4 S = A.t[3] - tile_tn(A.t[1], X, z);  // c - b' X
+    tile_regs(S, p);
+    tile_sweep16<false, true>(p, d - 16, dummy, ld, ok);
+    const dbl4 Si = tile_of(p);
+    const dbl4 Wt = tile_tn(Si, Z, z);  // S^{-1} X'
+    A.t[0] = tile_tn(Z, Wt, P);         // P + X S^{-1} X'
+    A.t[2] = -Wt;
+    A.t[1] = tile_t(A.t[2], scr);
+    A.t[3] = Si;
+    rm_mask<D>(A, d);
+  }
+  return ok;
+}
+
+// Lower Cholesky factor of a symmetric positive definite matrix held by one
+// wave (diagonal and upper tiles read): the diagonal tiles' factors l0, l1
+// (unit diagonal at padded indices) and both orientations of the tile between.
+// INV: also the tiles of the factor's inverse transpose, g0 = l0^{-T},
+// g1 = l1^{-T}, k01 = -g0 l10' g1.  scr: one padded tile of LDS.
+struct Chol32 {
+  dbl4 l0, l1, l10, l10t, g0, g1, k01;
+};
+template <bool INV>
+__device__ __forceinline__ bool chol32(const dbl4& a, const dbl4& b, const dbl4& c, int d, double* scr,
+                                       Chol32& o) {
+  const dbl4 z = {0.0, 0.0, 0.0, 0.0};
+  bool ok = true;
+  LogDet ld;
+  double p[4], Lk[4], G[4];
+  tile_regs(a, p);
+  tile_sweep16<true, false>(p, d, Lk, ld, ok);
+  o.l0 = tile_of(Lk);
+  chol_tile_rinv(p, Lk, G);
+  o.g0 = tile_of(G);
+  o.l10t = tile_tn(o.g0, b, z);  // (l10)' = l0^{-1} b
+  o.l10 = tile_tn(b, o.g0, z);
+  const dbl4 S = c - tile_tn(o.l10t, o.l10t, z);
+  tile_regs(S, p);
+  tile_sweep16<true, !INV>(p, d - 16, Lk, ld, ok);
+  o.l1 = tile_of(Lk);
+  if constexpr (INV) {
+    chol_tile_rinv(p, Lk, G);
+    o.g1 = tile_of(G);
+    o.k01 = -tile_tn(tile_t(o.g0, scr), tile_tn(o.l10, o.g1, z), z);
+  }
+  return ok;
+}
+
+// Lower Cholesky factor L of a matrix held by one wave, and its transpose LT.
+template <int D>
+__device__ __forceinline__ bool wave_chol(const RM<D>& A, RM<D>& L, RM<D>& LT, int d, double* scr) {
+  bool ok = true;
+  if constexpr (D == 16) {
+    LogDet ld;
+    double p[4], Lk[4];
+    tile_regs(A.t[0], p);
+    tile_sweep16<true, true>(p, d, Lk, ld, ok);
+    L.t[0] = tile_of(Lk);
+  } else {
+    const dbl4 z = {0.0, 0.0, 0.0, 0.0};
+    Chol32 c;
+    ok = chol32<false>(A.t[0], A.t[1], A.t[3], d, scr, c);
+    L.t[0] = c.l0;
+    L.t[1] = z;
+    L.t[2] = c.l10;
+    L.t[3] = c.l1;
+    LT.t[1] = c.l10t;
+    LT.t[2] = z;
+  }
+  AKF_RM_FOR(D, q, r, i, j) if (j > i || i >= d) L.t[q][r] = 0.0;
+  LT.t[0] = tile_t(L.t[0], scr);
+  if constexpr (D == 32) {
+    LT.t[3] = tile_t(L.t[3], scr);
+    AKF_RM_FOR(D, q, r, i, j) if (i >= d || j >= d) LT.t[q][r] = 0.0;
+  }
+  return ok;
+}
+
+// ---------------------------------------------------------------------------
+// Factorisations by a team.  Below D = 64 the team is one wave.  At D = 64 the
+// matrix is split into 32 x 32 blocks [[a, b], [b', c]] and the four waves go
+// through the formulas of wave_inv / chol32 one level up: the 32 x 32 blocks
+// are factored by every wave for itself (from LDS, so nothing is broadcast),
+// and each wave forms one tile of every 32 x 32 product: 21.9k cycles for the
+// inverse and 25.9k for the factor of a 64 x 64 matrix, four pivot tiles of 3.2k
+// each in them.  Four panels of the whole matrix, each with its pivot tile, its
+// block row through LDS and a third of the tiles' updates behind uniform
+// branches, took 27.7k and 34.9k.
+// ---------------------------------------------------------------------------
+// doubles of LDS scratch
 template <int D>
 constexpr int inv_scratch() {
-  using C = Cfg<D>;
-  constexpr int nbuf = C::NW > 1 ? 2 : 1;
-  constexpr int rows = nbuf * 16 * (D + 1), cols = nbuf * D * 17;
-  return D == 16 ? 0 : (rows > cols ? rows : cols);
+  return D == 16 ? 0 : (D == 32 ? 16 * 17 : 3 * 32 * 34);
+}
+
+// 32 x 32 blocks in LDS; the leading dimension makes one block hold a padded
+// tile (16 x 17) for each of the four waves
+struct Blk {
+  static constexpr int LD = 34, SIZE = 32 * LD;
+  // tile (ti, tj) in the accumulator layout, and its transpose
+  static __device__ __forceinline__ dbl4 get(const double* s, int ti, int tj) {
+    const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
+    const double* p = s + (16 * ti + lg) * LD + 16 * tj + lc;
+    return dbl4{p[0], p[4 * LD], p[8 * LD], p[12 * LD]};
+  }
+  static __device__ __forceinline__ dbl4 get_t(const double* s, int ti, int tj) {
+    const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
+    const double* p = s + (16 * ti + lc) * LD + 16 * tj + lg;
+    return dbl4{p[0], p[4], p[8], p[12]};
+  }
+  static __device__ __forceinline__ void put(double* s, int ti, int tj, const dbl4& t) {
+    const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
+    double* p = s + (16 * ti + lg) * LD + 16 * tj + lc;
+    p[0] = t[0];
+    p[4 * LD] = t[1];
+    p[8 * LD] = t[2];
+    p[12 * LD] = t[3];
+  }
+};
+
+__device__ __forceinline__ dbl4 pick2(int k, const dbl4& a, const dbl4& b) {
+  dbl4 o;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) o[r] = k ? b[r] : a[r];
+  return o;
 }
 
 // In-place inverse of a symmetric positive definite matrix held in registers
-// (zero outside the leading d x d block) by block Gauss-Jordan elimination
-// with 16 x 16 pivot blocks P = A_KK:
-//   A_KK <- P^{-1},  A_KJ <- P^{-1} A_KJ,  A_IK <- -A_IK P^{-1},
-//   A_IJ <- A_IJ - A_IK P^{-1} A_KJ.
-// The pivot block is inverted by every wave (tile_sweep16); the block row K
-// is staged through LDS and every other product is a 16 x 16 x 16 MFMA chain.
-// The elimination keeps A_IK = s_I A_KI' (s_I = -1 for processed blocks I < K,
-// +1 otherwise), so A_IK P^{-1} = s_I (P^{-1} A_KI)' needs only block row K.
-// Returns false on a non-positive pivot (the result is then unspecified);
-// *logdet = log det A from the pivots.  scr: inv_scratch<D>() doubles of LDS,
-// free at entry; the call begins and ends with a team barrier.
+// (zero outside the leading d x d block).  Returns false on a non-positive
+// pivot (the result is then unspecified); *logdet = log det A from the pivots.
+// scr: inv_scratch<D>() doubles of LDS, free at entry; the call begins and
+// ends with a team barrier.
 template <int D>
 __device__ bool spd_inv(RM<D>& A, int d, double* scr, double* logdet) {
-  using C = Cfg<D>;
-  static_assert(inv_scratch<D>() <= C::MAT, "scratch must fit one LDS matrix");
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lg = l >> 4, lc = l & 15;
-  bool ok = true;
+  static_assert(inv_scratch<D>() <= Cfg<D>::MAT, "scratch must fit one LDS matrix");
   LogDet ld;
+  bool ok;
   team_sync();
-  if constexpr (D == 16) {
-    double p[4], dummy[4];
-    tile_regs(A.t[0], p);
-    tile_sweep16<false, D == 16>(p, d, dummy, ld, ok);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) A.t[0][r] = p[r];
+  if constexpr (D <= 32) {
+    ok = wave_inv<D>(A, d, scr, ld);
   } else {
-    constexpr int nbuf = C::NW > 1 ? 2 : 1, LDR = D + 1;
-    const int R0 = (D == 64) ? 2 * (w >> 1) : 0, C0 = (D == 64) ? 2 * (w & 1) : 0;
-    const int nb = (d + 15) / 16;
-    for (int kb = 0; kb < nb; ++kb) {
-      double* BR = scr + (kb % nbuf) * 16 * LDR;
-      const int ti_k = kb - R0;
-      if (ti_k >= 0 && ti_k < C::TS) {
+    const int w = threadIdx.x >> 6, R0 = w >> 1, C0 = w & 1;
+    double *Ba = scr, *Bb = Ba + Blk::SIZE, *Bc = Bb + Blk::SIZE;
+    double* own = w == 0 ? Ba : (w == 1 ? Bb : Bc);
+    if (w != 2) {
 #pragma unroll
-        for (int tj = 0; tj < C::TS; ++tj)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            BR[(4 * r + lg) * LDR + 16 * (C0 + tj) + lc] = rm_pick_row<D>(A, ti_k, tj, r);
-      }
+      for (int q = 0; q < 4; ++q) Blk::put(own, q >> 1, q & 1, A.t[q]);
+    }
+    team_sync();
+    RM<32> P, Si;
+    P.t[0] = Blk::get(Ba, 0, 0);
+    P.t[1] = Blk::get(Ba, 0, 1);
+    P.t[3] = Blk::get(Ba, 1, 1);
+    team_sync();  // Ba is the waves' tile scratch now, then X
+    ok = wave_inv<32>(P, min(d, 32), Ba + w * 16 * 17, ld);  // a^{-1}
+    {
+      dbl4 x = {0.0, 0.0, 0.0, 0.0};  // X = P b
+      x = tile_tn(pick2(R0, P.t[0], P.t[1]), Blk::get(Bb, 0, C0), x);
+      x = tile_tn(pick2(R0, P.t[2], P.t[3]), Blk::get(Bb, 1, C0), x);
       team_sync();
-      auto brow = [&](int T, double x[4]) {  // B fragments of A_KT
+      Blk::put(Ba, R0, C0, x);
+    }
+    team_sync();
+    {
+      dbl4 x = {0.0, 0.0, 0.0, 0.0};  // S = c - b' X
+      x = tile_tn(Blk::get(Bb, 0, R0), Blk::get(Ba, 0, C0), x);
+      x = tile_tn(Blk::get(Bb, 1, R0), Blk::get(Ba, 1, C0), x);
+      Blk::put(Bc, R0, C0, Blk::get(Bc, R0, C0) - x);
+    }
+    team_sync();
+    Si.t[0] = Blk::get(Bc, 0, 0);
+    Si.t[1] = Blk::get(Bc, 0, 1);
+    Si.t[3] = Blk::get(Bc, 1, 1);
+    team_sync();  // Bc is scratch
+    ok = wave_inv<32>(Si, d - 32, Bc + w * 16 * 17, ld) && ok;
+    {
+      dbl4 x = {0.0, 0.0, 0.0, 0.0};  // S^{-1} X', over b
+      x = tile_tn(pick2(R0, Si.t[0], Si.t[1]), Blk::get_t(Ba, C0, 0), x);
+      x = tile_tn(pick2(R0, Si.t[2], Si.t[3]), Blk::get_t(Ba, C0, 1), x);
+      Blk::put(Bb, R0, C0, x);
+    }
+    team_sync();
+    {
+      // P + X S^{-1} X', over S
+      dbl4 x = pick2(R0, pick2(C0, P.t[0], P.t[1]), pick2(C0, P.t[2], P.t[3]));
+      x = tile_tn(Blk::get_t(Ba, R0, 0), Blk::get(Bb, 0, C0), x);
+      x = tile_tn(Blk::get_t(Ba, R0, 1), Blk::get(Bb, 1, C0), x);
+      Blk::put(Bc, R0, C0, x);
+    }
+    team_sync();
 #pragma unroll
-        for (int s = 0; s < 4; ++s) x[s] = BR[(4 * s + lg) * LDR + 16 * T + lc];
-      };
-      double pv[4], dummy[4];
-      brow(kb, pv);
-      // the row's other tiles are fetched while the pivot tile is swept
-      double bR[C::TS][4], bC[C::TS][4];
-#pragma unroll
-      for (int t = 0; t < C::TS; ++t) {
-        brow(R0 + t, bR[t]);
-        brow(C0 + t, bC[t]);
-      }
-      tile_sweep16<false, D == 16>(pv, d - 16 * kb, dummy, ld, ok);  // pv = P^{-1}
-      const dbl4 z = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int ti = 0; ti < C::TS; ++ti) {
-        const int TI = R0 + ti;
-        const double sI = (TI < kb) ? -1.0 : 1.0;
-        const double(&bi)[4] = bR[ti];
-        double xa[4];
-        if (TI != kb) {
-          const dbl4 xr = mfma16(pv, bi, z);  // P^{-1} A_KI
-#pragma unroll
-          for (int s = 0; s < 4; ++s) xa[s] = -sI * xr[s];
-        }
-#pragma unroll
-        for (int tj = 0; tj < C::TS; ++tj) {
-          const int TJ = C0 + tj, q = ti * C::TS + tj;
-          if (TI == kb && TJ == kb) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) A.t[q][r] = pv[r];
-          } else if (TI == kb) {
-            A.t[q] = mfma16(pv, bC[tj], z);  // P^{-1} A_KJ
-          } else if (TJ == kb) {
-            const dbl4 y = mfma16(bi, pv, z);  // A_KI' P^{-1}
-            A.t[q] = -sI * y;
-          } else {
-            A.t[q] = mfma16(xa, bC[tj], A.t[q]);  // A_IJ - s_I (P^{-1} A_KI)' A_KJ
-          }
-        }
-      }
+    for (int q = 0; q < 4; ++q) {
+      if (w == 0)
+        A.t[q] = Blk::get(Bc, q >> 1, q & 1);
+      else if (w == 1)
+        A.t[q] = -Blk::get_t(Bb, q & 1, q >> 1);
+      else if (w == 2)
+        A.t[q] = -Blk::get(Bb, q >> 1, q & 1);
+      else
+        A.t[q] = Si.t[q];
     }
   }
-  AKF_RM_FOR(D, q, r, i, j) if (i >= d || j >= d) A.t[q][r] = 0.0;
   team_sync();
   *logdet = ld.value();
   return ok;
 }
 
 // Lower Cholesky factor (positive diagonal) of a symmetric positive definite
-// matrix held in registers (zero outside the leading d x d block), in place,
-// blocked right-looking with 16-column panels: the diagonal block is factored
-// by every wave (tile_sweep16, which also yields A_KK^{-1}); the panel is
-// L_IK = A_IK L_KK^{-T} (chol_tile_rinv); the trailing lower blocks get
-// A_IJ -= L_IK L_JK'.  The block column K is staged through LDS; products are
-// 16 x 16 x 16 MFMA chains.  The strict upper triangle is zeroed.  Returns
-// false on a non-positive pivot; *logdet = log det A.  Same scr contract as
-// spd_inv.
+// matrix held in registers (zero outside the leading d x d block), in place;
+// the strict upper triangle is zeroed.  Returns false on a non-positive pivot.
+// Same scr contract as spd_inv.  At D = 64 with m = (chol a)^{-T}:
+// L10' = m' b, then chol(c - L10 L10').
 template <int D>
-__device__ bool chol_reg(RM<D>& A, int d, double* scr, double* logdet) {
-  using C = Cfg<D>;
-  static_assert(inv_scratch<D>() <= C::MAT, "scratch must fit one LDS matrix");
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lg = l >> 4, lc = l & 15;
+__device__ bool chol_reg(RM<D>& A, int d, double* scr) {
+  static_assert(inv_scratch<D>() <= Cfg<D>::MAT, "scratch must fit one LDS matrix");
+  const dbl4 z = {0.0, 0.0, 0.0, 0.0};
   bool ok = true;
-  LogDet ld;
   team_sync();
   if constexpr (D == 16) {
+    LogDet ld;
     double p[4], Lk[4];
     tile_regs(A.t[0], p);
-    tile_sweep16<true, D == 16>(p, d, Lk, ld, ok);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) A.t[0][r] = Lk[r];
+    tile_sweep16<true, true>(p, d, Lk, ld, ok);
+    A.t[0] = tile_of(Lk);
+  } else if constexpr (D == 32) {
+    Chol32 c;
+    ok = chol32<false>(A.t[0], A.t[1], A.t[3], d, scr, c);
+    A.t[0] = c.l0;
+    A.t[2] = c.l10;
+    A.t[3] = c.l1;
   } else {
-    constexpr int nbuf = C::NW > 1 ? 2 : 1, LDC = 17;
-    const int R0 = (D == 64) ? 2 * (w >> 1) : 0, C0 = (D == 64) ? 2 * (w & 1) : 0;
-    const int nb = (d + 15) / 16;
-    for (int kb = 0; kb < nb; ++kb) {
-      double* BC = scr + (kb % nbuf) * D * LDC;
-      const int tj_k = kb - C0;
-      if (tj_k >= 0 && tj_k < C::TS) {
+    const int w = threadIdx.x >> 6, R0 = w >> 1, C0 = w & 1;
+    double *Ba = scr, *Bb = Ba + Blk::SIZE, *Bc = Bb + Blk::SIZE;
+    double* own = w == 0 ? Ba : (w == 1 ? Bb : Bc);
+    if (w != 2) {
 #pragma unroll
-        for (int ti = 0; ti < C::TS; ++ti)
-          if (R0 + ti >= kb) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              BC[(16 * (R0 + ti) + 4 * r + lg) * LDC + lc] = rm_pick_col<D>(A, ti, tj_k, r);
-          }
-      }
+      for (int q = 0; q < 4; ++q) Blk::put(own, q >> 1, q & 1, A.t[q]);
+    }
+    team_sync();
+    Chol32 c, e;
+    {
+      const dbl4 a0 = Blk::get(Ba, 0, 0), a1 = Blk::get(Ba, 0, 1), a3 = Blk::get(Ba, 1, 1);
+      team_sync();  // Ba is the waves' tile scratch now, then L10'
+      ok = chol32<true>(a0, a1, a3, min(d, 32), Ba + w * 16 * 17, c);
+    }
+    {
+      // tile row 0 of m' b takes g0 alone, row 1 takes k01 and g1
+      dbl4 x = tile_tn(pick2(R0, c.g0, c.k01), Blk::get(Bb, 0, C0), z);
+      if (R0) x = tile_tn(c.g1, Blk::get(Bb, 1, C0), x);
       team_sync();
-      auto bcolt = [&](int T, double x[4]) {  // A fragments of A_TK (= B fragments of A_TK')
+      Blk::put(Ba, R0, C0, x);
+    }
+    team_sync();
+    {
+      dbl4 x = tile_tn(Blk::get(Ba, 0, R0), Blk::get(Ba, 0, C0), z);
+      x = tile_tn(Blk::get(Ba, 1, R0), Blk::get(Ba, 1, C0), x);
+      Blk::put(Bc, R0, C0, Blk::get(Bc, R0, C0) - x);
+    }
+    team_sync();
+    ok = chol32<false>(Blk::get(Bc, 0, 0), Blk::get(Bc, 0, 1), Blk::get(Bc, 1, 1), d - 32, nullptr, e) &&
+         ok;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) x[s] = BC[(16 * T + lc) * LDC + 4 * s + lg];
-      };
-      double pv[4], Lk[4], G[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) pv[r] = BC[(16 * kb + 4 * r + lg) * LDC + lc];
-      tile_sweep16<true, D == 16>(pv, d - 16 * kb, Lk, ld, ok);  // pv = A_KK^{-1}, Lk = L_KK
-      const dbl4 z = {0.0, 0.0, 0.0, 0.0};
-      chol_tile_rinv(pv, Lk, G);  // G = L_KK^{-T}
-      double LTr[C::TS][4], LTc[C::TS][4];  // (L_TK)' for the wave's row / column tiles
-#pragma unroll
-      for (int t = 0; t < C::TS; ++t) {
-        if (R0 + t > kb) {
-          double a[4];
-          bcolt(R0 + t, a);
-          tile_regs(mfma16(G, a, z), LTr[t]);
-#pragma unroll
-          for (int s = 0; s < 4; ++s) LTr[t][s] = -LTr[t][s];
-        }
-        if (C0 + t > kb) {
-          double a[4];
-          bcolt(C0 + t, a);
-          tile_regs(mfma16(G, a, z), LTc[t]);
-        }
-      }
-#pragma unroll
-      for (int ti = 0; ti < C::TS; ++ti) {
-        const int TI = R0 + ti;
-#pragma unroll
-        for (int tj = 0; tj < C::TS; ++tj) {
-          const int TJ = C0 + tj, q = ti * C::TS + tj;
-          if (TI == kb && TJ == kb) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) A.t[q][r] = Lk[r];
-          } else if (TJ == kb && TI > kb) {
-            double a[4];
-            bcolt(TI, a);
-            A.t[q] = mfma16(a, G, z);  // L_IK = A_IK G
-          } else if (TI > kb && TJ > kb && TI >= TJ) {
-            A.t[q] = mfma16(LTr[ti], LTc[tj], A.t[q]);  // A_IJ - L_IK L_JK'
-          }
-        }
-      }
+    for (int q = 0; q < 4; ++q) {
+      if (w == 2)
+        A.t[q] = Blk::get_t(Ba, q & 1, q >> 1);
+      else if (w != 1)
+        A.t[q] = pick2(w, q == 0 ? c.l0 : (q == 2 ? c.l10 : c.l1),
+                       q == 0 ? e.l0 : (q == 2 ? e.l10 : e.l1));
     }
   }
   AKF_RM_FOR(D, q, r, i, j) if (j > i || i >= d) A.t[q][r] = 0.0;
   team_sync();
-  *logdet = ld.value();
   return ok;
 }
 

@@ -33,19 +33,6 @@ constexpr size_t wave_lds_bytes() {
   return (size_t)(wave_scr<D>() + 8 * D) * sizeof(double);
 }
 
-// transpose of a tile through 16 x 17 doubles of LDS
-__device__ __forceinline__ dbl4 tile_t(const dbl4& t, double* s) {
-  const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) s[lc * 17 + 4 * r + lg] = t[r];
-  wave_lds_fence();
-  dbl4 o;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) o[r] = s[(4 * r + lg) * 17 + lc];
-  wave_lds_fence();
-  return o;
-}
-
 template <int D>
 __device__ __forceinline__ RM<D> rm_t(const RM<D>& a, double* scr) {
   constexpr int TS = Cfg<D>::TS;
@@ -56,13 +43,6 @@ __device__ __forceinline__ RM<D> rm_t(const RM<D>& a, double* scr) {
     for (int tj = 0; tj < TS; ++tj)
       o.t[tj * TS + ti] = tile_t(a.t[ti * TS + tj], scr + (ti * TS + tj) * 16 * 17);
   return o;
-}
-
-// c + a' b of one tile
-__device__ __forceinline__ dbl4 tile_tn(const dbl4& a, const dbl4& b, dbl4 c) {
-#pragma unroll
-  for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
-  return c;
 }
 
 // c += x' y over the first KT tile rows of x and y, result tile rows < RT and
@@ -171,84 +151,6 @@ __device__ __forceinline__ void vec_put(double* s, double v) {
 // ---------------------------------------------------------------------------
 // factorisations
 // ---------------------------------------------------------------------------
-template <int D>
-__device__ __forceinline__ void rm_mask(RM<D>& a, int d) {
-  AKF_RM_FOR(D, q, r, i, j) if (i >= d || j >= d) a.t[q][r] = 0.0;
-}
-
-__device__ __forceinline__ dbl4 tile_of(const double p[4]) { return dbl4{p[0], p[1], p[2], p[3]}; }
-
-// In-place inverse of a symmetric positive definite matrix (zero outside the
-// leading d x d block) by 2 x 2 blocks of tiles [[a, b], [b', c]]: with
-// P = a^{-1}, X = P b and S = c - b' X,
-//   inverse = [[P + X S^{-1} X', -X S^{-1}], [-S^{-1} X', S^{-1}]].
-// Reads the diagonal and upper tiles; the result's lower tile mirrors its
-// upper one.  KT = 1: d <= 16, the first tile alone (the others are not
-// touched).  Pivots, failure and ld as in spd_inv.
-template <int D, int KT = Cfg<D>::TS>
-__device__ __forceinline__ bool wave_inv(RM<D>& A, int d, double* scr, LogDet& ld) {
-  bool ok = true;
-  double p[4], dummy[4];
-  tile_regs(A.t[0], p);
-  tile_sweep16<false, KT == 1>(p, d, dummy, ld, ok);
-  if constexpr (KT == 1) {
-    A.t[0] = tile_of(p);
-    const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (4 * r + lg >= d || lc >= d) A.t[0][r] = 0.0;
-  } else {
-    const dbl4 z = {0.0, 0.0, 0.0, 0.0};
-    const dbl4 P = tile_of(p);
-    const dbl4 X = tile_tn(P, A.t[1], z);           // P b
-    const dbl4 Z = tile_t(X, scr);                  // X'
-    const dbl4 S = A.t[3] - tile_tn(A.t[1], X, z);  // c - b' X
-    tile_regs(S, p);
-    tile_sweep16<false, true>(p, d - 16, dummy, ld, ok);
-    const dbl4 Si = tile_of(p);
-    const dbl4 Wt = tile_tn(Si, Z, z);  // S^{-1} X'
-    A.t[0] = tile_tn(Z, Wt, P);         // P + X S^{-1} X'
-    A.t[2] = -Wt;
-    A.t[1] = tile_t(A.t[2], scr + 16 * 17);
-    A.t[3] = Si;
-    rm_mask<D>(A, d);
-  }
-  return ok;
-}
-
-// Lower Cholesky factor L of a symmetric positive definite matrix (diagonal
-// and upper tiles read) and its transpose LT.
-template <int D>
-__device__ __forceinline__ bool wave_chol(const RM<D>& A, RM<D>& L, RM<D>& LT, int d, double* scr) {
-  const dbl4 z = {0.0, 0.0, 0.0, 0.0};
-  bool ok = true;
-  LogDet ld;
-  double p[4], Lk[4];
-  tile_regs(A.t[0], p);
-  tile_sweep16<true, D == 16>(p, d, Lk, ld, ok);
-  L.t[0] = tile_of(Lk);
-  if constexpr (D == 32) {
-    double G[4];
-    chol_tile_rinv(p, Lk, G);  // L_00^{-T}
-    const dbl4 g = tile_of(G);
-    LT.t[1] = tile_tn(g, A.t[1], z);  // (L_10)'
-    L.t[1] = z;
-    L.t[2] = tile_tn(A.t[1], g, z);  // A_10 L_00^{-T}
-    const dbl4 S = A.t[3] - tile_tn(LT.t[1], LT.t[1], z);
-    tile_regs(S, p);
-    tile_sweep16<true, true>(p, d - 16, Lk, ld, ok);
-    L.t[3] = tile_of(Lk);
-  }
-  AKF_RM_FOR(D, q, r, i, j) if (j > i || i >= d) L.t[q][r] = 0.0;
-  LT.t[0] = tile_t(L.t[0], scr);
-  if constexpr (D == 32) {
-    LT.t[2] = z;
-    LT.t[3] = tile_t(L.t[3], scr + 16 * 17);
-    AKF_RM_FOR(D, q, r, i, j) if (i >= d || j >= d) LT.t[q][r] = 0.0;
-  }
-  return ok;
-}
-
 // x_ij *= v_i
 template <int D>
 __device__ __forceinline__ void scale_rows(RM<D>& x, const RV<D>& v) {

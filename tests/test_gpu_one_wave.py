@@ -133,3 +133,11 @@ def test_multivariate_t_sites(S, N, d, dy, repeat):
     for k in ("logZ_fwd", "logZ_rev", "log_ratio"):
         assert abs(float(out[k][0]) - r[k]) < 1e-9 * N * d * max(1.0, abs(r["logZ_fwd"]))
     assert _rel(N_(out["x_out"]), r["x_out"]) < TOL
+
+
+# width 64: factorisations by 2 x 2 blocks of 32, at the edges of the second
+# block and of its tiles
+@pytest.mark.parametrize("d", [33, 48, 49, 63, 64])
+@pytest.mark.parametrize("N,block", [(1, 0), (29, 4)])
+def test_width_64(S, d, N, block):
+    test_filter_and_sampler(S, d, N, block)
