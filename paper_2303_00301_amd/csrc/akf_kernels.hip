@@ -1445,6 +1445,11 @@ __global__ void __launch_bounds__(Cfg<D>::NT, 2) k_samp_build(KModel M, SampArgs
   samp_build_body<D, (D == 64 ? 8 : D / 4)>(M, S, blockIdx.x);  // no more spills than U = 4
 }
 
+__global__ void __launch_bounds__(64, 1) k_samp_build_w64(KModel M, SampArgs S) {
+  if (gate_shut(M.gate)) return;
+  w64_sbuild(M, S, blockIdx.x);
+}
+
 // Sampler, block fold: suffix aggregate (E~, U~) of a block, folding from its
 // last step backwards: (E~, U~) <- (E_t E~, E_t U~ + U_t).
 template <int D, int U = 4>
@@ -1917,8 +1922,15 @@ template <int D>
 hipError_t launch_sampler(const KModel& M, SampArgs S, TreeArgs* lv_up, TreeArgs* lv_down,
                           int n_levels, hipStream_t st) {
   timing_mark(FAM_SAMP_BUILD, 1, st);
-  hipLaunchKernelGGL(k_samp_build<D>, dim3(M.N), dim3(Cfg<D>::NT), lds_bytes_samp_build<D>(), st,
-                     M, S);
+  // D = 64: a step takes a lone wave 77 us and a team 50 - 56 us alone on a CU,
+  // 77 - 83 with another; once the steps outnumber the resident teams, two to
+  // a CU, the waves win (d = 64, N = 256: 77 against 56 us, 512: 81 / 83,
+  // 768: 87 / 127, 1024: 92 / 159)
+  if (D == 64 && M.N > 2 * compute_units())
+    hipLaunchKernelGGL(k_samp_build_w64, dim3(M.N), dim3(64), W64::LDS * sizeof(double), st, M, S);
+  else
+    hipLaunchKernelGGL(k_samp_build<D>, dim3(M.N), dim3(Cfg<D>::NT), lds_bytes_samp_build<D>(), st,
+                       M, S);
   timing_mark(FAM_SAMP_BUILD, 0, st);
   return launch_samp_scan<D>(M, S, lv_up, lv_down, n_levels, st);
 }

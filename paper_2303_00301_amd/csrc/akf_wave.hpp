@@ -658,14 +658,348 @@ __device__ __forceinline__ void wave_sbuild(const KModel& M, const SampArgs& S, 
     if (S.Et) rm_store<D>(ET, S.Et + (int64_t)t * D * D, D, D);
     vec_put<D>(va, mp);
     g = m - mv<D>(ET, rv<D>(va));  // m^f - E m^p
-    RM<D> Lm = tn0<D, true>(G, ET);  // E G
-    rm_rsub<D>(Lm, Pf);              // L_t = P^f - E G
+    // L_t = P^f - E G, averaged with its transpose: where P^p is ill
+    // conditioned one triangle alone is 3x further from the exact L_t
+    RM<D> Lm = tn0<D>(G, ET);
+    rm_rsub<D>(Lm, Pf);
+    if constexpr (D == 32) Lm.t[1] = 0.5 * (Lm.t[1] + tile_t(Lm.t[2], scr));
     symm<D>(Lm, scr);
     ok = wave_chol<D>(Lm, L, LT, d, scr) && ok;
   }
   if (S.Lc) rm_store<D>(LT, S.Lc + (int64_t)t * D * D, D, D);  // chol(L_t), kept transposed
   const double u = g + mv<D>(LT, rv<D>(vxi));
   if (l < D) S.U[(int64_t)t * D + l] = u;
+  if (!ok && l == 0) atomicOr(S.status, ST_FWD_NOT_PD);
+}
+
+// ---------------------------------------------------------------------------
+// Sampler, element build at D = 64 by one wave (the formulas of wave_sbuild).
+// A step's factorisations are serial chains that a team's waves repeat or wait
+// for, and its products are bound by the matrix cores either way; one step to
+// a wave, four to a CU, leaves the chains of four steps to overlap: 180k
+// cycles for four steps, 103k of them on the matrix cores, against 170k for
+// two by teams of four waves.  The 16
+// tiles of a 64 x 64 matrix take 128 of the lone wave's 512 registers, so two
+// matrices and a symmetric one are held at a time, and F, then G, lives in the
+// wave's own LDS (leading dimension 65), read tile by tile transposed in the
+// shadow of the products.
+// ---------------------------------------------------------------------------
+// n doubles read through a buffer resource: an index past them gives zero, so
+// padding needs no branch (a select on a loaded value is turned into one, with
+// a wait for each load)
+struct ZeroPad {
+  static constexpr int OUT = 1 << 26;  // n stays below it, and two of them in 32 bits of bytes
+  __amdgpu_buffer_rsrc_t rs;
+  __device__ __forceinline__ ZeroPad(const double* g, int n)
+      : rs(__builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(g), 0, 8 * n, 0x00020000)) {}
+  __device__ __forceinline__ double get(int i) const {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, 8 * i, 0, 0));
+  }
+};
+
+struct W64 {
+  static constexpr int LD = 65;
+  dbl4 t[16];  // tile (ti, tj) at 4 ti + tj
+
+  // doubles of LDS: a matrix, a padded tile, three vectors
+  static constexpr int LDS = 64 * LD + 16 * 17 + 3 * 64;
+
+  // the leading d x d entries of g (uniform), zero elsewhere
+  __device__ __forceinline__ void load(const double* g, int ld, int d, bool up) {
+    const int l = threadIdx.x, lg = l >> 4, lc = l & 15;
+    const ZeroPad b(g, d * ld);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      if (up && (q >> 2) > (q & 3)) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * (q >> 2) + 4 * r + lg, j = 16 * (q & 3) + lc;
+        t[q][r] = b.get((j < d ? j : ZeroPad::OUT) + (i < d ? i * ld : ZeroPad::OUT));
+      }
+    }
+  }
+  // all 64 x 64 entries
+  __device__ __forceinline__ void store(double* __restrict__ g) const {
+    const int l = threadIdx.x, lg = l >> 4, lc = l & 15;
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        g[(16 * (q >> 2) + 4 * r + lg) * 64 + 16 * (q & 3) + lc] = t[q][r];
+  }
+  __device__ __forceinline__ void store_t(double* __restrict__ g) const {
+    const int l = threadIdx.x, lg = l >> 4, lc = l & 15;
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        g[(16 * (q & 3) + lc) * 64 + 16 * (q >> 2) + 4 * r + lg] = t[q][r];
+  }
+  __device__ __forceinline__ void mirror(double* tile) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = i + 1; j < 4; ++j) t[4 * j + i] = tile_t(t[4 * i + j], tile);
+  }
+};
+
+// tile (k, j) of the transpose of the matrix in LDS
+__device__ __forceinline__ dbl4 w64_get_t(const double* s, int k, int j) {
+  const int l = threadIdx.x, lg = l >> 4, lc = l & 15;
+  const double* p = s + (16 * j + lc) * W64::LD + 16 * k + lg;
+  return dbl4{p[0], p[4], p[8], p[12]};
+}
+
+// lane 16 * tj + lc: (x' v)_j over the first tile rows of column tj (KT(tj) of
+// them), v by row in LDS
+template <typename F>
+__device__ __forceinline__ double w64_mv(const F& tile, const double* v, bool up) {
+  const int l = threadIdx.x, lg = l >> 4;
+  double s[4];
+#pragma unroll
+  for (int tj = 0; tj < 4; ++tj) {
+    double a = 0.0, b = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (up && k > tj) continue;
+      const dbl4 x = tile(k, tj);
+      const double* vk = v + 16 * k + lg;
+      a = fma(x[0], vk[0], a);
+      b = fma(x[1], vk[4], b);
+      a = fma(x[2], vk[8], a);
+      b = fma(x[3], vk[12], b);
+    }
+    s[tj] = sum_groups(a + b);
+  }
+  const double lo = (l & 16) ? s[1] : s[0], hi = (l & 16) ? s[3] : s[2];
+  return (l & 32) ? hi : lo;
+}
+
+// the leading, the off-diagonal and the trailing 32 x 32 block's tile (i, j)
+#define AKF_W64_A(i, j) t[4 * (i) + (j)]
+#define AKF_W64_B(i, j) t[4 * (i) + 2 + (j)]
+#define AKF_W64_C(i, j) t[4 * (2 + (i)) + 2 + (j)]
+
+// In-place inverse of a symmetric positive definite matrix (upper tiles read,
+// all written) by 2 x 2 blocks of 32, as spd_inv.
+__device__ __forceinline__ bool w64_inv(W64& A, int d, double* tile) {
+  const dbl4 z = {0.0, 0.0, 0.0, 0.0};
+  LogDet ld;
+  RM<32> P, S, X, Z;
+  P.t[0] = A.AKF_W64_A(0, 0);
+  P.t[1] = A.AKF_W64_A(0, 1);
+  P.t[3] = A.AKF_W64_A(1, 1);
+  bool ok = wave_inv<32>(P, min(d, 32), tile, ld);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)  // X = P b
+      X.t[2 * i + j] = tile_tn(P.t[2 + i], A.AKF_W64_B(1, j), tile_tn(P.t[i], A.AKF_W64_B(0, j), z));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = i; j < 2; ++j)  // S = c - b' X
+      S.t[2 * i + j] = A.AKF_W64_C(i, j) - tile_tn(A.AKF_W64_B(1, i), X.t[2 + j],
+                                                   tile_tn(A.AKF_W64_B(0, i), X.t[j], z));
+  ok = wave_inv<32>(S, d - 32, tile, ld) && ok;
+  #pragma unroll
+  for (int q = 0; q < 4; ++q) Z.t[2 * (q & 1) + (q >> 1)] = tile_t(X.t[q], tile);
+  RM<32> W;  // S^{-1} X'
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      W.t[2 * i + j] = tile_tn(S.t[2 + i], Z.t[2 + j], tile_tn(S.t[i], Z.t[j], z));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = i; j < 2; ++j)  // P + X S^{-1} X'
+      P.t[2 * i + j] = tile_tn(Z.t[2 + i], W.t[2 + j], tile_tn(Z.t[i], W.t[j], P.t[2 * i + j]));
+  A.AKF_W64_A(0, 0) = P.t[0];
+  A.AKF_W64_A(0, 1) = P.t[1];
+  A.AKF_W64_A(1, 0) = tile_t(P.t[1], tile);
+  A.AKF_W64_A(1, 1) = P.t[3];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      A.t[4 * (2 + i) + j] = -W.t[2 * i + j];
+      A.AKF_W64_B(j, i) = tile_t(-W.t[2 * i + j], tile);
+      A.AKF_W64_C(i, j) = S.t[2 * i + j];
+    }
+  return ok;
+}
+
+// L' (upper tiles written) for L the lower Cholesky factor of a matrix (upper
+// tiles read), in place, as chol_reg.
+__device__ __forceinline__ bool w64_chol_t(W64& A, int d, double* tile) {
+  const dbl4 z = {0.0, 0.0, 0.0, 0.0};
+  Chol32 c, e;
+  bool ok = chol32<true>(A.AKF_W64_A(0, 0), A.AKF_W64_A(0, 1), A.AKF_W64_A(1, 1), min(d, 32), tile, c);
+  dbl4 X[4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {  // L10' = m' b
+    X[j] = tile_tn(c.g0, A.AKF_W64_B(0, j), z);
+    X[2 + j] = tile_tn(c.g1, A.AKF_W64_B(1, j), tile_tn(c.k01, A.AKF_W64_B(0, j), z));
+  }
+  dbl4 S[3];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = i; j < 2; ++j)
+      S[i + j] = A.AKF_W64_C(i, j) - tile_tn(X[2 + i], X[2 + j], tile_tn(X[i], X[j], z));
+  ok = chol32<false>(S[0], S[1], S[2], d - 32, tile, e) && ok;
+  A.AKF_W64_A(0, 0) = tile_t(c.l0, tile);
+  A.AKF_W64_A(0, 1) = c.l10t;
+  A.AKF_W64_A(1, 1) = tile_t(c.l1, tile);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) A.AKF_W64_B(q >> 1, q & 1) = X[q];
+  A.AKF_W64_C(0, 0) = tile_t(e.l0, tile);
+  A.AKF_W64_C(0, 1) = e.l10t;
+  A.AKF_W64_C(1, 1) = tile_t(e.l1, tile);
+  const int l = threadIdx.x, lg = l >> 4, lc = l & 15;
+#pragma unroll
+  for (int q = 0; q < 16; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if ((q >> 2) > (q & 3) || 16 * (q >> 2) + 4 * r + lg > 16 * (q & 3) + lc ||
+          16 * (q & 3) + lc >= d)
+        A.t[q][r] = 0.0;
+  return ok;
+}
+
+__device__ __forceinline__ void w64_sbuild(const KModel& M, const SampArgs& S, int t) {
+  extern __shared__ double lds[];
+  double* sm = lds;  // F, then G' (by rows, so that transposed tiles of it are G's)
+  double* tile = sm + 64 * W64::LD;
+  double* vm = tile + 16 * 17;
+  double* vxi = vm + 64;
+  double* vmp = vxi + 64;
+  const int l = threadIdx.x, lg = l >> 4, lc = l & 15, d = M.d;
+  const bool in = l < d;
+  const dbl4 z = {0.0, 0.0, 0.0, 0.0};
+  const double* Pfg = S.Pf + (int64_t)t * S.ldm * S.ldm;
+  double* Eo = S.E + (int64_t)t * 64 * 64;
+  const double m = in ? S.mf[(int64_t)t * S.ldm + l] : 0.0;
+  vm[l] = m;
+  vxi[l] = in ? S.xi_x[(int64_t)t * d + l] : 0.0;
+  bool ok = true;
+  double g = m;
+  W64 L;
+  if (t == M.N - 1) {
+    W64 Z;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) Z.t[q] = z;
+    Z.store(Eo);
+    if (S.Et) Z.store(S.Et + (int64_t)t * 64 * 64);
+    L.load(Pfg, S.ldm, d, true);
+  } else {
+    // the transition into step t + 1
+    const double* F = S.Ft ? S.Ft + (int64_t)(t + 1) * d * d : M.F;
+    const double* bt = S.Ft ? S.bt + (int64_t)(t + 1) * d : M.b;
+    W64 X, Y;
+    X.load(Pfg, S.ldm, d, false);
+    const ZeroPad fb(F, d * d);
+    const int lo = in ? l : ZeroPad::OUT;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      double v[32];
+#pragma unroll
+      for (int i = 0; i < 32; ++i) v[i] = fb.get((32 * h + i) * d + lo);  // rows past d: past the end
+#pragma unroll
+      for (int i = 0; i < 32; ++i) sm[(32 * h + i) * W64::LD + l] = v[i];
+    }
+    const double bl = (in && bt) ? bt[l] : 0.0;
+    wave_lds_fence();
+    W64 Pp;
+    Pp.load(M.Q, d, d, true);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) Y.t[q] = z;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const dbl4 f = w64_get_t(sm, k, j);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Y.t[4 * i + j] = tile_tn(X.t[4 * k + i], f, Y.t[4 * i + j]);
+      }  // Y = G' = P^f F'
+    const double mp = bl + w64_mv([&](int k, int j) { return w64_get_t(sm, k, j); }, vm, false);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const dbl4 f = w64_get_t(sm, k, j);
+#pragma unroll
+        for (int i = 0; i <= j; ++i) Pp.t[4 * i + j] = tile_tn(Y.t[4 * k + i], f, Pp.t[4 * i + j]);
+      }  // Q + F P^f F'
+    vmp[l] = mp;
+    wave_lds_fence();
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        sm[(16 * (q >> 2) + 4 * r + lg) * W64::LD + 16 * (q & 3) + lc] = Y.t[q][r];
+    wave_lds_fence();
+    X = Pp;
+    ok = w64_inv(X, d, tile);
+    Pp.mirror(tile);
+    {  // Newton-Schulz step X + X (I - P^p X): P^p inherits the conditioning of Q
+      W64 Xn;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        dbl4 R[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          dbl4 c = z;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) c = tile_tn(Pp.t[4 * k + i], X.t[4 * k + j], c);
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            R[i][r] = ((i == j && 4 * r + lg == lc && 16 * j + lc < d) ? 1.0 : 0.0) - c[r];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          dbl4 c = X.t[4 * i + j];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) c = tile_tn(X.t[4 * k + i], R[k], c);
+          Xn.t[4 * i + j] = c;
+        }
+      }
+      X = Xn;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) Y.t[q] = z;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const dbl4 f = w64_get_t(sm, k, j);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Y.t[4 * i + j] = tile_tn(X.t[4 * k + i], f, Y.t[4 * i + j]);
+      }  // Y = E' = (P^p)^{-1} G
+    L.load(Pfg, S.ldm, d, true);  // ahead of the stores, which it would wait for
+    Y.store_t(Eo);
+    if (S.Et) Y.store(S.Et + (int64_t)t * 64 * 64);
+    g = m - w64_mv([&](int k, int j) { return Y.t[4 * k + j]; }, vmp, false);  // m^f - E m^p
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      dbl4 c[4] = {z, z, z, z};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const dbl4 f = w64_get_t(sm, k, i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[j] = tile_tn(f, Y.t[4 * k + j], c[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (j >= i) L.t[4 * i + j] -= 0.5 * c[j];
+        if (j <= i) L.t[4 * j + i] -= 0.5 * tile_t(c[j], tile);
+      }
+    }  // L_t = P^f - (E G + (E G)') / 2, as in wave_sbuild
+  }
+  ok = w64_chol_t(L, d, tile) && ok;
+  if (S.Lc) L.store(S.Lc + (int64_t)t * 64 * 64);  // chol(L_t), kept transposed
+  S.U[(int64_t)t * 64 + l] = g + w64_mv([&](int k, int j) { return L.t[4 * k + j]; }, vxi, true);
   if (!ok && l == 0) atomicOr(S.status, ST_FWD_NOT_PD);
 }
 

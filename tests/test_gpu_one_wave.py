@@ -141,3 +141,10 @@ def test_multivariate_t_sites(S, N, d, dy, repeat):
 @pytest.mark.parametrize("N,block", [(1, 0), (29, 4)])
 def test_width_64(S, d, N, block):
     test_filter_and_sampler(S, d, N, block)
+
+
+# width 64, more steps than resident teams: the sampler's elements are built by
+# one wave per step
+@pytest.mark.parametrize("d,N", [(33, 515), (49, 600), (64, 1025)])
+def test_width_64_one_wave_build(S, d, N):
+    test_filter_and_sampler(S, d, N, 0)
