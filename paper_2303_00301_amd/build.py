@@ -14,6 +14,12 @@ SOURCES = ["akf_kernels.hip", "akf_adjoint.hip", "akf_fact.hip", "akf_dyn.hip", 
            "akf_layout.cpp", "akf_capi.cpp", "akf_batch.cpp"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # Matrix instructions accumulate in the vector registers.  Otherwise the
+         # compiler gives every kernel that may use over 256 registers
+         # accumulators in the other half of the file, with 16 moves around the
+         # product of a 16 x 16 tile (4 instructions) where its operands or
+         # results are used elsewhere.
+         "-mllvm", "-amdgpu-mfma-vgpr-form",
          "-Wall", "-Wno-unused-function", "-Wno-unused-variable"]
 
 
