@@ -407,83 +407,164 @@ __device__ __forceinline__ double rsqrt_nr(double q) {
   return r;
 }
 
+// w[k] = the value of v in lane 16 k + l%16: each group's row to every lane, by
+// half exchanges.
+__device__ __forceinline__ void group_rows(double v, double w[4]) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  uint32_t h[2][4];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const uint32_t x = (uint32_t)(u >> (32 * s));
+    const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const auto c = __builtin_amdgcn_permlane16_swap(a[i], a[i], false, false);
+      h[s][2 * i] = c[0];
+      h[s][2 * i + 1] = c[1];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    w[k] = __builtin_bit_cast(double, ((uint64_t)h[1][k] << 32) | h[0][k]);
+}
+
+// v[l/16]
+__device__ __forceinline__ double group_pick(const double v[4]) {
+  const int l = threadIdx.x;
+  const double a = (l & 16) ? v[1] : v[0], b = (l & 16) ? v[3] : v[2];
+  return (l & 32) ? b : a;
+}
+
 // One wave inverts a symmetric positive definite 16 x 16 tile held in the
-// accumulator layout (p[r] = P[4r + l/16][l%16]) by 16 steps of the symmetric
-// sweep operator: with c = column k of the current matrix and pivot q = c_k,
-//   a_ij <- a_ij - c_i c_j / q (i, j != k),  a_ik = a_ki <- c_i / q,  a_kk <- -1/q,
-// which leaves -P^{-1}.  The matrix stays symmetric, so column k is also row k.
-// Column k reaches the lanes of each row of 16 by a DPP row broadcast of lane
-// k (c_i for the lane's rows i = 4r + l/16), row k by a lane permute (c_j for
-// the lane's column j = l%16), the pivot by a lane read.  Every element update
-// is one FMA, a' = c_i g_j + m a, with g_j = -c_j/q (g_k = 1/q) and m = 0 on
-// column k, 1 elsewhere; row k is then -g.  The pivots are those of the LDL'
-// factorisation; with CHOL column k's unscaled entries and its pivot are kept
-// as they pass (by the lanes of column k) and scaled by 1/sqrt(q) at the end,
-// one square root for all sixteen.  Bound by the chain update - lane permute
-// (58 cycles) - scaling - update of a lone wave: 190 cycles a pivot; with CHOL
-// 237, against 283 with the factor scaled pivot by pivot.  Indices >= nv are
-// padding: they get a unit diagonal.  A non-positive pivot clears ok (the results are then
-// unspecified).
-template <bool CHOL, bool PART = false>
+// accumulator layout (p[r] = P[4r + l/16][l%16]) by four steps of the
+// symmetric sweep operator on blocks of four pivots: with W the block's rows
+// (4 x 16, one register of the layout) and B their 4 x 4 block,
+//   a <- a - W' B^{-1} W,  block columns <- W' B^{-1},  block rows <- B^{-1} W,
+//   block <- -B^{-1},
+// which leaves -P^{-1}.  With W~ = W, but -I in the block's columns, all of it
+// is one MFMA, m a - W' G with G = B^{-1} W~ and m = 0 in the block's columns,
+// and the block's rows are G itself.  Every lane factors B = L D L' for itself
+// (W's rows reach all lane groups by half exchanges, B's entries by DPP
+// broadcasts) and solves for its own column of G.  The pivots are those of the
+// LDL' factorisation of the tile; with CHOL the columns of L D are the rows
+// L^{-1} W, transposed into place by a second MFMA off the chain, and scaled by
+// 1/sqrt(pivot) at the end, one square root for all sixteen.  Bound by the
+// issue of about 110 vector instructions a block and the MFMA's latency:
+// 2.4k cycles a tile, with CHOL 2.9k; sixteen single pivots, each a lane
+// permute (58 cycles), a scaling and an update in a chain, took 3.0k and 3.8k.
+// Indices >= nv are padding: they get a unit diagonal.  A non-positive pivot
+// clears ok (the results are then unspecified).
+template <bool CHOL, int PART = 0>
 __device__ __forceinline__ void tile_sweep16(double p[4], int nv, double Lk[4], LogDet& ld,
                                              bool& ok) {
   const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int r = 0; r < 4; ++r)
     if (4 * r + lg >= nv && 4 * r + lg == lc) p[r] = 1.0;
-    if constexpr (CHOL) Lk[r] = 0.0;
-  }
-  double prod = 1.0, qd = 1.0;
-  auto step = [&](auto kc) {
+  dbl4 La = {0.0, 0.0, 0.0, 0.0};
+  double qd = 1.0;
+  auto step = [&](auto bc) {
+    constexpr int b = decltype(bc)::value;
+    const double W = p[b];
+    double w[4], v[4], g[4];
+    group_rows(W, w);
+    const double a00 = row_bcast<4 * b>(w[0]), a01 = row_bcast<4 * b + 1>(w[0]),
+                 a02 = row_bcast<4 * b + 2>(w[0]), a03 = row_bcast<4 * b + 3>(w[0]);
+    const double a11 = row_bcast<4 * b + 1>(w[1]), a12 = row_bcast<4 * b + 2>(w[1]),
+                 a13 = row_bcast<4 * b + 3>(w[1]);
+    const double a22 = row_bcast<4 * b + 2>(w[2]), a23 = row_bcast<4 * b + 3>(w[2]);
+    const double a33 = row_bcast<4 * b + 3>(w[3]);
+    // B = L D L': pivots q, their reciprocals i, columns of L
+    const double i0 = recip(a00);
+    const double l1 = a01 * i0, l2 = a02 * i0, l3 = a03 * i0;
+    const double b11 = fma(-l1, a01, a11), b12 = fma(-l1, a02, a12), b13 = fma(-l1, a03, a13);
+    const double b22 = fma(-l2, a02, a22), b23 = fma(-l2, a03, a23), b33 = fma(-l3, a03, a33);
+    const double i1 = recip(b11);
+    const double m2 = b12 * i1, m3 = b13 * i1;
+    const double c22 = fma(-m2, b12, b22), c23 = fma(-m2, b13, b23), c33 = fma(-m3, b13, b33);
+    const double i2 = recip(c22);
+    const double n3 = c23 * i2;
+    const double q3 = fma(-n3, c23, c33);
+    const double i3 = recip(q3);
+    ok = ok && (a00 > 0.0) && (b11 > 0.0) && (c22 > 0.0) && (q3 > 0.0);
+    ld.mul((a00 * b11) * (c22 * q3));
+    // opaque to the compiler, which would otherwise hold the lane masks in
+    // registers across the loops around the sweep (and spill)
+    int lcb = lc;
+    asm volatile("" : "+v"(lcb));
+    const bool blk = (lcb >> 2) == b;
+    const double mc = blk ? 0.0 : 1.0;
+    auto forward = [&](const double x[4]) {  // L^{-1} x
+      v[0] = x[0];
+      v[1] = fma(-l1, v[0], x[1]);
+      v[2] = fma(-m2, v[1], fma(-l2, v[0], x[2]));
+      v[3] = fma(-n3, v[2], fma(-m3, v[1], fma(-l3, v[0], x[3])));
+    };
+    if constexpr (CHOL) {
+      forward(w);
+      La = __builtin_amdgcn_mfma_f64_16x16x4f64(group_pick(v), lcb == 4 * b + lg ? 1.0 : 0.0, La, 0,
+                                                0, 0);
+      const double qk[4] = {a00, b11, c22, q3};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) qd = lcb == 4 * b + k ? qk[k] : qd;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = blk ? (lcb == 4 * b + k ? -1.0 : 0.0) : w[k];
+    forward(w);
+    g[3] = v[3] * i3;
+    g[2] = fma(-n3, g[3], v[2] * i2);
+    g[1] = fma(-m2, g[2], fma(-m3, g[3], v[1] * i1));
+    g[0] = fma(-l1, g[1], fma(-l2, g[2], fma(-l3, g[3], v[0] * i0)));
+    const double G = group_pick(g);
+    const dbl4 a = {p[0] * mc, p[1] * mc, p[2] * mc, p[3] * mc};
+    const dbl4 o = __builtin_amdgcn_mfma_f64_16x16x4f64(-W, G, a, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = (r == b) ? G : o[r];
+  };
+  // one pivot k < 4: a_ij <- a_ij - c_i c_j / q, column and row k as above
+  auto single = [&](auto kc) {
     constexpr int k = decltype(kc)::value;
-    constexpr int rk = k >> 2;
+    if (k >= nv) return;
     double ci[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) ci[r] = row_bcast<k>(p[r]);
-    const double q = lane_bcast(p[rk], 16 * (k & 3) + k);
-    const double cj = lane_fetch(p[rk], 16 * (k & 3) + lc);
+    const double q = lane_bcast(p[0], 17 * k);
+    const double cj = lane_fetch(p[0], 16 * k + lc);
     ok = ok && (q > 0.0);
     const double iq = recip(q);
-    prod *= q;
-    if constexpr ((k & 3) == 3) {
-      ld.mul(prod);
-      prod = 1.0;
-    }
-    // opaque to the compiler, which would otherwise hold all sixteen masks in
-    // registers across the loops around the sweep (and spill)
-    int lck = lc;
-    asm volatile("" : "+v"(lck));
-    const bool jk = (lck == k), ik = (lg == (k & 3));
+    ld.mul(q);
+    const bool jk = (lc == k);
     const double gj = jk ? iq : -(cj * iq);
     const double mc = jk ? 0.0 : 1.0;
     if constexpr (CHOL) {
-      const double mk = jk ? 1.0 : 0.0;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Lk[r] = fma(p[r], mk, Lk[r]);
+      for (int r = 0; r < 4; ++r) La[r] = jk ? p[r] : La[r];
       qd = jk ? q : qd;
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) p[r] = fma(ci[r], gj, p[r] * mc);
-    p[rk] = ik ? -gj : p[rk];
+    p[0] = (lg == k) ? -gj : p[0];
   };
   if (!PART || nv >= 16) {
-    static_for<0, 16>(step);
+    static_for<0, 4>(step);
+  } else if (PART == 2 && nv < 4) {
+    // a block of four costs as much as three and a half single pivots
+    static_for<0, 3>(single);
   } else {
-    // PART, a tile with padding (a team wider than d): the steps of padded
+    // PART, a tile with padding (a team wider than d): the blocks of padded
     // pivots change no valid entry (their column is zero there), so they are
     // skipped and the padded part is set to what they would have left (unit
-    // diagonal).  Only the 16-wide teams take this path: in wider teams the
-    // second code path costs registers that the big kernels do not have.
-    auto some = [&](auto kc) {
-      if (decltype(kc)::value < nv) step(kc);
+    // diagonal).  2: with single pivots, for the 16-wide bodies (in wider ones
+    // that path costs registers).
+    auto some = [&](auto bc) {
+      if (4 * decltype(bc)::value < nv) step(bc);
     };
-    static_for<0, 16>(some);
-    ld.mul(prod);  // pivots of an unfinished group of four
+    static_for<0, 4>(some);
   }
   if constexpr (CHOL) {
     const double isq = rsqrt_nr(qd);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) Lk[r] = (4 * r + lg >= lc) ? Lk[r] * isq : 0.0;
+    for (int r = 0; r < 4; ++r) Lk[r] = (4 * r + lg >= lc) ? La[r] * isq : 0.0;
   }
   if (PART && nv < 16) {
 #pragma unroll
@@ -579,7 +660,7 @@ __device__ __forceinline__ bool wave_inv(RM<D>& A, int d, double* scr, LogDet& l
   bool ok = true;
   double p[4], dummy[4];
   tile_regs(A.t[0], p);
-  tile_sweep16<false, KT == 1>(p, d, dummy, ld, ok);
+  tile_sweep16<false, KT == 1 ? 2 : 0>(p, d, dummy, ld, ok);
   if constexpr (KT == 1) {
     A.t[0] = tile_of(p);
     const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
@@ -593,7 +674,7 @@ __device__ __forceinline__ bool wave_inv(RM<D>& A, int d, double* scr, LogDet& l
     const dbl4 Z = tile_t(X, scr);                  // X'
     const dbl4 S = A.t[3] - tile_tn(A.t[1], X, z);  // c - b' X
     tile_regs(S, p);
-    tile_sweep16<false, true>(p, d - 16, dummy, ld, ok);
+    tile_sweep16<false, 1>(p, d - 16, dummy, ld, ok);
     const dbl4 Si = tile_of(p);
     const dbl4 Wt = tile_tn(Si, Z, z);  // S^{-1} X'
     A.t[0] = tile_tn(Z, Wt, P);         // P + X S^{-1} X'
@@ -621,7 +702,7 @@ __device__ __forceinline__ bool chol32(const dbl4& a, const dbl4& b, const dbl4&
   LogDet ld;
   double p[4], Lk[4], G[4];
   tile_regs(a, p);
-  tile_sweep16<true, false>(p, d, Lk, ld, ok);
+  tile_sweep16<true, 0>(p, d, Lk, ld, ok);
   o.l0 = tile_of(Lk);
   chol_tile_rinv(p, Lk, G);
   o.g0 = tile_of(G);
@@ -629,7 +710,7 @@ __device__ __forceinline__ bool chol32(const dbl4& a, const dbl4& b, const dbl4&
   o.l10 = tile_tn(b, o.g0, z);
   const dbl4 S = c - tile_tn(o.l10t, o.l10t, z);
   tile_regs(S, p);
-  tile_sweep16<true, !INV>(p, d - 16, Lk, ld, ok);
+  tile_sweep16<true, INV ? 0 : 1>(p, d - 16, Lk, ld, ok);
   o.l1 = tile_of(Lk);
   if constexpr (INV) {
     chol_tile_rinv(p, Lk, G);
@@ -647,7 +728,7 @@ __device__ __forceinline__ bool wave_chol(const RM<D>& A, RM<D>& L, RM<D>& LT, i
     LogDet ld;
     double p[4], Lk[4];
     tile_regs(A.t[0], p);
-    tile_sweep16<true, true>(p, d, Lk, ld, ok);
+    tile_sweep16<true, 2>(p, d, Lk, ld, ok);
     L.t[0] = tile_of(Lk);
   } else {
     const dbl4 z = {0.0, 0.0, 0.0, 0.0};
@@ -813,7 +894,7 @@ __device__ bool chol_reg(RM<D>& A, int d, double* scr) {
     LogDet ld;
     double p[4], Lk[4];
     tile_regs(A.t[0], p);
-    tile_sweep16<true, true>(p, d, Lk, ld, ok);
+    tile_sweep16<true, 2>(p, d, Lk, ld, ok);
     A.t[0] = tile_of(Lk);
   } else if constexpr (D == 32) {
     Chol32 c;
