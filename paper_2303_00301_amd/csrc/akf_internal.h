@@ -10,11 +10,12 @@ enum { EMIT_GAUSSIAN = 0, EMIT_POISSON_LOG = 1, EMIT_STUDENT_T = 2, EMIT_STOCH_V
 enum { DYN_LINEAR = 0, DYN_LORENZ63 = 1, DYN_LORENZ96 = 2 };
 enum { ST_FWD_NOT_PD = 1, ST_REV_NOT_PD = 2, ST_NONFINITE = 4 };
 
-// time steps (one wave each) per workgroup of the multivariate-t linearisation
+// time steps (columns of a matrix product) per workgroup of the multivariate-t
+// linearisation
 constexpr int kMvtSteps = 4;
-// time steps per workgroup of the Gaussian-emission linearisation (four waves,
-// each taking every fourth of them)
-constexpr int kGaussStepsPerBlock = 16;
+// workgroups (and partial sums) of the Gaussian linearisation: four time steps
+// each, a wave per step, as long as that is few enough to be summed at once
+inline int gauss_parts(int N) { return N < 4096 ? (N + 3) / 4 : 1024; }
 
 // Device-side gate of a launch: the kernel runs iff w == nullptr or
 // lo <= *w <= hi; every workgroup reads the word at entry and leaves at once

@@ -69,7 +69,7 @@ void make_layout(Layout& Lo, int N, int d, int dy, int block, int kind, bool dyn
     return o;
   };
   const int nparts_diag = (int)(((int64_t)N * d + 255) / 256);
-  const int nparts_gauss = (N + kGaussStepsPerBlock - 1) / kGaussStepsPerBlock;
+  const int nparts_gauss = gauss_parts(N);
   const int nparts_mvt = (N + kMvtSteps - 1) / kMvtSteps;
   Lo.n_part = nparts_diag > nparts_gauss ? nparts_diag : nparts_gauss;
   if (nparts_mvt > Lo.n_part) Lo.n_part = nparts_mvt;

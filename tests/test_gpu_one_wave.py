@@ -148,3 +148,25 @@ def test_width_64(S, d, N, block):
 @pytest.mark.parametrize("d,N", [(33, 515), (49, 600), (64, 1025)])
 def test_width_64_one_wave_build(S, d, N):
     test_filter_and_sampler(S, d, N, 0)
+
+
+# Gaussian linearisation: columns in registers at the widths of the two register
+# forms and past them, one step, a partial workgroup, more steps than waves
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("N,d,dy", [(1, 1, 1), (3, 16, 16), (5, 5, 17), (6, 32, 32), (5, 33, 4),
+                                    (5, 4, 40), (4099, 2, 1)])
+def test_gaussian_linearisation(S, N, d, dy, order):
+    rng = np.random.default_rng(N + 10 * d + dy)
+    m0, P0, F, b, Q = _model(rng, d)
+    H, R = rng.standard_normal((dy, d)) / np.sqrt(d), 0.5 * np.eye(dy) + 0.1 * np.ones((dy, dy))
+    y, x = rng.standard_normal((N, dy)), rng.standard_normal((N, d))
+    xi = rng.standard_normal((2, N, d))
+    kw = dict(m0=m0, P0=P0, F=F, Q=Q, b=b, H=H, R=R)
+    r = oracle.mh_step(oracle.Model(emit=W.EMIT_GAUSSIAN, **kw), y, x, 0.5, order, xi[0], xi[1],
+                       1e-300)
+    M = S.DeviceModel.from_arrays(N, emit=S.EMIT_GAUSSIAN, **kw)
+    out = S.mh_step(M, T(y), T(x), 0.5, order, T(xi), T([1e-300]))
+    assert int(out["status"][0]) == 0 and int(out["accepted"][0]) == r["accepted"]
+    assert _rel(N_(out["logZ_fwd"])[0], r["logZ_fwd"]) < TOL
+    assert _rel(N_(out["logZ_rev"])[0], r["logZ_rev"]) < TOL
+    assert _rel(N_(out["x_out"]), r["x_out"]) < TOL
