@@ -134,7 +134,7 @@ def auto_block(N: int, d: int) -> int:
     D = 16 if d <= 16 else (32 if d <= 32 else 64)
     teams = 1 if D == 64 else (4 if D == 32 else 8)
     target = 256 * teams
-    B = max(4, (N + target - 1) // target)
+    B = max(2 if D > 16 and N <= 512 else 4, (N + target - 1) // target)
     return min(B, N)
 
 

@@ -31,12 +31,18 @@ int pick_D(int d) { return d <= 16 ? 16 : (d <= 32 ? 32 : (d <= 64 ? 64 : 0)); }
 // and no more, so that the fold runs in one round (register-limited: 1 team of
 // 4 waves at D = 64, four single-wave teams at D = 32, eight at D = 16), and at
 // least 4 steps per block so that small problems do not pay for a deep tree of
-// tiny launches.
+// tiny launches.  Above D = 16 a fold step costs more than half a tree level,
+// so blocks of 2 are the better ones while all of them run at once (two steps
+// of order 2, blocks of 4 / 2: stochastic volatility, d = 30, N = 250: 855 /
+// 824 us, N = 512: 949 / 942, N = 1000: 1063 / 1112; latent field, d = 64,
+// N = 512: 2567 / 2526, N = 1024: 2884 / 4124; d = 8: 295 / 291 at N = 250,
+// 350 / 373 at 1024).
 int auto_block(int N, int D) {
   const int teams_per_cu = D == 64 ? 1 : (D == 32 ? 4 : 8);
   const int target = 256 * teams_per_cu;
+  const int least = D > 16 && N <= 2 * 256 ? 2 : 4;
   int B = (N + target - 1) / target;
-  if (B < 4) B = 4;
+  if (B < least) B = least;
   if (B > N) B = N;
   return B;
 }
