@@ -1678,9 +1678,9 @@ __global__ void __launch_bounds__(64) k_samp_final(KModel M, SampArgs S) {
 }
 
 // One chain, D <= 32: the scan over the aggregates (one launch per level of
-// more than kPathRadix nodes) and the final pass that starts from it.
+// more than kPathChain nodes) and the final pass that starts from it.
 template <int D>
-__global__ void __launch_bounds__(64 * kPathRadix) k_path_scan(KModel M, double* agg, int n,
+__global__ void __launch_bounds__(64 * kPathRadix<D>) k_path_scan(KModel M, double* agg, int n,
                                                                int64_t str) {
   if (gate_shut(M.gate)) return;
   path_scan<D>(agg, n, str, blockIdx.x);
@@ -1968,10 +1968,11 @@ hipError_t launch_samp_scan(const KModel& M, SampArgs S, TreeArgs* lv_up, TreeAr
   if constexpr (D <= 32) {
     const double* root = n_levels > 0 ? lv_down[n_levels - 1].pre_src : S.xin;
     int64_t str = 1;
-    for (int n = nb; n > kPathRadix; n = (n + kPathRadix - 1) / kPathRadix, str *= kPathRadix) {
+    for (int n = nb; n > kPathChain;
+         n = (n + kPathRadix<D> - 1) / kPathRadix<D>, str *= kPathRadix<D>) {
       timing_mark(FAM_SAMP_UP, 1, st);
-      hipLaunchKernelGGL(k_path_scan<D>, dim3((n + kPathRadix - 1) / kPathRadix),
-                         dim3(64 * kPathRadix), path_scan_lds_bytes<D>(), st, M, S.agg, n, str);
+      hipLaunchKernelGGL(k_path_scan<D>, dim3((n + kPathRadix<D> - 1) / kPathRadix<D>),
+                         dim3(64 * kPathRadix<D>), path_scan_lds_bytes<D>(), st, M, S.agg, n, str);
       timing_mark(FAM_SAMP_UP, 0, st);
     }
     timing_mark(FAM_SAMP_FINAL, 1, st);

@@ -676,9 +676,9 @@ __device__ __forceinline__ void wave_sbuild(const KModel& M, const SampArgs& S, 
 // Sampler, element build at D = 64 by one wave (the formulas of wave_sbuild).
 // A step's factorisations are serial chains that a team's waves repeat or wait
 // for, and its products are bound by the matrix cores either way; one step to
-// a wave, four to a CU, leaves the chains of four steps to overlap: 180k
-// cycles for four steps, 103k of them on the matrix cores, against 170k for
-// two by teams of four waves.  The 16
+// a wave, four to a CU, leaves the chains of four steps to overlap: 163k
+// cycles for four steps, 112k of them on the matrix cores, against 170k for
+// two by teams of four waves (573 -> 306 us at d = 64, N = 4096).  The 16
 // tiles of a 64 x 64 matrix take 128 of the lone wave's 512 registers, so two
 // matrices and a symmetric one are held at a time, and F, then G, lives in the
 // wave's own LDS (leading dimension 65), read tile by tile transposed in the
@@ -1012,11 +1012,16 @@ __device__ __forceinline__ void w64_sbuild(const KModel& M, const SampArgs& S, i
 // launch per level up and one down (16 launches of 2.3 - 3.4 us at 256 blocks
 // of width 16).
 // ---------------------------------------------------------------------------
-constexpr int kPathRadix = 16;
+// Eight at D = 32, where 16 waves on four SIMDs would wait for the matrix cores
+// (125 blocks: 10.2 us for the scan against 21.7).  A level of at most kPathChain
+// nodes is not scanned: the chain goes through its nodes.
+template <int D>
+constexpr int kPathRadix = D == 16 ? 16 : 8;
+constexpr int kPathChain = 16;
 
 template <int D>
 constexpr size_t path_scan_lds_bytes() {
-  return (size_t)kPathRadix * (Cfg<D>::MAT + D) * sizeof(double);
+  return (size_t)kPathRadix<D> * (Cfg<D>::MAT + D) * sizeof(double);
 }
 
 // Node j of the level (an aggregate, str apart) becomes node j o ... o the
@@ -1029,10 +1034,10 @@ __device__ __forceinline__ void path_scan(double* agg, int n, int64_t str, int g
   constexpr int SLOT = Cfg<D>::MAT + D;
   const int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int cnt = min(kPathRadix, n - group * kPathRadix);
+  const int cnt = min(kPathRadix<D>, n - group * kPathRadix<D>);
   const bool on = w < cnt;
   double* my = lds + w * SLOT;
-  double* el = agg + (int64_t)(group * kPathRadix + w) * str * SL::SIZE;
+  double* el = agg + (int64_t)(group * kPathRadix<D> + w) * str * SL::SIZE;
   RM<D> ET;  // the node's E transposed: x' y of a right neighbour's E with it is (E E_r)'
   double u = 0.0;
   if (on) {
@@ -1045,7 +1050,7 @@ __device__ __forceinline__ void path_scan(double* agg, int n, int64_t str, int g
     AKF_RM_FOR(D, q, r, i, j) ET.t[q][r] = my[j * Cfg<D>::LD + i];
   }
 #pragma unroll 1
-  for (int s = 1; s < kPathRadix; s <<= 1) {
+  for (int s = 1; s < kPathRadix<D>; s <<= 1) {
     __syncthreads();
     const bool go = w + s < cnt;
     RM<D> c;
@@ -1109,7 +1114,7 @@ __device__ __forceinline__ double path_apply(const PathRow<D>& R, double x, doub
 }
 
 // x* just after block k, from the state `root` after the last block and the n
-// scanned aggregates (path_scan on every level of more than kPathRadix nodes)
+// scanned aggregates (path_scan on every level of more than kPathChain nodes)
 template <int D>
 __device__ __forceinline__ double path_entry(const double* agg, int n, const double* root, int k,
                                              double* vx) {
@@ -1120,9 +1125,9 @@ __device__ __forceinline__ double path_entry(const double* agg, int n, const dou
   };
   int64_t str = 1;
   int top = n;
-  while (top > kPathRadix) {
-    top = (top + kPathRadix - 1) / kPathRadix;
-    str *= kPathRadix;
+  while (top > kPathChain) {
+    top = (top + kPathRadix<D> - 1) / kPathRadix<D>;
+    str *= kPathRadix<D>;
   }
   double x = root[threadIdx.x % D];
   const int jt = (int)(k / str);
@@ -1135,9 +1140,9 @@ __device__ __forceinline__ double path_entry(const double* agg, int n, const dou
     }
   }
   while (str > 1) {
-    str /= kPathRadix;
+    str /= kPathRadix<D>;
     const int64_t j = k / str + 1, nl = (n + str - 1) / str;
-    if (j % kPathRadix != 0 && j < nl) x = path_apply<D>(row(j * str), x, vx);
+    if (j % kPathRadix<D> != 0 && j < nl) x = path_apply<D>(row(j * str), x, vx);
   }
   return x;
 }

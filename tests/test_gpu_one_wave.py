@@ -170,3 +170,10 @@ def test_gaussian_linearisation(S, N, d, dy, order):
     assert _rel(N_(out["logZ_fwd"])[0], r["logZ_fwd"]) < TOL
     assert _rel(N_(out["logZ_rev"])[0], r["logZ_rev"]) < TOL
     assert _rel(N_(out["x_out"]), r["x_out"]) < TOL
+
+
+# width 32: groups of eight blocks, and a last level of at most sixteen nodes
+# that is chained instead of scanned
+@pytest.mark.parametrize("N", [8, 16, 17, 128, 129])
+def test_path_scan_levels_32(S, N):
+    test_path_scan_levels(S, N, 17, 1)
