@@ -51,7 +51,16 @@ akf_status akf_mh_step_noalloc(const akf_model* model, const double* y, const do
                                double* logZ_fwd, double* logZ_rev, int32_t* status, int32_t block,
                                void* stream) {
   // size check first: an invalid model sizes to 0 and akf_mh_step reports why
-  const size_t need = akf_mh_workspace_bytes(model, order, block);
+  size_t need = akf_mh_workspace_bytes(model, order, block);
+  // the default's blocks of two steps hold twice the elements of blocks of four:
+  // a problem that fits with those alone takes them
+  if (block <= 0 && need > (size_t)AKF_NOALLOC_SCRATCH_BYTES) {
+    const size_t need4 = akf_mh_workspace_bytes(model, order, 4);
+    if (need4 <= (size_t)AKF_NOALLOC_SCRATCH_BYTES) {
+      need = need4;
+      block = 4;
+    }
+  }
   if (need > (size_t)AKF_NOALLOC_SCRATCH_BYTES)
     return akf::fail(AKF_ERR_SHAPE, "akf_mh_step_noalloc: this problem needs %zu bytes of scratch "
                      "memory, more than the %zu bytes the library holds per device; use "

@@ -143,7 +143,7 @@ def test_width_64(S, d, N, block):
     test_filter_and_sampler(S, d, N, block)
 
 
-# width 64, more steps than resident teams: the sampler's elements are built by
+# width 64, more steps than compute units: the sampler's elements are built by
 # one wave per step
 @pytest.mark.parametrize("d,N", [(33, 515), (49, 600), (64, 1025)])
 def test_width_64_one_wave_build(S, d, N):
@@ -177,3 +177,23 @@ def test_gaussian_linearisation(S, N, d, dy, order):
 @pytest.mark.parametrize("N", [8, 16, 17, 128, 129])
 def test_path_scan_levels_32(S, N):
     test_path_scan_levels(S, N, 17, 1)
+
+
+def test_noalloc_default_blocks_at_the_scratch_limit(S):
+    """d = 64, N = 300: the default's blocks of two steps need more than the fixed
+    scratch array, blocks of four fit it and are taken."""
+    w = W.latent_field(N=300, d=64, n_sites=32)
+    M = S.DeviceModel.from_workload(w)
+    args = (M, T(w.y), T(w.x_true), w.delta, w.order, T(w.normals(1)[0]), T(w.uniforms(1)[:1]))
+    ref = S.mh_step(*args, block=4)
+    f, i = dict(dtype=torch.float64, device="cuda"), dict(dtype=torch.int32, device="cuda")
+    new = lambda: (torch.empty_like(args[2]), torch.empty(1, **f), torch.empty(1, **i),
+                   torch.empty(1, **f), torch.empty(1, **f), torch.empty(1, **i))
+    out = new()
+    S.mh_step_noalloc(*args, *out)
+    torch.cuda.synchronize()
+    assert int(out[5][0]) == 0 and int(out[2][0]) == int(ref["accepted"][0])
+    assert _rel(N_(out[0]), N_(ref["x_out"])) < 1e-12
+    assert _rel(N_(out[3]), N_(ref["logZ_fwd"])) < 1e-12
+    with pytest.raises(RuntimeError):
+        S.mh_step_noalloc(*args, *new(), block=2)
