@@ -747,7 +747,7 @@ __device__ __forceinline__ void vec_load(double* s, const double* __restrict__ g
 // N(A x_{s-1} + b, C) and p(omega_{s:t} | x_{s-1}) ~ exp(-x'Jx/2 + eta'x).
 // Appending step t (predict through the dynamics, condition on omega_t):
 //   Pp = F C F' + Q, T = F A, mu = F b + bias,  S = Pp + Omega_t (inverted in
-//   registers by Gauss-Jordan), w = omega_t - mu
+//   registers), w = omega_t - mu
 //   C <- Pp - Pp S^{-1} Pp,  A <- T - Pp S^{-1} T,  J <- J + T' S^{-1} T,
 //   b <- mu + Pp S^{-1} w,   eta <- eta + T' S^{-1} w
 // which is the element combine of App. A with the raw element of step t
@@ -755,6 +755,9 @@ __device__ __forceinline__ void vec_load(double* s, const double* __restrict__ g
 // from the prior (A = 0 throughout).  Output element layout: ElemLayout.
 // Below D = 64 a team is one wave and runs wave_fold, which also takes general
 // observations y_t = H x_t + N(0, R).
+// Bound by the chain of a lone team's products (4.1k cycles each on the matrix
+// cores) and pivot tiles: d = 64, N = 4096 in 256 blocks 432 us, 512 with the
+// inverse by four panels, products unrolled eight deep and none skipped.
 // ---------------------------------------------------------------------------
 // FIRST: the block contains t = 0 (its element has A = 0 and J = 0).  The
 // two cases are compiled separately so that A and T hold no registers across
@@ -956,7 +959,7 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_fold(KModel M, FilterArgs
 // ---------------------------------------------------------------------------
 // Filter, phase 2 up-sweep: node k of a level = left (earlier) (x) right.
 // With C_i = L L' (register Cholesky), W = I + L' J_j L (SPD, eigenvalues
-// >= 1, inverted by Gauss-Jordan) and M = L W^{-1} L' = (I + C_i J_j)^{-1} C_i:
+// >= 1) and M = L W^{-1} L' = (I + C_i J_j)^{-1} C_i:
 //   A   = A_j (A_i - M J_j A_i)
 //   b   = A_j (b_i + M c) + b_j,             c = eta_j - J_j b_i
 //   C   = A_j M A_j' + C_j
@@ -973,6 +976,11 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_fold(KModel M, FilterArgs
 // their products) and then one side of the outputs: SIDE 1 the J side (J,
 // eta, A: four products after M), SIDE 2 the C side (C, b and lc: two), so a
 // level waits for the prefix and four products instead of eight.
+// A level is bound by one combine's chain, two factorisations and eight
+// products, however many combines it holds; us a level of whole elements / of
+// sides: d = 64 58 / 48 (66 / 55 with panel factorisations and LDS sums),
+// d = 30 20 / 17 and d = 8 6.6 / 5.5 (29 / 26 and 9.8 / 8.7 with operands staged
+// through LDS and pivots swept one by one).
 template <int D, int U = 4, int G = D * D / Cfg<D>::NT, int SIDE = 0>
 __device__ __forceinline__ void filter_combine(const KModel& M, const double* __restrict__ ei,
                                                const double* __restrict__ ej,
@@ -1280,6 +1288,8 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_down(KModel M, TreeArgs T
 // (sequential Kalman filter, App. A "Kalman filter"), with the predictive-
 // form likelihood term ell_t = log N(omega_t; m^p_t, P^p_t + Omega_t).
 // Writes m^f_t, P^f_t (when requested) and ell_t.
+// Bound like the fold: d = 64, N = 4096 338 us, 395 before the block
+// factorisations and half-exchange sums.
 // ---------------------------------------------------------------------------
 template <int D, int OBS, int U = 4>
 __device__ __forceinline__ void filter_final_impl(const KModel& M, const FilterArgs& P, int item) {
@@ -1416,7 +1426,7 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_final(KModel M, FilterArg
 
 // ---------------------------------------------------------------------------
 // Sampler, element build (eq. backward, Alg. "Parallel RTS sampler"), one team
-// per t:  G = F P^f,  P^p = G F' + Q (inverted by Gauss-Jordan),
+// per t:  G = F P^f,  P^p = G F' + Q (inverted in registers),
 //   E_t = G' (P^p)^{-1} = P^f F' (P^p)^{-1},   L_t = P^f - E_t G,
 //   g_t = m^f - E_t (F m^f + bias),            U_t = g_t + chol(L_t) xi_t.
 // Terminal step: E = 0, U = m^f + chol(P^f) xi.
@@ -2002,11 +2012,11 @@ template <int D>
 hipError_t launch_sampler(const KModel& M, SampArgs S, TreeArgs* lv_up, TreeArgs* lv_down,
                           int n_levels, hipStream_t st) {
   timing_mark(FAM_SAMP_BUILD, 1, st);
-  // D = 64: a step takes a lone wave 77 us and a team 50 - 56 us alone on a CU,
-  // 77 - 83 with another; once the steps outnumber the resident teams, two to
-  // a CU, the waves win (d = 64, N = 256: 77 against 56 us, 512: 81 / 83,
-  // 768: 87 / 127, 1024: 92 / 159)
-  if (D == 64 && M.N > 2 * compute_units())
+  // D = 64: a step takes a lone wave 69 - 78 us and a team 47 - 54 us alone on a
+  // CU, 78 - 84 with another; once the steps outnumber the CUs the waves win
+  // (d = 64, waves / teams: N = 256 73 / 54 us, 300 75 / 78, 512 78 / 84,
+  // 768 83 / 124, 1024 88 / 156)
+  if (D == 64 && M.N > compute_units())
     hipLaunchKernelGGL(k_samp_build_w64, dim3(M.N), dim3(64), W64::LDS * sizeof(double), st, M, S);
   else
     hipLaunchKernelGGL(k_samp_build<D>, dim3(M.N), dim3(Cfg<D>::NT), lds_bytes_samp_build<D>(), st,

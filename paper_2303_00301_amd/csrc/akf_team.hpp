@@ -450,7 +450,7 @@ __device__ __forceinline__ double group_pick(const double v[4]) {
 // L^{-1} W, transposed into place by a second MFMA off the chain, and scaled by
 // 1/sqrt(pivot) at the end, one square root for all sixteen.  Bound by the
 // issue of about 110 vector instructions a block and the MFMA's latency:
-// 2.4k cycles a tile, with CHOL 2.9k; sixteen single pivots, each a lane
+// 2.4k cycles a tile, with CHOL 2.6k; sixteen single pivots, each a lane
 // permute (58 cycles), a scaling and an update in a chain, took 3.0k and 3.8k.
 // Indices >= nv are padding: they get a unit diagonal.  A non-positive pivot
 // clears ok (the results are then unspecified).
@@ -755,11 +755,12 @@ __device__ __forceinline__ bool wave_chol(const RM<D>& A, RM<D>& L, RM<D>& LT, i
 // matrix is split into 32 x 32 blocks [[a, b], [b', c]] and the four waves go
 // through the formulas of wave_inv / chol32 one level up: the 32 x 32 blocks
 // are factored by every wave for itself (from LDS, so nothing is broadcast),
-// and each wave forms one tile of every 32 x 32 product: 21.9k cycles for the
-// inverse and 25.9k for the factor of a 64 x 64 matrix, four pivot tiles of 3.2k
-// each in them.  Four panels of the whole matrix, each with its pivot tile, its
-// block row through LDS and a third of the tiles' updates behind uniform
-// branches, took 27.7k and 34.9k.
+// and each wave forms one tile of every 32 x 32 product: 19.9k cycles for the
+// inverse and 23.3k for the factor of a 64 x 64 matrix, four pivot tiles of
+// 2.4k (with the factor 2.6k) in each.  Four panels of the whole matrix, each
+// with its pivot tile, its block row through LDS and a third of the tiles'
+// updates behind uniform branches, took 27.7k and 34.9k with tiles of 3.0k and
+// 3.8k.
 // ---------------------------------------------------------------------------
 // doubles of LDS scratch
 template <int D>

@@ -12,7 +12,10 @@
 // team is a few KB, and the registers alone decide how many waves share a
 // SIMD.  With operands staged through LDS instead (a store, a wait and two
 // loads around each product) a fold step of a lone wave took 10.8k cycles at
-// D = 16 and 38k at D = 32.
+// D = 16 and 38k at D = 32.  Bound by the chain of products (256 cycles a tile)
+// and pivot tiles of a lone wave, or by the registers' one or two waves a SIMD:
+// fold of d = 8, N = 1024 20 -> 12.6 us; 128 ragged chains of up to 8192 steps,
+// D = 32: fold 3.05 -> 1.90 ms, re-scan 2.45 -> 1.21, element build 3.4 -> 2.2.
 #pragma once
 #include "akf_internal.h"
 #include "akf_team.hpp"
