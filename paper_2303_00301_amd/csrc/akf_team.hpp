@@ -356,9 +356,9 @@ __device__ __forceinline__ void tile_regs(const dbl4& t, double x[4]) {
 struct LogDet {
   double m = 1.0;
   int e = 0;
-  __device__ __forceinline__ void mul(double x) {
+  __device__ __forceinline__ void mul(double x, double y = 1.0) {  // 1/2 <= m < 1: m x is in range with x
     int ex;
-    m = frexp(m * x, &ex);
+    m = frexp((m * x) * y, &ex);
     e += ex;
   }
   __device__ __forceinline__ double value() const { return log(m) + e * 0.69314718055994530942; }
@@ -487,7 +487,9 @@ __device__ __forceinline__ void tile_sweep16(double p[4], int nv, double Lk[4], 
     const double q3 = fma(-n3, c23, c33);
     const double i3 = recip(q3);
     ok = ok && (a00 > 0.0) && (b11 > 0.0) && (c22 > 0.0) && (q3 > 0.0);
-    ld.mul((a00 * b11) * (c22 * q3));
+    // in pivot order, as single pivots are taken: two large pivots multiplied with
+    // each other first would overflow where the four together do not
+    ld.mul((a00 * b11) * c22, q3);
     // opaque to the compiler, which would otherwise hold the lane masks in
     // registers across the loops around the sweep (and spill)
     int lcb = lc;
