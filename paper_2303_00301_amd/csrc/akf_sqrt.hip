@@ -297,7 +297,8 @@ __device__ __forceinline__ double dot(const T* x, const T* y, int d, double* red
   return team_sum(v, red);
 }
 
-// d = sqrt(p) and r = 1 / d, correctly rounded (zero for p <= 0), for finite p:
+// d = sqrt(p) and r = 1 / d, correctly rounded (zero for p <= 0; infinity and
+// zero for a pivot that overflowed):
 // scaled by a power of four into [1/4, 1), Goldschmidt's iteration from the
 // hardware estimates with Markstein's final corrections.  Half the length of
 // the library's square root followed by its division, and no branch, so that
@@ -316,8 +317,9 @@ __device__ __forceinline__ void sqrt_and_rcp(double p, double& d, double& r) {
   y = fma(fma(-s, y, 1.0), y, y);
   y = fma(fma(-s, y, 1.0), y, y);
   y = fma(fma(-s, y, 1.0), y, y);
-  d = (p > 0.0) ? ldexp(s, e >> 1) : 0.0;
-  r = (p > 0.0) ? ldexp(y, -(e >> 1)) : 0.0;
+  const bool fin = p < INFINITY;
+  d = (p > 0.0) ? (fin ? ldexp(s, e >> 1) : p) : 0.0;
+  r = (p > 0.0 && fin) ? ldexp(y, -(e >> 1)) : 0.0;
 }
 
 // ---------------------------------------------------------------------------

@@ -30,3 +30,25 @@ def test_log_det_of_pivots_far_apart(S, d):
     assert int(st[0]) == 0
     # a sum of d terms: half an ulp of its largest partial sum for each
     assert abs(float(ell[0]) + 0.5 * terms.sum()) < d * 2.0 ** -52 * np.abs(terms).sum()
+
+
+@pytest.mark.parametrize("d", [1, 17])
+def test_square_root_pivot_overflow(S, d):
+    """A pivot P + Omega past the largest number is infinite: the gain of that
+    coordinate is zero, so its moments are the prior's, and its density is zero.
+    The other coordinates do not see it (the square-root filter has one mantissa
+    per coordinate of a diagonal model)."""
+    P0, Om = np.full(d, 2.0), np.full(d, 0.5)
+    P0[0], Om[0] = 1.2e308, 1.2e308
+    om = np.arange(1.0, d + 1.0)
+    M = S.DeviceModel.from_arrays(1, np.zeros(d), np.diag(P0), 0.5 * np.eye(d), np.eye(d), 1)
+    o = S.sqrt_filter_sample(M, T(om[None]), T(Om[None]), dtype="f64")
+    assert int(o["status"][0]) == 0
+    gain = P0 / (P0 + Om)
+    gain[0] = 0.0
+    U = np.sqrt(P0 * Om / (P0 + Om))
+    U[0] = np.sqrt(P0[0])
+    # a handful of roundings on each diagonal element
+    np.testing.assert_allclose(o["mf"].cpu().numpy()[0], gain * om, rtol=1e-14, atol=0.0)
+    np.testing.assert_allclose(o["Uf"].cpu().numpy()[0], np.diag(U), rtol=1e-14, atol=0.0)
+    assert float(o["ell"][0]) == -np.inf
