@@ -214,7 +214,8 @@ __device__ __forceinline__ T group_bcast(T v) {
 // a group of NT / D lanes that holds it in registers, lane r owning the rows
 // r + m NT / D; x_i is formed by its owner, broadcast across the group, and
 // every lane updates its remaining rows.  Bound by that chain (a division and
-// a broadcast a row); with X updated in LDS a row took 350 cycles.
+// a broadcast a row); with X updated in LDS a row took 350 cycles.  Rows go eight
+// to a branch; fewer than four in all go one by one (d = 1, T = 20: 127 -> 117 us).
 // UP = false: X <- L^{-1} X (forward); UP = true: X <- L^{-T} X (backward).
 // Returns false on a non-positive pivot.
 template <class T, int D, bool UP>
@@ -253,7 +254,14 @@ __device__ __forceinline__ bool solve_t(T* X, int rs, int cs, const T* L, int nc
       static_for<0, 8>(one);
     }
   };
-  static_for<0, D / 8>(rows8);
+  auto each = [&](auto ic) {  // rows 2, 1, 0 or 0, 1, 2
+    constexpr int i = UP ? D - 3 + decltype(ic)::value : decltype(ic)::value;
+    if ((UP ? D - 1 - i : i) < d) row(std::integral_constant<int, i>{});
+  };
+  if (d < 4)
+    static_for<0, 3>(each);
+  else
+    static_for<0, D / 8>(rows8);
   if (on) {
 #pragma unroll
     for (int m = 0; m < RP; ++m) {
@@ -345,7 +353,9 @@ __device__ __forceinline__ void sqrt_and_rcp(double p, double& d, double& r) {
 // the same order.  Bound by the panels' chain pivot - square root -
 // reciprocal - update (about 400 cycles a column): 60 x 60 in 40k cycles.  With
 // the trailing matrix updated in LDS by all threads, two barriers a column, a
-// filter and sample at d = 30, T = 250 took 2.07 ms, now 0.81.
+// filter and sample at d = 30, T = 250 took 2.07 ms, now 0.77; at d = 1, T = 20,
+// where one panel holds all, 123 us, now 117 (183 with sixteen columns
+// eliminated, of which two are not padding).
 // ---------------------------------------------------------------------------
 template <int D>
 __device__ __forceinline__ void tria(double* W, int r, int c, double* dv) {
@@ -427,20 +437,34 @@ __device__ __forceinline__ void tria(double* W, int r, int c, double* dv) {
       // the next pivot's column is updated first, by lane reads; the others take
       // their multipliers from LDS while its square root and reciprocal are formed
       double pv = lane_bcast(p[0], c0);
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
+      auto column = [&](auto kc) {
+        constexpr int k = decltype(kc)::value;
         double dk, inv;
         sqrt_and_rcp(pv, dk, inv);
         const double lk = (l == c0 + k) ? dk : p[k] * inv;
         if (l < r && c0 + k < r && l >= c0 + k) W[l * LW + c0 + k] = lk;
-        if (k < 15) {
+        if constexpr (k < 15) {
           p[k + 1] = fma(-lk, lane_bcast(lk, c0 + k + 1), p[k + 1]);
           pv = lane_bcast(p[k + 1], c0 + k + 1);
         }
         wave_lds_fence();
 #pragma unroll
         for (int j = k + 2; j < 16; ++j) p[j] = fma(-lk, W[(c0 + j) * LW + c0 + k], p[j]);
-      }
+      };
+      // padded columns of a last panel are left out, four at a time; fewer than
+      // four in all are taken one by one
+      auto columns = [&](auto gc) {
+        constexpr int g = decltype(gc)::value;
+        auto one = [&](auto ic) { column(std::integral_constant<int, 4 * g + decltype(ic)::value>{}); };
+        if (c0 + 4 * g < r) static_for<0, 4>(one);
+      };
+      auto each = [&](auto kc) {
+        if (decltype(kc)::value < r) column(kc);
+      };
+      if (r < 4)
+        static_for<0, 3>(each);
+      else
+        static_for<0, 4>(columns);
     }
     __syncthreads();
     const int m = nt - 1 - kb;  // trailing tile rows
