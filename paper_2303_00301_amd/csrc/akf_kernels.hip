@@ -2012,11 +2012,14 @@ template <int D>
 hipError_t launch_sampler(const KModel& M, SampArgs S, TreeArgs* lv_up, TreeArgs* lv_down,
                           int n_levels, hipStream_t st) {
   timing_mark(FAM_SAMP_BUILD, 1, st);
-  // D = 64: a step takes a lone wave 69 - 78 us and a team 47 - 54 us alone on a
-  // CU, 78 - 84 with another; once the steps outnumber the CUs the waves win
-  // (d = 64, waves / teams: N = 256 73 / 54 us, 300 75 / 78, 512 78 / 84,
-  // 768 83 / 124, 1024 88 / 156)
-  if (D == 64 && M.N > compute_units())
+  // D = 64: a transition takes a lone wave 69 - 78 us and a team 47 - 54 us alone
+  // on a CU, 78 - 84 with another, 124 with two (the terminal step has none).  So
+  // teams win while they have a CU each, and up to two a CU where the last tile
+  // row is padding (build, scan and path, teams / waves: d = 64, N = 257 150 /
+  // 171 us, 258 172 / 171, 512 179 / 176, 514 225 / 185; d = 48, N = 257 147 /
+  // 168, 258 166 / 167, 512 174 / 175, 514 215 / 183; d = 33, N = 512 174 / 176)
+  const int team_slots = (M.d > 48 ? 1 : 2) * compute_units();
+  if (D == 64 && M.N - 1 > team_slots)
     hipLaunchKernelGGL(k_samp_build_w64, dim3(M.N), dim3(64), W64::LDS * sizeof(double), st, M, S);
   else
     hipLaunchKernelGGL(k_samp_build<D>, dim3(M.N), dim3(Cfg<D>::NT), lds_bytes_samp_build<D>(), st,

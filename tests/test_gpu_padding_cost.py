@@ -58,3 +58,20 @@ def test_square_root_cost_of_one_coordinate(S):
         return _us(lambda: S.sqrt_filter_sample(M, om, Om, xi))
     one, eight = run(1), run(8)
     assert one < 0.8 * eight, (one, eight)
+
+
+def test_sampler_build_while_every_step_has_a_cu(S):
+    """Width 64, as many transitions as compute units (the last step has none):
+    one team per CU, not the slower wave per step (150 us against 171)."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def run(N, d=64):
+        rng = np.random.default_rng(N)
+        m0, P0, F, b, Q = _model(rng, d, 1e1)
+        M = S.DeviceModel.from_arrays(N, m0, P0, F, Q, 1, b=b)
+        om, Om = T(rng.standard_normal((N, d))), T(rng.uniform(0.1, 1.0, (N, d)))
+        mf, Pf, _, _ = S.aux_filter(M, om, Om)
+        xi = T(rng.standard_normal((N, d)))
+        return _us(lambda: S.rts_sample(M, mf, Pf, xi))
+    fits, more = run(n_cu + 1), run(n_cu + 44)
+    assert fits < 0.94 * more, (fits, more)
