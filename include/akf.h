@@ -506,7 +506,9 @@ typedef struct akf_batch_plan akf_batch_plan;
  * block = 0 autotunes: each candidate block size is timed on one step of the
  * real batch (on scratch copies of x; no state changes), and the choice is
  * appended to the text cache `tune_cache` (one JSON object per line; NULL =
- * no cache) and reused when the same group shape is seen again.
+ * no cache) and reused when the same group shape is seen again by the same
+ * build of the kernels (a line names the digest of its kernels' sources; lines
+ * of other builds are passed over).
  */
 akf_status akf_batch_plan_create(akf_batch_plan** plan, int32_t n_chains, const akf_chain* chains,
                                  int32_t n_steps, int32_t block, const char* tune_cache,

@@ -1,6 +1,7 @@
 """Build libauxkf.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
 from __future__ import annotations
 
+import hashlib
 import os
 import subprocess
 import sys
@@ -23,16 +24,28 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          "-Wall", "-Wno-unused-function", "-Wno-unused-variable"]
 
 
+def kernel_id() -> str:
+    """Digest of the library's sources and compiler flags: the identity under
+    which the batch planner stores what it measured."""
+    h = hashlib.sha256("\0".join(FLAGS).encode())
+    for f in sorted(os.listdir(CSRC)):
+        if f.endswith((".hip", ".hpp", ".h", ".cpp")):
+            with open(os.path.join(CSRC, f), "rb") as src:
+                h.update(b"\0" + f.encode() + b"\0" + src.read())
+    return h.hexdigest()[:16]
+
+
 def build(verbose: bool = False, jobs: int = 0) -> str:
     """Compile every source (in parallel, `jobs` at a time; 0 = one per CPU up
     to 16) and link libauxkf.so in place."""
     from concurrent.futures import ThreadPoolExecutor
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     jobs = jobs or max(1, min(16, os.cpu_count() or 1))
+    defines = {"akf_batch.cpp": [f'-DAKF_KERNEL_ID="{kernel_id()}"']}
     cmds, objs = [], []
     for src in SOURCES:
         obj = os.path.join(CSRC, src + ".o")
-        cmds.append([hipcc, *FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj])
+        cmds.append([hipcc, *FLAGS, *defines.get(src, []), "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     if verbose:
         for cmd in cmds:

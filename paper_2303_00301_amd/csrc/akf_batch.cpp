@@ -481,9 +481,14 @@ double time_candidate(const std::vector<akf_chain>& chains, ClassPlan cp, const 
   return ms;
 }
 
-// Cache key of a class: its team size and the shape of its batch (chain
-// count, lengths, the histograms of d_x, order and emission family).  Stored
-// as the leading fields of a cache line, before "block".
+// Cache key of a class: the kernels that were timed (a digest of their sources
+// and compiler flags: a choice made for other kernels is not theirs), its team
+// size and the shape of its batch (chain count, lengths, the histograms of d_x,
+// order and emission family).  Stored as the leading fields of a cache line,
+// before "block".
+#ifndef AKF_KERNEL_ID
+#error "AKF_KERNEL_ID: digest of the kernel sources and flags, defined by build.py"
+#endif
 std::string cache_key(const ClassPlan& cp, const std::vector<akf_chain>& chains) {
   long long sumN = 0;
   int maxN = 0;
@@ -498,6 +503,7 @@ std::string cache_key(const ClassPlan& cp, const std::vector<akf_chain>& chains)
   }
   std::string k;
   char buf[96];
+  k += "\"kernels\": \"" AKF_KERNEL_ID "\", ";
   snprintf(buf, sizeof buf, "\"D\": %d, \"chains\": %zu, \"sum_N\": %lld, \"max_N\": %d, \"dx\": \"",
            cp.D, cp.chains.size(), sumN, maxN);
   k += buf;
