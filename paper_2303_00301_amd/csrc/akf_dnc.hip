@@ -211,7 +211,6 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_dnc_root(KModel M, DncArgs A) {
   double* vz = vt + D;
   const int tid = threadIdx.x, d = M.d, T = A.T;
   RM<D> R;
-  double ld;
   rm_load<D>(R, A.Pf + (int64_t)T * A.ldm * A.ldm, A.ldm, d);
   bool ok = chol_reg<D>(R, d, scr);
   rm_stage<D>(R, B1);

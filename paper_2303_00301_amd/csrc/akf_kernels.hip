@@ -692,24 +692,6 @@ __global__ void __launch_bounds__(64 * GL_WAVES) k_lin_gauss(KModel M, StepArgs 
 // Shared pieces of the filter kernels
 // ---------------------------------------------------------------------------
 
-// S = P + Omega_t into LDS buffer s (diagonal Omega from om_diag, or the dense
-// constant Omega when dense != nullptr).  Team-wide; ends synchronised.
-template <int D>
-__device__ __forceinline__ void build_S(double* s, const RM<D>& P, const double* __restrict__ Om_t,
-                                        const double* __restrict__ dense, int d) {
-  rm_stage<D>(P, s);
-  team_sync();
-  const int tid = threadIdx.x;
-  if (dense) {
-    team_move<Cfg<D>::NT, D * D, 4>(
-        d * d, [&](int e) { return dense[e]; },
-        [&](int e, double v) { s[(e / d) * Cfg<D>::LD + (e % d)] += v; });
-  } else if (tid < d) {
-    s[tid * Cfg<D>::LD + tid] += Om_t[tid];
-  }
-  team_sync();
-}
-
 // Load a d x d user matrix into an LDS buffer, zero padded.
 // (A rolled loop: its callers sit in per-step loops that hold most of the
 // register file, where the unrolled form of lds_fill keeps its addresses live
@@ -733,13 +715,6 @@ __device__ __forceinline__ void lds_load_pad(double* s, const double* __restrict
     lds_fill<D, G>(s, [=](int i, int j) { return g[i * D + j]; });
   }
 }
-
-template <int D>
-__device__ __forceinline__ void vec_load(double* s, const double* __restrict__ g, int d) {
-  const int tid = threadIdx.x;
-  if (tid < D) s[tid] = (tid < d && g) ? g[tid] : 0.0;
-}
-
 
 // ---------------------------------------------------------------------------
 // Filter, phase 1: fold the elements of one block.
@@ -1433,6 +1408,7 @@ __global__ void __launch_bounds__(Cfg<D>::NT) k_filter_final(KModel M, FilterArg
 // ---------------------------------------------------------------------------
 template <int D, int U = 4>
 __device__ __forceinline__ void samp_build_impl(const KModel& M, const SampArgs& S, int item) {
+  static_assert(D == 64, "narrower teams are one wave (akf_wave.hpp)");
   // two LDS matrices (X, Y), so that two teams share a CU: both buffers serve
   // the inverse as scratch, and G = F P^f is formed again after it
   using C = Cfg<D>;
@@ -1473,13 +1449,13 @@ __device__ __forceinline__ void samp_build_impl(const KModel& M, const SampArgs&
     const double* bt = S.Ft ? S.bt + (int64_t)(t + 1) * d : M.b;
     rm_stage<D>(Pf, Y);
     team_sync();
-    // at D = 64 the first two products fully unrolled: the register budget
-    // allows it here (and the allocator then spills less than with U)
-    gemm<D, false, false, false, (D == 64 ? D / 4 : U)>(R1, X, Y);  // G = F P^f
+    // the first two products fully unrolled: the register budget allows it here
+    // (and the allocator then spills less than with U)
+    gemm<D, false, false, false, D / 4>(R1, X, Y);  // G = F P^f
     team_sync();
     rm_stage<D>(R1, Y);  // Y = G
     team_sync();
-    gemm<D, false, true, true, (D == 64 ? D / 4 : U)>(R2, Y, X);  // Q + G F'
+    gemm<D, false, true, true, D / 4>(R2, Y, X);  // Q + G F'
     matvec<D, false>(vmp, X, vm);
     if (tid < d && bt) vmp[tid] += bt[tid];
     {
@@ -1758,10 +1734,6 @@ __device__ __forceinline__ void mh_finalize_body(const KModel& M, const StepArgs
   }
 }
 
-__global__ void __launch_bounds__(256) k_mh_finalize(KModel M, StepArgs A, FinalArgs F) {
-  mh_finalize_body(M, A, F);
-}
-
 // One chain: the decision fused with the select.  Every workgroup forms the
 // same sums in the same order, hence the same decision; workgroup 0 writes the
 // outputs and clears the next step's status word; each workgroup writes its
@@ -1860,13 +1832,6 @@ __device__ __forceinline__ void mh_select_body(int64_t n, const double* __restri
   if (i < n) x_out[i] = (*accept_flag) ? xs[i] : x[i];
 }
 
-__global__ void __launch_bounds__(256) k_mh_select(int64_t n, const double* __restrict__ x,
-                                                   const double* __restrict__ xs,
-                                                   double* __restrict__ x_out,
-                                                   const int* __restrict__ accept_flag) {
-  mh_select_body(n, x, xs, x_out, accept_flag, blockIdx.x);
-}
-
 // ---------------------------------------------------------------------------
 // Host-side launch helpers (templated on D), used by akf_capi.cpp
 // ---------------------------------------------------------------------------
@@ -1931,8 +1896,6 @@ hipError_t launch_filter_scan(const KModel& M, FilterArgs P, const HsArgs* lv, i
   return hipGetLastError();
 }
 
-// log Z only: fold, then the up-sweep reduction of the block elements; the
-// root's normaliser is log p(omega_{0:N-1}).
 // compute units of the current device (queried once per process)
 static int compute_units() {
   static const int n = [] {
@@ -1945,6 +1908,8 @@ static int compute_units() {
   return n;
 }
 
+// log Z only: fold, then the up-sweep reduction of the block elements; the
+// root's normaliser is log p(omega_{0:N-1}).
 template <int D, int OBS>
 hipError_t launch_filter_logz(const KModel& M, FilterArgs P, const TreeArgs* up, int n_levels,
                               hipStream_t st) {
@@ -1953,7 +1918,10 @@ hipError_t launch_filter_logz(const KModel& M, FilterArgs P, const TreeArgs* up,
   timing_mark(FAM_FILTER_FOLD, 1, st);
   hipLaunchKernelGGL((k_filter_fold<D, OBS>), dim3(nb), dim3(Cfg<D>::NT), lds, st, M, P);
   timing_mark(FAM_FILTER_FOLD, 0, st);
-  // a level whose nodes fit on the chip twice runs each node on two workgroups
+  // a level with a CU for each of twice its nodes runs each node on two workgroups.
+  // (CUs are counted at every width.  Four one-wave teams share a CU, so at widths
+  // up to 32 the line is a cautious one: a level just above it takes 7.0 us against
+  // 4.9 just below at d = 3, 23.3 against 17.4 at d = 32.)
   const int n_cu = compute_units();
   for (int l = 0; l < n_levels; ++l) {
     timing_mark(FAM_FILTER_UP, 1, st);
@@ -2334,13 +2302,16 @@ __global__ void __launch_bounds__(Cfg<D>::NT, D == 64 ? 1 : D == 16 ? 3 : 2) kb_
     const ChainDev& c = L.cd[I.c];
     SampArgs S = c.S;
     S.xi_x = c.xi_base + (int64_t)s * c.xi_stride + (int64_t)c.M.N * c.M.d;
-    samp_build_body<D>(c.M, S, I.i);  // two teams per SIMD: the register budget keeps U = 4
+    samp_build_body<D>(c.M, S, I.i);
     __syncthreads();
   }
 }
 
-// the same with one team per SIMD and the whole register file: no spills and
-// fully unrolled products, half the teams (the autotuner times both layouts)
+// the same compiled for one team per SIMD and the whole register file, half the
+// teams.  The one-wave bodies fit two to a SIMD without spills, so they gain
+// nothing from it (128 ragged chains, blocks of 64: 17.1 ms a step against 16.5
+// with two); it is the other layout that a plan's cache line can name, and the
+// autotuner times both.
 template <int D>
 __global__ void __launch_bounds__(Cfg<D>::NT, 1) kb_sbuild1(BatchLaunch L, const int* step) {
   const int s = *step;

@@ -390,7 +390,9 @@ __device__ __forceinline__ double lane_fetch(double v, int src) {
 
 // 1/q for q > 0: the hardware reciprocal estimate (relative error e about
 // 2^-23) refined by one cubic step r <- r + r (e + e^2), e = 1 - q r: three
-// dependent operations where two Newton-Raphson steps take four.
+// dependent operations where two Newton-Raphson steps take four.  For 1/q in the
+// normal range (q below 2^1022); an infinite q, where a variance or a product of
+// two overflowed, gives NaN, not 0.
 __device__ __forceinline__ double recip(double q) {
   const double r = __builtin_amdgcn_rcp(q);
   const double e = fma(-q, r, 1.0);

@@ -122,7 +122,7 @@ __device__ __forceinline__ RV<D> rv(const double* s) {
   return o;
 }
 
-// lane l < D: (x' v)_l (plus add, a value of that lane); other lanes: unspecified
+// lane l < D: (x' v)_l; other lanes: unspecified
 template <int D, int KT = Cfg<D>::TS>
 __device__ __forceinline__ double mv(const RM<D>& x, const RV<D>& v) {
   constexpr int TS = Cfg<D>::TS;
