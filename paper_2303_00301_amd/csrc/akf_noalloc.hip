@@ -53,12 +53,13 @@ akf_status akf_mh_step_noalloc(const akf_model* model, const double* y, const do
   // size check first: an invalid model sizes to 0 and akf_mh_step reports why
   size_t need = akf_mh_workspace_bytes(model, order, block);
   // the default's blocks of two steps hold twice the elements of blocks of four:
-  // a problem that fits with those alone takes them
+  // a problem that fits with those alone takes them (a negative block is left for
+  // akf_mh_step to refuse)
   if (block <= 0 && need > (size_t)AKF_NOALLOC_SCRATCH_BYTES) {
     const size_t need4 = akf_mh_workspace_bytes(model, order, 4);
     if (need4 <= (size_t)AKF_NOALLOC_SCRATCH_BYTES) {
       need = need4;
-      block = 4;
+      if (block == 0) block = 4;
     }
   }
   if (need > (size_t)AKF_NOALLOC_SCRATCH_BYTES)
