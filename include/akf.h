@@ -191,9 +191,13 @@ akf_status akf_mh_run(const akf_model* model, const double* y, double* x, double
  * fixed array of AKF_NOALLOC_SCRATCH_BYTES bytes inside the library, one per
  * device (each device holds it until the process ends).  The call allocates
  * and frees nothing.
- *   - Limit: a problem whose akf_mh_workspace_bytes(model, order, block)
- *     exceeds AKF_NOALLOC_SCRATCH_BYTES returns AKF_ERR_SHAPE (64 MiB covers,
- *     e.g., dx = 8 at N = 1024, dx = 30 at N = 250, dx = 64 at N = 96).
+ *   - Limit: with block > 0, a problem whose akf_mh_workspace_bytes(model,
+ *     order, block) exceeds AKF_NOALLOC_SCRATCH_BYTES returns AKF_ERR_SHAPE.
+ *     With block = 0 the scan block is the default one where it fits and 4
+ *     otherwise (the default of a short, wide problem is 2, with twice the block
+ *     elements), and AKF_ERR_SHAPE is returned when neither fits: test
+ *     akf_mh_workspace_bytes with block 0 and with block 4.  64 MiB covers, e.g.,
+ *     dx = 8 at N = 1024, dx = 30 at N = 512, dx = 64 at N = 300.
  *   - Every call on one device shares that device's array: calls that may
  *     overlap on one device (other streams, other host threads) race; order
  *     them on one stream.  The array keeps the last call's contents; the step
