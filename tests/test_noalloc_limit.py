@@ -15,7 +15,7 @@ HEADER = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))
 def test_sizes_named_by_the_header():
     lib = _lib.load()
     text = re.sub(r"\s*\n \*\s*", " ", open(HEADER).read())
-    (rule,) = re.findall(r"With block = 0 the scan block is .*?\. 64 MiB covers, e\.g\., (.*?)\. ", text)
+    (rule,) = re.findall(r"With block = 0 the scan block is .*?\.\s+64 MiB covers, e\.g\., (.*?)\. ", text)
     sizes = [tuple(map(int, p)) for p in re.findall(r"dx = (\d+) at N = (\d+)", rule)]
     assert len(sizes) == 3
     by_default = 0
