@@ -306,11 +306,11 @@ __device__ __forceinline__ double dot(const T* x, const T* y, int d, double* red
 }
 
 // d = sqrt(p) and r = 1 / d, correctly rounded (zero for p <= 0; infinity and
-// zero for a pivot that overflowed):
-// scaled by a power of four into [1/4, 1), Goldschmidt's iteration from the
-// hardware estimates with Markstein's final corrections.  Half the length of
-// the library's square root followed by its division, and no branch, so that
-// the steps around it can be scheduled into its chain.
+// zero for a pivot that overflowed): scaled by a power of four into [1/2, 2),
+// Goldschmidt's iteration from the hardware estimates with Markstein's final
+// corrections.  Half the length of the library's square root followed by its
+// division, and no branch, so that the steps around it can be scheduled into its
+// chain.
 __device__ __forceinline__ void sqrt_and_rcp(double p, double& d, double& r) {
   const int e = __builtin_amdgcn_frexp_exp(p) & ~1;
   const double q = ldexp(p, -e);
