@@ -538,8 +538,9 @@ void akf_batch_plan_destroy(akf_batch_plan* plan);
  * Kernel timing, for diagnostics and benchmarks.  While enabled for `family`
  * (0 filter fold, 1 filter scan levels (Hillis-Steele levels for one chain,
  * up-sweep levels for batched chains), 2 filter down-sweep, 3 filter final,
- * 4 sampler element build, 5 sampler fold, 6 sampler up-sweep, 7 sampler
- * down-sweep, 8 sampler final, 9 factorised scalar filter/sampler,
+ * 4 sampler element build, 5 sampler fold, 6 sampler up-sweep (at team widths
+ * up to 32 the scan of the block aggregates), 7 sampler down-sweep (width 64
+ * and batched chains), 8 sampler final, 9 factorised scalar filter/sampler,
  * 10 emission and dynamics linearisation, 11 the whole divide-and-conquer
  * sampler, 12 and 13 the block folds of akf_mh_run_first_order's filtering
  * means and sampled path, 14 the adjoint's per-step gradient contractions,

@@ -44,10 +44,8 @@ def test_square_root_pivot_overflow(S, d):
     M = S.DeviceModel.from_arrays(1, np.zeros(d), np.diag(P0), 0.5 * np.eye(d), np.eye(d), 1)
     o = S.sqrt_filter_sample(M, T(om[None]), T(Om[None]), dtype="f64")
     assert int(o["status"][0]) == 0
-    gain = P0 / (P0 + Om)
-    gain[0] = 0.0
-    U = np.sqrt(P0 * Om / (P0 + Om))
-    U[0] = np.sqrt(P0[0])
+    gain = np.r_[0.0, P0[1:] / (P0[1:] + Om[1:])]
+    U = np.sqrt(np.r_[P0[0], P0[1:] * Om[1:] / (P0[1:] + Om[1:])])
     # a handful of roundings on each diagonal element
     np.testing.assert_allclose(o["mf"].cpu().numpy()[0], gain * om, rtol=1e-14, atol=0.0)
     np.testing.assert_allclose(o["Uf"].cpu().numpy()[0], np.diag(U), rtol=1e-14, atol=0.0)
